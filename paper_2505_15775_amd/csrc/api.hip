@@ -659,15 +659,15 @@ static void enqueue_inner_step(alm_bm_problem* p, int r, T* R, const double* y, 
     if (lb.s) {
       // L-BFGS: the direction E = H G and its line-search totals replace G's;
       // the line-search product gathers E in the ring type
-      launch_lbfgs_dots<T>((long)d.n * r, r, G, lb, p->part, p->nblk, sc, st);
-      launch_fin_lbfgs(p->part, p->nblk, sc, lb.s, st);
+      const int nbd = launch_lbfgs_dots<T>((long)d.n * r, r, p->lb_m, G, lb, p->part, p->nblk, sc, st);
+      launch_fin_lbfgs(p->part, nbd, p->lb_m, sc, lb.s, st);
       launch_lbfgs_combine<T>(d.n, r, p->variant, R, G, y, d.b, sigma, p->Av, lb, p->part, sc, p->nblk, st);
       launch_fin_lsdir(p->part, p->nblk, sc, lb.s, st);
       launch_quadq_diag<S>(cost_of<S>(p), r, p->variant, lb.e, Q, p->part_c2, sc, p->tab, p->nblk, st, lb);
     } else {
       launch_quadq_diag<T>(cost_of<T>(p), r, p->variant, G, Q, p->part_c2, sc, p->tab, p->nblk, st);
     }
-    launch_fin_step(p->part_c2, p->nblk, 1, sc, sigma, 0.0, 1, nullptr, nullptr, st, p->tab, p->count);
+    launch_fin_step(p->part_c2, p->nblk, sc, sigma, 1, nullptr, nullptr, st, p->tab, p->count);
   } else {
     enqueue_objgrad<T>(p, r, R, y, sigma, G, p->Av, sc, 1, nullptr, st);
     launch_edges_p3<T>(cost_of<T>(p), p->adj, r, p->variant, R, G, y, d.b, p->Av, p->part, sc, p->nblk, st,
@@ -780,7 +780,7 @@ extern "C" alm_bm_status alm_bm_gd_step(alm_bm_problem* p, int32_t r, void* R, c
     enqueue_objgrad<T>(p, r, Rt, y, sigma, Gt, p->Av, sc, 0, f, st);
     if (d.cons_kind == ALM_BM_CONS_DIAG) {
       launch_quad_diag<T>(cost_of<T>(p), r, p->variant, Gt, p->part_c2, sc, p->nblk, st);
-      launch_fin_step(p->part_c2, p->nblk, 1, sc, sigma, 0.0, 0, nullptr, t, st);
+      launch_fin_step(p->part_c2, p->nblk, sc, sigma, 0, nullptr, t, st);
     } else {
       launch_edges_p3<T>(cost_of<T>(p), p->adj, r, p->variant, Rt, Gt, y, d.b, p->Av, p->part, sc, p->nblk, st);
       launch_fin_edges3(p->part, p->nblk, r, sc, y, d.b, sigma, d.trace_coef, d.j_coef, 0, nullptr, t, st, p->part2);
@@ -2660,8 +2660,8 @@ static void batch_enqueue_step(alm_bm_batch* b, T* R, const double* y, double si
     // L-BFGS per instance: states, ring regions and partial slots follow the
     // block table, so one launch per width class covers every instance
     for (int c = 0; c < b->nclass; ++c)
-      launch_lbfgs_dots<T>(d.n, b->c_w[c], G, lb, p->part, b->c_nb[c], sc, st, batch_class_tab(b, c));
-    launch_fin_lbfgs(p->part, p->nblk, sc, lb.s, st, p->tab, p->count);
+      launch_lbfgs_dots<T>(d.n, b->c_w[c], p->lb_m, G, lb, p->part, b->c_nb[c], sc, st, batch_class_tab(b, c));
+    launch_fin_lbfgs(p->part, p->nblk, p->lb_m, sc, lb.s, st, p->tab, p->count);
     for (int c = 0; c < b->nclass; ++c)
       launch_lbfgs_combine<T>(d.n, b->c_w[c], b->c_var[c], R, G, y, d.b, sigma, p->Av, lb, p->part, sc,
                               b->c_nb[c], st, batch_class_tab(b, c));
@@ -2674,7 +2674,7 @@ static void batch_enqueue_step(alm_bm_batch* b, T* R, const double* y, double si
       launch_quadq_diag<T>(cost_of<T>(p), b->c_w[c], b->c_var[c], G, Q, p->part_c2, sc, batch_class_tab(b, c),
                            b->c_nb[c], st);
   }
-  launch_fin_step(p->part_c2, p->nblk, 1, sc, sigma, 0.0, 1, nullptr, nullptr, st, p->tab, p->count);
+  launch_fin_step(p->part_c2, p->nblk, sc, sigma, 1, nullptr, nullptr, st, p->tab, p->count);
 }
 
 // Objective pass (API mode, into sc_api) over the active instances.

@@ -129,6 +129,93 @@ __device__ __forceinline__ void block_sum_store(double (&acc)[NS], double* __res
   }
 }
 
+// Sums over the 64 lanes of a wave of P (a power of two up to 64) values per
+// lane, by halving: in each step a lane keeps one half of its values and adds
+// the partner's copy of that half, so P + 5 - log2 P double shuffles do the
+// work of 6 P.  Lane l ends with the total of value l / (64 / P) in v[0].
+template <int P, int BIT = kWave / 2>
+__device__ __forceinline__ double wave_sum_many(const double (&v)[P], int lane) {
+  if constexpr (P == 1) {
+    double x = v[0];
+#pragma unroll
+    for (int o = BIT; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
+    return x;
+  } else {
+    double w[P / 2];
+    const bool up = (lane & BIT) != 0;
+#pragma unroll
+    for (int k = 0; k < P / 2; ++k) {
+      const double keep = up ? v[k + P / 2] : v[k];
+      const double send = up ? v[k] : v[k + P / 2];
+      w[k] = keep + __shfl_xor(send, BIT, kWave);
+    }
+    return wave_sum_many<P / 2, BIT / 2>(w, lane);
+  }
+}
+
+// Deterministic block sum of NS <= 64 doubles per thread into out[0..NS) (the
+// many-slot counterpart of block_sum_store).
+template <int NS>
+__device__ __forceinline__ void block_sum_many(const double (&acc)[NS], double* __restrict__ out) {
+  constexpr int P = NS <= 16 ? 16 : (NS <= 32 ? 32 : 64);
+  __shared__ double red[kBlock / kWave][P];
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  double v[P];
+#pragma unroll
+  for (int s = 0; s < P; ++s) v[s] = s < NS ? acc[s] : 0.0;
+  const double x = wave_sum_many<P>(v, lane);
+  if (lane % (kWave / P) == 0) red[wave][lane / (kWave / P)] = x;
+  __syncthreads();
+  if (threadIdx.x < NS) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kBlock / kWave; ++w) t += red[w][threadIdx.x];
+    out[threadIdx.x] = t;
+  }
+}
+
+// Totals of a table of per-block partial sums, by one block of kFin threads:
+// out[s] (shared, NS doubles) = sum over the rows of part[row * NS + s].  The
+// table is read as one flat array, thread t taking elements t, t + A, ... with
+// A the largest multiple of NS up to kFin, so that loads are coalesced and a
+// thread stays on one column; kFinUnroll of them are in flight per thread.  A
+// wave then adds each column's A / NS threads.  Fixed order, independent of
+// timing.  Bound by the latency of one CU's loads: 4096 x 15 doubles took 18 us
+// with 256 threads walking rows (15 strided loads a row, 15 block reductions by
+// shuffles) and take 11 us this way.  Every thread of the block must call it.
+constexpr int kFin = 1024;
+constexpr int kFinUnroll = 16;
+template <int NS>
+__device__ __forceinline__ void fin_rows(const double* __restrict__ part, int rows, double* __restrict__ out) {
+  constexpr int A = kFin / NS * NS;
+  __shared__ double buf[A];
+  const int t = threadIdx.x;
+  const long len = (long)rows * NS;
+  if (t < A) {
+    double a = 0.0;
+    for (long k = t; k < len; k += (long)kFinUnroll * A) {
+      double v[kFinUnroll];
+#pragma unroll
+      for (int u = 0; u < kFinUnroll; ++u) v[u] = k + (long)u * A < len ? part[k + (long)u * A] : 0.0;
+#pragma unroll
+      for (int o = kFinUnroll / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < o; ++u) v[u] += v[u + o];
+      a += v[0];
+    }
+    buf[t] = a;
+  }
+  __syncthreads();
+  const int lane = t % kWave, wave = t / kWave;
+  for (int s = wave; s < NS; s += kFin / kWave) {
+    double a = 0.0;
+    for (int g = lane; g < A / NS; g += kWave) a += buf[g * NS + s];
+    a = wave_sum(a);
+    if (lane == 0) out[s] = a;
+  }
+  __syncthreads();
+}
+
 // Rows owned by this block: the row range is split into gridDim.x contiguous
 // chunks and blocks are renumbered so that the blocks the hardware sends to one
 // XCD (blockIdx % 8 equal) own one contiguous eighth of the rows; neighbour rows

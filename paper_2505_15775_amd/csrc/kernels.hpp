@@ -65,7 +65,8 @@ struct DevScalars {
 // of 4m times.
 constexpr int kMaxLbfgs = 8;
 constexpr int kLbfgsSlots = kMaxLbfgs + 1;   // ring slots of E and of y
-constexpr int kLbfgsDots = 5 * kLbfgsSlots;  // inner-product partial slots per block
+// inner-product partial slots per block of a kernel for up to M pairs
+constexpr int lbfgs_dot_slots(int M) { return 5 * (M + 1); }
 
 struct LbfgsState {
   int32_t m;                       // pairs kept (1..kMaxLbfgs)

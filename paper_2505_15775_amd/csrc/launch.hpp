@@ -31,14 +31,16 @@ void launch_upd_eval_diag(long n, int r, int variant, T* R, T* G, const typename
 // L-BFGS steps (lbfgs_kernels.hip).  Reset at the start of a subproblem.
 // Empty memories of m pairs for `count` instances (states s[0..count)).
 void launch_lbfgs_reset(LbfgsState* s, int m, hipStream_t st, int count = 1);
-// Inner products of the new gradient G and of y_k with the stored vectors
-// (len = n*r elements each without a table; with one, the rows of each block
-// at width r), per block of nb blocks into part[slot][kLbfgsDots].
+// Inner products of the new gradient G and of y_k with the stored vectors of a
+// memory of m pairs (len = n*r elements each without a table; with one, the
+// rows of each block at width r), lbfgs_dot_slots of them per block of at most
+// nb blocks; returns the blocks launched.
 template <typename T>
-void launch_lbfgs_dots(long len, int r, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
-                       const DevScalars* sc, hipStream_t st, const BlockTab& tab = BlockTab{});
-// Pair update and the coefficients of the next direction (one block per instance).
-void launch_fin_lbfgs(const double* part, int nb, const DevScalars* sc, LbfgsState* s, hipStream_t st,
+int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
+                      const DevScalars* sc, hipStream_t st, const BlockTab& tab = BlockTab{});
+// Pair update and the coefficients of the next direction (one block per
+// instance) from the partials of nb blocks.
+void launch_fin_lbfgs(const double* part, int nb, int m, const DevScalars* sc, LbfgsState* s, hipStream_t st,
                       const BlockTab& tab = BlockTab{}, int count = 1);
 // E = cg G + sum (ce E_a + cy y_a) into the current slot, and the quartic's
 // direction-dependent partial sums along -E (NUM_P per block).
@@ -80,9 +82,8 @@ void launch_fin_edges3(const double* part, int nb, int r, DevScalars* sc, const 
 
 void launch_fin_objgrad(const double* part, int nb, DevScalars* sc, double sigma, int mode, double* f_out,
                         hipStream_t st, const BlockTab& tab = BlockTab{}, int count = 1);
-void launch_fin_step(const double* part_c2, int nb, int c2_stride, DevScalars* sc, double sigma, double j_extra,
-                     int mode, double* coeffs_out, double* t_out, hipStream_t st, const BlockTab& tab = BlockTab{},
-                     int count = 1);
+void launch_fin_step(const double* part_c2, int nb, DevScalars* sc, double sigma, int mode, double* coeffs_out,
+                     double* t_out, hipStream_t st, const BlockTab& tab = BlockTab{}, int count = 1);
 void launch_dual_batch(long m, const double* Av, const double* b, const double* y_in, double* y_out, double sigma,
                        double* part, DevScalars* sc, const double* bnorms, const BlockTab& tab, int nb, int count,
                        hipStream_t st);

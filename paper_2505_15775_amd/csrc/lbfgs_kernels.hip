@@ -14,6 +14,8 @@
 //   k_fin_lsdir       their totals
 // then the line-search product C E and the step rule as for gradient descent.
 // Pure streaming kernels: no gathers, no MFMA.
+#include <algorithm>
+
 #include "spmm_row.hpp"
 
 namespace almbm {
@@ -42,10 +44,11 @@ __global__ void k_lbfgs_reset(LbfgsState* s, int m) {
 
 // ---- inner products ------------------------------------------------------------
 //
-// Partial slots per block, kLbfgsSlots each: G . E_a, G . y_a, y_k . E_a,
-// y_k . y_a for the held pairs a < cnt in set order at positions a and for the
-// current direction (E_k, y_k) at position kMaxLbfgs; then E_k . y_a (a < cnt).
-// The y_k and E_k products only when a direction was taken (have).
+// Partial slots per block, M + 1 each (M the template bound on the pairs held):
+// G . E_a, G . y_a, y_k . E_a, y_k . y_a for the held pairs a < cnt in set order
+// at positions a and for the current direction (E_k, y_k) at position M; then
+// E_k . y_a (a < cnt).  The y_k and E_k products only when a direction was
+// taken (have).
 
 template <typename T> struct FlatVec { static constexpr int N = 16 / sizeof(T); };
 
@@ -62,16 +65,15 @@ __device__ __forceinline__ void load_flat(const T* __restrict__ p, typename Acc<
   }
 }
 
-template <typename V> struct DotAcc {
-  V gE[kLbfgsSlots], gY[kLbfgsSlots], kE[kLbfgsSlots], kY[kLbfgsSlots], eY[kMaxLbfgs];
+template <typename V, int M> struct DotAcc {
+  V gE[M + 1], gY[M + 1], kE[M + 1], kY[M + 1], eY[M];
 };
 
 // NV consecutive elements at idx of every vector.
-template <typename T, int NV, typename S = RingT<T>>
-__device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type>& A, long idx, const T* __restrict__ G,
+template <typename T, int NV, int M, typename S = RingT<T>>
+__device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type, M>& A, long idx, const T* __restrict__ G,
                                            const S* __restrict__ yk, const S* __restrict__ ek,
-                                           const S* const (&ea)[kMaxLbfgs], const S* const (&ya)[kMaxLbfgs],
-                                           int cnt, bool have) {
+                                           const S* const (&ea)[M], const S* const (&ya)[M], int cnt, bool have) {
   using V = typename Acc<T>::type;
   V g[NV], y_k[NV], e_k[NV];
   load_flat<T, NV>(G + idx, g);
@@ -80,7 +82,7 @@ __device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type>& A, lon
     load_flat<S, NV>(ek + idx, e_k);
   }
 #pragma unroll
-  for (int a = 0; a < kMaxLbfgs; ++a) {
+  for (int a = 0; a < M; ++a) {
     if (a < cnt) {
       V ev[NV], yv[NV];
       load_flat<S, NV>(ea[a] + idx, ev);
@@ -103,10 +105,10 @@ __device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type>& A, lon
   if (have) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      A.gE[kMaxLbfgs] += g[v] * e_k[v];
-      A.gY[kMaxLbfgs] += g[v] * y_k[v];
-      A.kE[kMaxLbfgs] += y_k[v] * e_k[v];
-      A.kY[kMaxLbfgs] += y_k[v] * y_k[v];
+      A.gE[M] += g[v] * e_k[v];
+      A.gY[M] += g[v] * y_k[v];
+      A.kE[M] += y_k[v] * e_k[v];
+      A.kY[M] += y_k[v] * y_k[v];
     }
   }
 }
@@ -114,7 +116,13 @@ __device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type>& A, lon
 // Without a table the grid strides over all len elements.  With a table each
 // block takes the elements of its rows, [xbase + lo r, xbase + hi r) of its
 // instance (stored at width r), with the instance's own state and stop flag.
-template <typename T>
+//
+// Bound by HBM streaming (2 M + 3 vectors).  M bounds the pairs at compile
+// time: with the memory of 3 that solves use by default 19 accumulators remain
+// of the 44 of memory 8, and the block's sums take 32 shuffles instead of 270.
+// n = 193 176, r = 16, FP64, memory 3 (222 MB): 88 us with 44
+// accumulators on one block per 64 rows, 36 us (6.2 TB/s) now.
+template <typename T, int M>
 __global__ void __launch_bounds__(kBlock)
 k_lbfgs_dots(long len, int r, const T* __restrict__ G, LbfgsRing<RingT<T>> lb, double* __restrict__ part,
              const DevScalars* __restrict__ sc_base, BlockTab tab) {
@@ -137,43 +145,49 @@ k_lbfgs_dots(long len, int r, const T* __restrict__ G, LbfgsRing<RingT<T>> lb, d
   const bool have = S->have != 0;
   const R* yk = lb.y + (long)S->cur * lb.stride;
   const R* ek = lb.e + (long)S->cur * lb.stride;
-  const R* ea[kMaxLbfgs];
-  const R* ya[kMaxLbfgs];
+  const R* ea[M];
+  const R* ya[M];
 #pragma unroll
-  for (int a = 0; a < kMaxLbfgs; ++a) {
+  for (int a = 0; a < M; ++a) {
     const int sl = a < cnt ? S->ord[a] : 0;
     ea[a] = lb.e + (long)sl * lb.stride;
     ya[a] = lb.y + (long)sl * lb.stride;
   }
-  DotAcc<V> A;
+  DotAcc<V, M> A;
 #pragma unroll
-  for (int a = 0; a < kLbfgsSlots; ++a) A.gE[a] = A.gY[a] = A.kE[a] = A.kY[a] = V(0);
+  for (int a = 0; a <= M; ++a) A.gE[a] = A.gY[a] = A.kE[a] = A.kY[a] = V(0);
 #pragma unroll
-  for (int a = 0; a < kMaxLbfgs; ++a) A.eY[a] = V(0);
+  for (int a = 0; a < M; ++a) A.eY[a] = V(0);
   // element-wise head up to N-element alignment, N-element chunks, element-wise tail
   const long pad = (N - a % N) % N;
   const long a_al = a + pad < e ? a + pad : e;
-  for (long idx = a + t0; idx < a_al; idx += tstride) dots_chunk<T, 1>(A, idx, G, yk, ek, ea, ya, cnt, have);
+  for (long idx = a + t0; idx < a_al; idx += tstride) dots_chunk<T, 1, M>(A, idx, G, yk, ek, ea, ya, cnt, have);
   const long nvec = (e - a_al) / N;
-  for (long q = t0; q < nvec; q += tstride) dots_chunk<T, N>(A, a_al + q * N, G, yk, ek, ea, ya, cnt, have);
+  for (long q = t0; q < nvec; q += tstride) dots_chunk<T, N, M>(A, a_al + q * N, G, yk, ek, ea, ya, cnt, have);
   for (long idx = a_al + nvec * N + t0; idx < e; idx += tstride)
-    dots_chunk<T, 1>(A, idx, G, yk, ek, ea, ya, cnt, have);
-  double acc[kLbfgsDots];
+    dots_chunk<T, 1, M>(A, idx, G, yk, ek, ea, ya, cnt, have);
+  constexpr int ND = lbfgs_dot_slots(M);
+  double acc[ND];
 #pragma unroll
-  for (int a = 0; a < kLbfgsSlots; ++a) {
+  for (int a = 0; a <= M; ++a) {
     acc[a] = (double)A.gE[a];
-    acc[kLbfgsSlots + a] = (double)A.gY[a];
-    acc[2 * kLbfgsSlots + a] = (double)A.kE[a];
-    acc[3 * kLbfgsSlots + a] = (double)A.kY[a];
-    acc[4 * kLbfgsSlots + a] = a < kMaxLbfgs ? (double)A.eY[a] : 0.0;
+    acc[M + 1 + a] = (double)A.gY[a];
+    acc[2 * (M + 1) + a] = (double)A.kE[a];
+    acc[3 * (M + 1) + a] = (double)A.kY[a];
+    acc[4 * (M + 1) + a] = a < M ? (double)A.eY[a] : 0.0;
   }
-  block_sum_store<kLbfgsDots>(acc, part + part_slot(tab) * kLbfgsDots);
+  block_sum_many<ND>(acc, part + part_slot(tab) * ND);
 }
 
 // ---- pair update and the two-loop recursion on coefficients ----------------------
 
-// One block per instance (blockIdx.x; a single instance without a table).
-__global__ void __launch_bounds__(kBlock)
+// One block per instance (blockIdx.x; a single instance without a table).  M as
+// in k_lbfgs_dots: every loop over the pairs is unrolled to M and guarded, so
+// that thread 0's small matrices stay in registers (indexed by a run-time count
+// they would live in scratch memory).  Bound by latency; n = 193 176, r = 16,
+// memory 3: 51 us before, 10 us now (with the rows of fewer blocks to add).
+template <int M>
+__global__ void __launch_bounds__(kFin)
 k_fin_lbfgs(const double* __restrict__ part, int nb, const DevScalars* __restrict__ sc_base,
             LbfgsState* __restrict__ S_base, BlockTab tab) {
   const DevScalars* sc = sc_base + blockIdx.x;
@@ -181,62 +195,69 @@ k_fin_lbfgs(const double* __restrict__ part, int nb, const DevScalars* __restric
   if (sc->flag) return;
   int b0, b1;
   inst_blocks(tab, blockIdx.x, nb, b0, b1);
-  // fixed-order totals: thread t sums blocks b0 + t, b0 + t + kBlock, ..., then the block tree
-  double acc[kLbfgsDots];
-#pragma unroll
-  for (int k = 0; k < kLbfgsDots; ++k) acc[k] = 0.0;
-  for (int bi = b0 + threadIdx.x; bi < b1; bi += kBlock)
-#pragma unroll
-    for (int k = 0; k < kLbfgsDots; ++k) acc[k] += part[(long)bi * kLbfgsDots + k];
-  __shared__ double tot[kLbfgsDots];
-  block_sum_store<kLbfgsDots>(acc, tot);
-  __syncthreads();
+  constexpr int ND = lbfgs_dot_slots(M);
+  __shared__ double tot[ND];
+  fin_rows<ND>(part + (long)b0 * ND, b1 - b0, tot);
   if (threadIdx.x != 0) return;
   const double* gE = tot;
-  const double* gY = tot + kLbfgsSlots;
-  const double* kE = tot + 2 * kLbfgsSlots;
-  const double* kY = tot + 3 * kLbfgsSlots;
-  const double* eY = tot + 4 * kLbfgsSlots;
+  const double* gY = tot + (M + 1);
+  const double* kE = tot + 2 * (M + 1);
+  const double* kY = tot + 3 * (M + 1);
+  const double* eY = tot + 4 * (M + 1);
   const int m = S->m;
   int c = S->cnt;
   const int cur = S->cur;
   const double t = sc->t;  // the step just taken along E_k
-  // products of G with the held pairs, in set order after the update below
-  double gsE[kMaxLbfgs], gsY[kMaxLbfgs];
-  for (int a = 0; a < c; ++a) {
+  // the held pairs in set order: slots, steps, Gram matrices, products with G
+  int ord[M];
+  double tp[M], SY[M][M], YY[M][M], gsE[M], gsY[M];
+#pragma unroll
+  for (int a = 0; a < M; ++a) {
+    const bool in = a < c;
+    ord[a] = in ? S->ord[a] : 0;
+    tp[a] = in ? S->tp[ord[a]] : 0.0;
     gsE[a] = gE[a];
     gsY[a] = gY[a];
+#pragma unroll
+    for (int b = 0; b < M; ++b) {
+      SY[a][b] = in && b < c ? S->SY[a][b] : 0.0;
+      YY[a][b] = in && b < c ? S->YY[a][b] : 0.0;
+    }
   }
   int next = cur;
+  bool taken = false;
   if (S->have) {
     if (!(t > 0.0)) {
       // a zero step: clear the memory, the next direction is the gradient
       c = 0;
       S->resets += 1;
     } else {
-      const double sy = -t * kE[kMaxLbfgs];  // s_k . y_k with s_k = -t E_k
+      const double sy = -t * kE[M];  // s_k . y_k with s_k = -t E_k
       const double ss = t * t * S->ee;
-      const double yy = kY[kMaxLbfgs];
+      const double yy = kY[M];
       if (sy > 1e-12 * sqrt(ss) * sqrt(yy)) {
-        double col[kMaxLbfgs], row[kMaxLbfgs], yrow[kMaxLbfgs];
-        for (int a = 0; a < c; ++a) {
-          col[a] = -S->tp[S->ord[a]] * kE[a];  // s_a . y_k
-          row[a] = -t * eY[a];                 // s_k . y_a
-          yrow[a] = kY[a];                     // y_k . y_a
+        double col[M], row[M], yrow[M];
+#pragma unroll
+        for (int a = 0; a < M; ++a) {
+          col[a] = -tp[a] * kE[a];  // s_a . y_k
+          row[a] = -t * eY[a];      // s_k . y_a
+          yrow[a] = kY[a];          // y_k . y_a
         }
-        const double gE_new = gE[kMaxLbfgs], gY_new = gY[kMaxLbfgs];
         if (c == m) {  // drop the oldest pair
-          next = S->ord[0];
-          for (int a = 0; a + 1 < c; ++a) {
-            S->ord[a] = S->ord[a + 1];
+          next = ord[0];
+#pragma unroll
+          for (int a = 0; a + 1 < M; ++a) {
+            ord[a] = ord[a + 1];
+            tp[a] = tp[a + 1];
             gsE[a] = gsE[a + 1];
             gsY[a] = gsY[a + 1];
             col[a] = col[a + 1];
             row[a] = row[a + 1];
             yrow[a] = yrow[a + 1];
-            for (int b = 0; b + 1 < c; ++b) {
-              S->SY[a][b] = S->SY[a + 1][b + 1];
-              S->YY[a][b] = S->YY[a + 1][b + 1];
+#pragma unroll
+            for (int b = 0; b + 1 < M; ++b) {
+              SY[a][b] = SY[a + 1][b + 1];
+              YY[a][b] = YY[a + 1][b + 1];
             }
           }
           c -= 1;
@@ -244,67 +265,100 @@ k_fin_lbfgs(const double* __restrict__ part, int nb, const DevScalars* __restric
           // first slot held by no pair and not the current one
           for (int sl = 0; sl < kLbfgsSlots; ++sl) {
             bool used = sl == cur;
-            for (int a = 0; a < c; ++a) used = used || S->ord[a] == sl;
+#pragma unroll
+            for (int a = 0; a < M; ++a) used = used || (a < c && ord[a] == sl);
             if (!used) {
               next = sl;
               break;
             }
           }
         }
-        S->tp[cur] = t;
-        S->ord[c] = cur;
-        for (int a = 0; a < c; ++a) {
-          S->SY[a][c] = col[a];
-          S->SY[c][a] = row[a];
-          S->YY[a][c] = S->YY[c][a] = yrow[a];
+#pragma unroll
+        for (int d = 0; d < M; ++d) {
+          if (d != c) continue;  // the new pair's position
+          ord[d] = cur;
+          tp[d] = t;
+          gsE[d] = gE[M];
+          gsY[d] = gY[M];
+#pragma unroll
+          for (int a = 0; a < M; ++a) {
+            if (a >= c) continue;
+            SY[a][d] = col[a];
+            SY[d][a] = row[a];
+            YY[a][d] = YY[d][a] = yrow[a];
+          }
+          SY[d][d] = sy;
+          YY[d][d] = yy;
         }
-        S->SY[c][c] = sy;
-        S->YY[c][c] = yy;
-        gsE[c] = gE_new;
-        gsY[c] = gY_new;
+        S->tp[cur] = t;
         c += 1;
         S->accepted += 1;
+        taken = true;
+      }
+    }
+  }
+  if (taken) {
+#pragma unroll
+    for (int a = 0; a < M; ++a) {
+      if (a >= c) continue;
+      S->ord[a] = ord[a];
+#pragma unroll
+      for (int b = 0; b < M; ++b) {
+        if (b >= c) continue;
+        S->SY[a][b] = SY[a][b];
+        S->YY[a][b] = YY[a][b];
       }
     }
   }
   // two-loop recursion on the coefficients of q = H G in {G, y_a, s_a}
-  double gs[kMaxLbfgs], rho[kMaxLbfgs], alpha[kMaxLbfgs], qy[kMaxLbfgs], rs[kMaxLbfgs];
-  for (int a = 0; a < c; ++a) {
-    gs[a] = -S->tp[S->ord[a]] * gsE[a];
-    rho[a] = 1.0 / S->SY[a][a];
-    qy[a] = 0.0;
-    rs[a] = 0.0;
+  double gs[M], rho[M], alpha[M], qy[M], rs[M];
+  double gam = 1.0;
+#pragma unroll
+  for (int a = 0; a < M; ++a) {
+    const bool in = a < c;
+    gs[a] = in ? -tp[a] * gsE[a] : 0.0;
+    rho[a] = in ? 1.0 / SY[a][a] : 0.0;
+    qy[a] = rs[a] = alpha[a] = 0.0;
+    if (a == c - 1) gam = SY[a][a] / YY[a][a];
   }
-  for (int a = c - 1; a >= 0; --a) {
+#pragma unroll
+  for (int a = M - 1; a >= 0; --a) {
+    if (a >= c) continue;
     double sq = gs[a];
-    for (int b = 0; b < c; ++b) sq += qy[b] * S->SY[a][b];
+#pragma unroll
+    for (int b = 0; b < M; ++b)
+      if (b < c) sq += qy[b] * SY[a][b];
     alpha[a] = rho[a] * sq;
     qy[a] -= alpha[a];
   }
-  const double gam = c > 0 ? S->SY[c - 1][c - 1] / S->YY[c - 1][c - 1] : 1.0;
   const double rg = gam;
-  for (int b = 0; b < c; ++b) qy[b] *= gam;
-  for (int a = 0; a < c; ++a) {
+#pragma unroll
+  for (int b = 0; b < M; ++b) qy[b] *= gam;
+#pragma unroll
+  for (int a = 0; a < M; ++a) {
+    if (a >= c) continue;
     double yr = rg * gsY[a];
-    for (int b = 0; b < c; ++b) yr += qy[b] * S->YY[a][b] + rs[b] * S->SY[b][a];
+#pragma unroll
+    for (int b = 0; b < M; ++b)
+      if (b < c) yr += qy[b] * YY[a][b] + rs[b] * SY[b][a];
     const double beta = rho[a] * yr;
     rs[a] += alpha[a] - beta;
   }
   // descent test E . G > 0 from the same products
   double eg = rg * sc->tot[P_GG];
-  for (int a = 0; a < c; ++a) eg += qy[a] * gsY[a] + rs[a] * gs[a];
+#pragma unroll
+  for (int a = 0; a < M; ++a)
+    if (a < c) eg += qy[a] * gsY[a] + rs[a] * gs[a];
   if (c > 0 && !(eg > 0.0)) {
     c = 0;
     S->resets += 1;
   }
-  if (c == 0) {
-    S->cg = 1.0;
-  } else {
-    S->cg = rg;
-    for (int a = 0; a < c; ++a) {
-      S->cy[a] = qy[a];
-      S->ce[a] = -S->tp[S->ord[a]] * rs[a];
-    }
+  S->cg = c == 0 ? 1.0 : rg;
+#pragma unroll
+  for (int a = 0; a < M; ++a) {
+    if (a >= c) continue;
+    S->cy[a] = qy[a];
+    S->ce[a] = -tp[a] * rs[a];
   }
   S->cnt = c;
   S->cur = next;
@@ -383,7 +437,7 @@ k_lbfgs_combine(long n, int r, const T* __restrict__ R, const T* __restrict__ G,
   acc.block_store(lane, part + part_slot(tab) * NUM_P);
 }
 
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kFin)
 k_fin_lsdir(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc_base, LbfgsState* __restrict__ S_base,
             BlockTab tab) {
   DevScalars* sc = sc_base + blockIdx.x;
@@ -391,20 +445,14 @@ k_fin_lsdir(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc
   if (sc->flag) return;
   int b0, b1;
   inst_blocks(tab, blockIdx.x, nb, b0, b1);
+  __shared__ double tot[NUM_P];
+  fin_rows<NUM_P>(part + (long)b0 * NUM_P, b1 - b0, tot);
+  if (threadIdx.x != 0) return;
   constexpr int K = 10;
   const int sl[K] = {P_GG, P_GP, P_YA1, P_YA2, P_EA1, P_EA2, P_A1A1, P_A1A2, P_A2A2, P_RG};
-  double acc[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) acc[k] = 0.0;
-  for (int bi = b0 + threadIdx.x; bi < b1; bi += kBlock)
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] += part[(long)bi * NUM_P + sl[k]];
-  __shared__ double tot[K];
-  block_sum_store<K>(acc, tot);
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int k = 0; k < K; ++k) sc->tot[sl[k]] = tot[k];
-  S->ee = tot[0];
+  for (int k = 0; k < K; ++k) sc->tot[sl[k]] = tot[sl[k]];
+  S->ee = tot[P_GG];
 }
 
 // ---- launchers ---------------------------------------------------------------------
@@ -413,15 +461,31 @@ void launch_lbfgs_reset(LbfgsState* s, int m, hipStream_t st, int count) {
   hipLaunchKernelGGL(k_lbfgs_reset, dim3(count), dim3(64), 0, st, s, m);
 }
 
-template <typename T>
-void launch_lbfgs_dots(long len, int r, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
-                       const DevScalars* sc, hipStream_t st, const BlockTab& tab) {
-  hipLaunchKernelGGL((k_lbfgs_dots<T>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab);
+// Blocks of the inner-product pass over len elements without a table: four
+// vector chunks per thread and at most eight blocks per CU, so that the block
+// sums and the finalizer's rows stay few.
+template <typename T> static int dots_blocks(long len, int cap) {
+  const long nb = (len / FlatVec<T>::N + 4 * kBlock - 1) / (4 * kBlock);
+  return (int)std::min<long>(std::min(cap, 2048), std::max<long>(8, nb));
 }
 
-void launch_fin_lbfgs(const double* part, int nb, const DevScalars* sc, LbfgsState* s, hipStream_t st,
+template <typename T>
+int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
+                      const DevScalars* sc, hipStream_t st, const BlockTab& tab) {
+  if (!tab.inst) nb = dots_blocks<T>(len, nb);
+  if (m <= 3)
+    hipLaunchKernelGGL((k_lbfgs_dots<T, 3>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab);
+  else
+    hipLaunchKernelGGL((k_lbfgs_dots<T, kMaxLbfgs>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab);
+  return nb;
+}
+
+void launch_fin_lbfgs(const double* part, int nb, int m, const DevScalars* sc, LbfgsState* s, hipStream_t st,
                       const BlockTab& tab, int count) {
-  hipLaunchKernelGGL(k_fin_lbfgs, dim3(count), dim3(kBlock), 0, st, part, nb, sc, s, tab);
+  if (m <= 3)
+    hipLaunchKernelGGL(k_fin_lbfgs<3>, dim3(count), dim3(kFin), 0, st, part, nb, sc, s, tab);
+  else
+    hipLaunchKernelGGL(k_fin_lbfgs<kMaxLbfgs>, dim3(count), dim3(kFin), 0, st, part, nb, sc, s, tab);
 }
 
 template <typename T, int LPR, int VEC>
@@ -445,12 +509,12 @@ void launch_lbfgs_combine(long n, int r, int variant, const T* R, const T* G, co
 
 void launch_fin_lsdir(const double* part, int nb, DevScalars* sc, LbfgsState* s, hipStream_t st,
                       const BlockTab& tab, int count) {
-  hipLaunchKernelGGL(k_fin_lsdir, dim3(count), dim3(kBlock), 0, st, part, nb, sc, s, tab);
+  hipLaunchKernelGGL(k_fin_lsdir, dim3(count), dim3(kFin), 0, st, part, nb, sc, s, tab);
 }
 
 #define ALMBM_LBFGS_INST(T)                                                                               \
-  template void launch_lbfgs_dots<T>(long, int, const T*, const LbfgsRing<RingT<T>>&, double*, int,       \
-                                     const DevScalars*, hipStream_t, const BlockTab&);                     \
+  template int launch_lbfgs_dots<T>(long, int, int, const T*, const LbfgsRing<RingT<T>>&, double*, int,    \
+                                    const DevScalars*, hipStream_t, const BlockTab&);                      \
   template void launch_lbfgs_combine<T>(long, int, int, const T*, const T*, const double*, const double*,   \
                                         double, const double*, const LbfgsRing<RingT<T>>&, double*,          \
                                         const DevScalars*, int, hipStream_t, const BlockTab&);

@@ -7,25 +7,6 @@
 
 namespace almbm {
 
-// ---- deterministic reduction of per-block partials ---------------------------
-// part is [nb][NS]; thread t sums blocks t, t+256, ... in order, then the block
-// tree is fixed, so the total does not depend on timing.
-template <int NS>
-__device__ void reduce_partials(const double* __restrict__ part, int b0, int b1, int stride, double* __restrict__ out) {
-  double acc[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) acc[s] = 0.0;
-  for (int bi = b0 + threadIdx.x; bi < b1; bi += kBlock) {
-#pragma unroll
-    for (int s = 0; s < NS; ++s) acc[s] += part[(long)bi * stride + s];
-  }
-  __shared__ double res[NS];
-  block_sum_store<NS>(acc, res);
-  __syncthreads();
-  if (threadIdx.x < NS) out[threadIdx.x] = res[threadIdx.x];
-  __syncthreads();
-}
-
 __device__ __forceinline__ bool finite(double x) { return isfinite(x); }
 
 // ---- finalize kernels (one block) ------------------------------------------------
@@ -34,7 +15,7 @@ __device__ __forceinline__ bool finite(double x) { return isfinite(x); }
 // mode 1: inner loop step 1 -- after max_inner steps stop (flag 2), else the
 // stop test ||G|| ||R|| <= tol (1 + |<C,RR^T>|) (flag 1), else count the step.
 // One block per instance (blockIdx.x; a single instance without a table).
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kFin)
 k_fin_objgrad(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc_base, double sigma, int mode,
               double* __restrict__ f_out, BlockTab tab) {
   const int q = blockIdx.x;
@@ -43,10 +24,10 @@ k_fin_objgrad(const double* __restrict__ part, int nb, DevScalars* __restrict__ 
   int b0, b1;
   inst_blocks(tab, q, nb, b0, b1);
   __shared__ double tot[NUM_P];
-  reduce_partials<NUM_P>(part, b0, b1, NUM_P, tot);
+  fin_rows<NUM_P>(part + (long)b0 * NUM_P, b1 - b0, tot);
+  if (threadIdx.x < NUM_P) sc->tot[threadIdx.x] = tot[threadIdx.x];
   if (threadIdx.x != 0) return;
   if (f_out) f_out += q;
-  for (int s = 0; s < NUM_P; ++s) sc->tot[s] = tot[s];
   const double f = tot[P_C0] + tot[P_YBMA] + 0.5 * sigma * tot[P_EE];
   sc->f = f;
   if (!finite(f) || !finite(tot[P_GG])) sc->numeric_error = 1;
@@ -65,18 +46,17 @@ k_fin_objgrad(const double* __restrict__ part, int nb, DevScalars* __restrict__ 
 
 // Step rule: reduce the <G, CG> partials into tot[P_C2], form the quartic and
 // pick t.  mode 0: API (coeffs/t to the given pointers).  mode 1: inner loop.
-__global__ void __launch_bounds__(kBlock)
-k_fin_step(const double* __restrict__ part_c2, int nb, int c2_stride, DevScalars* __restrict__ sc_base, double sigma,
-           double j_extra_c2, int mode, double* __restrict__ coeffs_out, double* __restrict__ t_out, BlockTab tab) {
+__global__ void __launch_bounds__(kFin)
+k_fin_step(const double* __restrict__ part_c2, int nb, DevScalars* __restrict__ sc_base, double sigma, int mode, double* __restrict__ coeffs_out, double* __restrict__ t_out, BlockTab tab) {
   const int q = blockIdx.x;
   DevScalars* sc = sc_base + q;
   if (mode == 1 && sc->flag) return;
   int b0, b1;
   inst_blocks(tab, q, nb, b0, b1);
   __shared__ double c2[1];
-  if (part_c2) reduce_partials<1>(part_c2, b0, b1, c2_stride, c2);
+  fin_rows<1>(part_c2 + b0, b1 - b0, c2);
   if (threadIdx.x != 0) return;
-  if (part_c2) sc->tot[P_C2] = c2[0] + j_extra_c2;
+  sc->tot[P_C2] = c2[0];
   double k[5];
   quartic_coeffs(sc->tot, sigma, k);
   for (int s = 0; s < 5; ++s) sc->coeffs[s] = k[s];
@@ -92,15 +72,15 @@ k_fin_step(const double* __restrict__ part_c2, int nb, int c2_stride, DevScalars
 }
 
 // Full reduction of all NUM_P partials (API line search), then the step.
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kFin)
 k_fin_ls(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc, double sigma,
          double* __restrict__ coeffs_out, double* __restrict__ t_out) {
   __shared__ double tot[NUM_P];
-  reduce_partials<NUM_P>(part, 0, nb, NUM_P, tot);
+  fin_rows<NUM_P>(part, nb, tot);
+  if (threadIdx.x < NUM_P) sc->tot[threadIdx.x] = tot[threadIdx.x];
   if (threadIdx.x != 0) return;
-  for (int s = 0; s < NUM_P; ++s) sc->tot[s] = tot[s];
   double k[5];
-  quartic_coeffs(sc->tot, sigma, k);
+  quartic_coeffs(tot, sigma, k);
   const double t = quartic_argmin(k);
   for (int s = 0; s < 5; ++s) sc->coeffs[s] = k[s];
   sc->t = t;
@@ -148,7 +128,7 @@ k_dual(long m, const double* __restrict__ Av, const double* __restrict__ b, cons
   block_sum_store<2>(acc, part + (long)blockIdx.x * 2);
 }
 
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kFin)
 k_fin_dual(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc_base, double bnorm,
            const double* __restrict__ bnorms, double* __restrict__ pinf_out, BlockTab tab) {
   const int q = blockIdx.x;
@@ -157,7 +137,7 @@ k_fin_dual(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc_
   int b0, b1;
   inst_blocks(tab, q, nb, b0, b1);
   __shared__ double tot[2];
-  reduce_partials<2>(part, b0, b1, 2, tot);
+  fin_rows<2>(part + (long)b0 * 2, b1 - b0, tot);
   if (threadIdx.x != 0) return;
   if (pinf_out) pinf_out += q;
   sc->res2 = tot[0];
@@ -276,16 +256,16 @@ __global__ void __launch_bounds__(kBlock) k_convert(long len, const S* __restric
 
 void launch_fin_objgrad(const double* part, int nb, DevScalars* sc, double sigma, int mode, double* f_out,
                         hipStream_t st, const BlockTab& tab, int count) {
-  hipLaunchKernelGGL(k_fin_objgrad, dim3(count), dim3(kBlock), 0, st, part, nb, sc, sigma, mode, f_out, tab);
+  hipLaunchKernelGGL(k_fin_objgrad, dim3(count), dim3(kFin), 0, st, part, nb, sc, sigma, mode, f_out, tab);
 }
-void launch_fin_step(const double* part_c2, int nb, int c2_stride, DevScalars* sc, double sigma, double j_extra,
-                     int mode, double* coeffs_out, double* t_out, hipStream_t st, const BlockTab& tab, int count) {
-  hipLaunchKernelGGL(k_fin_step, dim3(count), dim3(kBlock), 0, st, part_c2, nb, c2_stride, sc, sigma, j_extra, mode,
-                     coeffs_out, t_out, tab);
+void launch_fin_step(const double* part_c2, int nb, DevScalars* sc, double sigma, int mode, double* coeffs_out,
+                     double* t_out, hipStream_t st, const BlockTab& tab, int count) {
+  hipLaunchKernelGGL(k_fin_step, dim3(count), dim3(kFin), 0, st, part_c2, nb, sc, sigma, mode, coeffs_out, t_out,
+                     tab);
 }
 void launch_fin_ls(const double* part, int nb, DevScalars* sc, double sigma, double* coeffs_out, double* t_out,
                    hipStream_t st) {
-  hipLaunchKernelGGL(k_fin_ls, dim3(1), dim3(kBlock), 0, st, part, nb, sc, sigma, coeffs_out, t_out);
+  hipLaunchKernelGGL(k_fin_ls, dim3(1), dim3(kFin), 0, st, part, nb, sc, sigma, coeffs_out, t_out);
 }
 static int elem_blocks(long len) {
   long nb = (len + kBlock * 4 - 1) / (kBlock * 4);
@@ -313,13 +293,13 @@ void launch_dual(long m, const double* Av, const double* b, const double* y_in, 
   if (!(sigma_tail > 0.0)) sigma_tail = sigma;
   hipLaunchKernelGGL(k_dual, dim3(nb), dim3(kBlock), 0, st, m, Av, b, y_in, y_out, sigma, sigma_tail, part,
                      BlockTab{});
-  hipLaunchKernelGGL(k_fin_dual, dim3(1), dim3(kBlock), 0, st, part, nb, sc, bnorm, nullptr, pinf_out, BlockTab{});
+  hipLaunchKernelGGL(k_fin_dual, dim3(1), dim3(kFin), 0, st, part, nb, sc, bnorm, nullptr, pinf_out, BlockTab{});
 }
 void launch_dual_batch(long m, const double* Av, const double* b, const double* y_in, double* y_out, double sigma,
                        double* part, DevScalars* sc, const double* bnorms, const BlockTab& tab, int nb, int count,
                        hipStream_t st) {
   hipLaunchKernelGGL(k_dual, dim3(nb), dim3(kBlock), 0, st, m, Av, b, y_in, y_out, sigma, sigma, part, tab);
-  hipLaunchKernelGGL(k_fin_dual, dim3(count), dim3(kBlock), 0, st, part, nb, sc, 0.0, bnorms, nullptr, tab);
+  hipLaunchKernelGGL(k_fin_dual, dim3(count), dim3(kFin), 0, st, part, nb, sc, 0.0, bnorms, nullptr, tab);
 }
 void launch_inner_reset(DevScalars* sc, double tol, int max_inner, int step_rule, double eta, hipStream_t st) {
   hipLaunchKernelGGL(k_inner_reset, dim3(1), dim3(64), 0, st, sc, tol, max_inner, step_rule, eta);
