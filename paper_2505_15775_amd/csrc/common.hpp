@@ -57,6 +57,37 @@ template <> struct VecWord<16> { using type = uint4; };
 template <> struct VecWord<32> { struct type { uint4 a, b; }; };
 template <> struct VecWord<64> { struct type { uint4 a, b, c, d; }; };
 
+// The first m (any int) of N elements at p, aligned to one element only, with
+// the widest accesses that fit: all N at once when m >= N, else the two halves.
+// Global accesses need no more than that alignment here; the copies leave the
+// choice of instruction to the compiler.
+template <typename T, int N>
+__device__ __forceinline__ void load_some(const T* __restrict__ p, int m, typename Acc<T>::type* out) {
+  if (m >= N) {
+    T e[N];
+    __builtin_memcpy(e, p, N * sizeof(T));
+#pragma unroll
+    for (int v = 0; v < N; ++v) out[v] = to_acc<T>(e[v]);
+  } else if constexpr (N > 1) {
+    load_some<T, N / 2>(p, m, out);
+    load_some<T, N / 2>(p + N / 2, m - N / 2, out + N / 2);
+  } else {
+    out[0] = typename Acc<T>::type(0);
+  }
+}
+template <typename T, int N>
+__device__ __forceinline__ void store_some(T* __restrict__ p, int m, const typename Acc<T>::type* in) {
+  if (m >= N) {
+    T e[N];
+#pragma unroll
+    for (int v = 0; v < N; ++v) e[v] = from_acc<T>(in[v]);
+    __builtin_memcpy(p, e, N * sizeof(T));
+  } else if constexpr (N > 1) {
+    store_some<T, N / 2>(p, m, in);
+    store_some<T, N / 2>(p + N / 2, m - N / 2, in + N / 2);
+  }
+}
+
 template <typename T, int VEC, bool FULL>
 __device__ __forceinline__ void load_frag(const T* __restrict__ row, int lane, int r,
                                           typename Acc<T>::type (&out)[VEC]) {
@@ -67,11 +98,7 @@ __device__ __forceinline__ void load_frag(const T* __restrict__ row, int lane, i
 #pragma unroll
     for (int v = 0; v < VEC; ++v) out[v] = to_acc<T>(e[v]);
   } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-      int c = lane * VEC + v;
-      out[v] = (c < r) ? to_acc<T>(row[c]) : typename Acc<T>::type(0);
-    }
+    load_some<T, VEC>(row + lane * VEC, r - lane * VEC, out);
   }
 }
 
@@ -86,11 +113,7 @@ __device__ __forceinline__ void store_frag(T* __restrict__ row, int lane, int r,
     for (int v = 0; v < VEC; ++v) e[v] = from_acc<T>(in[v]);
     *reinterpret_cast<W*>(row + lane * VEC) = w;
   } else {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-      int c = lane * VEC + v;
-      if (c < r) row[c] = from_acc<T>(in[v]);
-    }
+    store_some<T, VEC>(row + lane * VEC, r - lane * VEC, in);
   }
 }
 
@@ -129,35 +152,42 @@ __device__ __forceinline__ void block_sum_store(double (&acc)[NS], double* __res
   }
 }
 
-// Sums over the 64 lanes of a wave of P (a power of two up to 64) values per
-// lane, by halving: in each step a lane keeps one half of its values and adds
-// the partner's copy of that half, so P + 5 - log2 P double shuffles do the
-// work of 6 P.  Lane l ends with the total of value l / (64 / P) in v[0].
-template <int P, int BIT = kWave / 2>
-__device__ __forceinline__ double wave_sum_many(const double (&v)[P], int lane) {
+// Sums of P (a power of two) values per lane over the lanes of a wave that
+// agree in l % LOW, by halving: in each step a lane keeps one half of its values
+// and adds the partner's copy of that half, so that P + log2(64 / LOW) - log2 P
+// shuffles do the work of P log2(64 / LOW).  Needs P <= 64 / LOW.  Lane l ends
+// with the total of value l / (64 / P).
+template <int P, int LOW = 1, int BIT = kWave / 2, typename V>
+__device__ __forceinline__ V wave_sum_many(const V (&v)[P], int lane) {
   if constexpr (P == 1) {
-    double x = v[0];
+    V x = v[0];
 #pragma unroll
-    for (int o = BIT; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
+    for (int o = BIT; o >= LOW; o >>= 1) x += __shfl_xor(x, o, kWave);
     return x;
   } else {
-    double w[P / 2];
+    static_assert(BIT >= LOW, "more values than lanes to spread them over");
+    V w[P / 2];
     const bool up = (lane & BIT) != 0;
 #pragma unroll
     for (int k = 0; k < P / 2; ++k) {
-      const double keep = up ? v[k + P / 2] : v[k];
-      const double send = up ? v[k] : v[k + P / 2];
+      const V keep = up ? v[k + P / 2] : v[k];
+      const V send = up ? v[k] : v[k + P / 2];
       w[k] = keep + __shfl_xor(send, BIT, kWave);
     }
-    return wave_sum_many<P / 2, BIT / 2>(w, lane);
+    return wave_sum_many<P / 2, LOW, BIT / 2>(w, lane);
   }
+}
+constexpr int pow2_at_least(int x) {
+  int p = 1;
+  while (p < x) p *= 2;
+  return p;
 }
 
 // Deterministic block sum of NS <= 64 doubles per thread into out[0..NS) (the
 // many-slot counterpart of block_sum_store).
 template <int NS>
 __device__ __forceinline__ void block_sum_many(const double (&acc)[NS], double* __restrict__ out) {
-  constexpr int P = NS <= 16 ? 16 : (NS <= 32 ? 32 : 64);
+  constexpr int P = pow2_at_least(NS);
   __shared__ double red[kBlock / kWave][P];
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   double v[P];
@@ -175,22 +205,21 @@ __device__ __forceinline__ void block_sum_many(const double (&acc)[NS], double* 
 }
 
 // Totals of a table of per-block partial sums, by one block of kFin threads:
-// out[s] (shared, NS doubles) = sum over the rows of part[row * NS + s].  The
+// out[s] (shared, ns <= kFin doubles) = sum over the rows of part[row * ns + s].  The
 // table is read as one flat array, thread t taking elements t, t + A, ... with
-// A the largest multiple of NS up to kFin, so that loads are coalesced and a
+// A the largest multiple of ns up to kFin, so that loads are coalesced and a
 // thread stays on one column; kFinUnroll of them are in flight per thread.  A
-// wave then adds each column's A / NS threads.  Fixed order, independent of
+// wave then adds each column's A / ns threads.  Fixed order, independent of
 // timing.  Bound by the latency of one CU's loads: 4096 x 15 doubles took 18 us
 // with 256 threads walking rows (15 strided loads a row, 15 block reductions by
 // shuffles) and take 11 us this way.  Every thread of the block must call it.
 constexpr int kFin = 1024;
 constexpr int kFinUnroll = 16;
-template <int NS>
-__device__ __forceinline__ void fin_rows(const double* __restrict__ part, int rows, double* __restrict__ out) {
-  constexpr int A = kFin / NS * NS;
-  __shared__ double buf[A];
+__device__ __forceinline__ void fin_table(const double* __restrict__ part, int rows, int ns, double* __restrict__ out) {
+  const int A = kFin / ns * ns;
+  __shared__ double buf[kFin];
   const int t = threadIdx.x;
-  const long len = (long)rows * NS;
+  const long len = (long)rows * ns;
   if (t < A) {
     double a = 0.0;
     for (long k = t; k < len; k += (long)kFinUnroll * A) {
@@ -207,13 +236,17 @@ __device__ __forceinline__ void fin_rows(const double* __restrict__ part, int ro
   }
   __syncthreads();
   const int lane = t % kWave, wave = t / kWave;
-  for (int s = wave; s < NS; s += kFin / kWave) {
+  for (int s = wave; s < ns; s += kFin / kWave) {
     double a = 0.0;
-    for (int g = lane; g < A / NS; g += kWave) a += buf[g * NS + s];
+    for (int g = lane; g < A / ns; g += kWave) a += buf[g * ns + s];
     a = wave_sum(a);
     if (lane == 0) out[s] = a;
   }
   __syncthreads();
+}
+template <int NS>
+__device__ __forceinline__ void fin_rows(const double* __restrict__ part, int rows, double* __restrict__ out) {
+  fin_table(part, rows, NS, out);
 }
 
 // Rows owned by this block: the row range is split into gridDim.x contiguous

@@ -97,7 +97,7 @@ k_objgrad_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ R,
       acc.add(lane, P_RG, (double)rg);
     }
   }
-  acc.block_store(lane, part + part_slot(tab) * NUM_P);
+  acc.block_store(part + part_slot(tab) * NUM_P);
 }
 
 // c2 = <G, C G> for the quartic line search (sparse product of the direction).
@@ -269,7 +269,7 @@ k_upd_eval_diag(long n, int r, T* __restrict__ R, T* __restrict__ G, const typen
       acc.add(lane, P_RG, (double)rg);
     }
   }
-  if (!update_only) acc.block_store(lane, part + part_slot(tab) * NUM_P);
+  if (!update_only) acc.block_store(part + part_slot(tab) * NUM_P);
 }
 
 // All line-search partials for an arbitrary direction G (API entry point).
@@ -331,7 +331,7 @@ k_ls_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ R, const T
       acc.add(lane, P_C2, (double)gq);
     }
   }
-  acc.block_store(lane, part + (long)blockIdx.x * NUM_P);
+  acc.block_store(part + (long)blockIdx.x * NUM_P);
 }
 
 // ---- launchers -----------------------------------------------------------------

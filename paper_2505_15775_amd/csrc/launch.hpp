@@ -58,27 +58,21 @@ template <typename T>
 void launch_ls_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, const T* R, const T* G,
                     const double* y, const double* b, double* part, int nblk, hipStream_t st);
 
+// Objective and gradient of the edge family at R (passes 1 and 2 and their
+// finalizers).  With G_in the direction is read instead of computed and G is
+// not written (line-search API).  mode and f_out as for launch_fin_objgrad.
 template <typename T>
-void launch_edges_p1(const EdgeAdj& A, long n, int r, int variant, const T* R, const double* y, const double* b,
-                     double sigma, double* Av, double* wE, double* part, const DevScalars* sc, int nblk,
-                     hipStream_t st, double rho = 1.0);
-template <typename T>
-void launch_edges_p2(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, int variant, const T* R,
-                     const double* wE, double c_tr, double j_coef, const T* G_in, T* G, double* part,
-                     const DevScalars* sc, int nblk, hipStream_t st);
+void launch_edges_eval(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, long n, int r, int variant, const T* R,
+                       const double* y, const double* b, double sigma, double c_tr, double j_coef, double rho,
+                       double* Av, double* wE, const T* G_in, T* G, double* part, DevScalars* sc, int nblk, int mode,
+                       double* f_out, hipStream_t st);
 template <typename T>
 void launch_edges_p3(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, int variant, const T* R,
                      const T* G, const double* y, const double* b, const double* Av, double* part,
                      const DevScalars* sc, int nblk, hipStream_t st, double rho = 1.0);
-// part2 (64 x (NUM_P + kMaxR) doubles, nullable): the finalizers first reduce
-// the nb partial rows to 64 with 64 blocks, then finish with one block.
-void launch_fin_edges1(const double* part, int nb, int r, DevScalars* sc, const double* y, const double* b,
-                       double sigma, double c_tr, double* Av, hipStream_t st, double* part2 = nullptr);
-void launch_fin_edges2(const double* part, int nb, int r, DevScalars* sc, double sigma, int mode, double* f_out,
-                       hipStream_t st, double* part2 = nullptr);
 void launch_fin_edges3(const double* part, int nb, int r, DevScalars* sc, const double* y, const double* b,
                        double sigma, double c_tr, double j_coef, int mode, double* coeffs_out, double* t_out,
-                       hipStream_t st, double* part2 = nullptr);
+                       hipStream_t st);
 
 void launch_fin_objgrad(const double* part, int nb, DevScalars* sc, double sigma, int mode, double* f_out,
                         hipStream_t st, const BlockTab& tab = BlockTab{}, int count = 1);

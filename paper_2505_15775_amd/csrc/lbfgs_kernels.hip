@@ -434,7 +434,7 @@ k_lbfgs_combine(long n, int r, const T* __restrict__ R, const T* __restrict__ G,
     acc.add(lane, P_A2A2, a2 * a2);
     acc.add(lane, P_RG, (double)re);
   }
-  acc.block_store(lane, part + part_slot(tab) * NUM_P);
+  acc.block_store(part + part_slot(tab) * NUM_P);
 }
 
 __global__ void __launch_bounds__(kFin)

@@ -91,19 +91,26 @@ struct SplitAcc {
       a[s / LPR] += (lane == s % LPR) ? v : 0.0;
     }
   }
-  // Deterministic block total of every slot into out[0..NS): per-thread slots
-  // to LDS, then slot s summed over threads t = s % LPR, s % LPR + LPR, ... in order.
-  __device__ __forceinline__ void block_store(int lane, double* __restrict__ out) {
-    __shared__ double buf[kBlock][K];
+  // Deterministic block total of every slot into out[0..NS): each wave sums its
+  // lanes by halving (lane l keeps slots of l % LPR throughout), then the waves
+  // are added in order.
+  __device__ __forceinline__ void block_store(double* __restrict__ out) {
+    constexpr int P = pow2_at_least(K);
+    __shared__ double red[kBlock / kWave][NS];
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    double v[P];
 #pragma unroll
-    for (int q = 0; q < K; ++q) buf[threadIdx.x][q] = a[q];
+    for (int q = 0; q < P; ++q) v[q] = q < K ? a[q] : 0.0;
+    const double x = wave_sum_many<P, LPR>(v, lane);
+    constexpr int W = kWave / P;  // lanes that end with the same slot group
+    const int s = lane / W * LPR + lane % LPR;
+    if (lane % W < LPR && s < NS) red[wave][s] = x;
     __syncthreads();
     if (threadIdx.x < NS) {
-      const int s = threadIdx.x;
-      const int l = s % LPR, q = s / LPR;
       double t = 0.0;
-      for (int th = l; th < kBlock; th += LPR) t += buf[th][q];
-      out[s] = t;
+#pragma unroll
+      for (int w = 0; w < kBlock / kWave; ++w) t += red[w][threadIdx.x];
+      out[threadIdx.x] = t;
     }
   }
 };

@@ -40,3 +40,61 @@ def test_objective_over_partial_row_counts(blocks):
     k, _ = p.line_search(p.factor(R), p.factor(G_o), torch.from_numpy(y).to(DEV), 1.3)
     k_o = oracle.line_search_coeffs(po, R, G_o, y, 1.3)
     np.testing.assert_allclose(k.cpu().numpy(), k_o, rtol=1e-10, atol=1e-10 * float(np.max(np.abs(k_o))))
+
+
+@pytest.mark.parametrize("r", [1, 3, 4, 5, 8, 11, 16, 17, 32, 40, 64, 100, 128])
+@pytest.mark.parametrize("shape", ["long", "short", "one_edge"])
+def test_edge_family_tiles_against_oracle(shape, r):
+    """Every tile of the edge kernels, full and with remainder columns, on long rows (a wave per row), on short
+    ones and on a single edge; edge counts that leave partial groups.  FP64 sums of at most n r products."""
+    rng = np.random.default_rng(r)
+    n, E = {"long": (120, 5001), "short": (700, 1503), "one_edge": (5, 1)}[shape]
+    iu, ju = np.triu_indices(n, 1)
+    pick = np.sort(rng.choice(iu.size, size=E, replace=False))
+    ei, ej = iu[pick], ju[pick]
+    b = rng.standard_normal(E + 1)
+    dg = rng.standard_normal(n)
+    trace, j_coef = (0.0, 0.0) if r % 2 else (1.5, 0.5)
+    p = _almbm().Problem.edges(n, ei, ej, b, trace, j_coef=j_coef, cost_diag=dg, precision="f64", r_max=128,
+                               lanczos_kmax=0, device=DEV)
+    R, G, y = rng.standard_normal((n, r)), rng.standard_normal((n, r)), rng.standard_normal(E + 1)
+
+    def amap(A, B):
+        edge = 0.5 * ((A[ei] * B[ej]).sum(1) + (B[ei] * A[ej]).sum(1))
+        return np.concatenate([[trace * (A * B).sum()], edge])
+
+    def cost(X):
+        return dg[:, None] * X - j_coef * X.sum(0)[None, :]
+
+    s, a = 1.3, amap(R, R)
+    e = a - b
+    w = y - s * e
+    adj = trace * w[0] * R
+    np.add.at(adj, ei, 0.5 * w[1:, None] * R[ej])
+    np.add.at(adj, ej, 0.5 * w[1:, None] * R[ei])
+    f_o = (R * cost(R)).sum() + y @ (b - a) + 0.5 * s * (e @ e)
+    f, Gg, Av = p.objective_grad(p.factor(R), torch.from_numpy(y).to(DEV), s)
+    assert abs(f.item() - f_o) <= 1e-11 * (1 + abs(f_o) + abs(s * (e @ e)))
+    assert rel(Gg.cpu(), 2 * (cost(R) - adj)) <= 1e-12 and rel(Av.cpu(), a) <= 1e-12
+    a1, a2 = 2 * amap(R, G), amap(G, G)
+    k_o = np.array([f_o, -2 * (G * cost(R)).sum() + y @ a1 - s * (e @ a1),
+                    (G * cost(G)).sum() - y @ a2 + 0.5 * s * (a1 @ a1 + 2 * (e @ a2)), -s * (a1 @ a2),
+                    0.5 * s * (a2 @ a2)])
+    k, _ = p.line_search(p.factor(R), p.factor(G), torch.from_numpy(y).to(DEV), s)
+    np.testing.assert_allclose(k.cpu().numpy(), k_o, rtol=1e-10, atol=1e-11 * float(np.max(np.abs(k_o))))
+
+
+@pytest.mark.parametrize("prec,tol", [("f32", 2e-5), ("bf16", 2e-2)])
+@pytest.mark.parametrize("r", [1, 3, 7, 11, 13, 23, 31, 47, 100])
+def test_odd_ranks_wide_partial_rows(r, prec, tol):
+    """Rows whose width no tile fills are read with the widest accesses that fit: every remainder, both storage
+    types.  Tolerances: a sum of at most 100 rounded products in float, one bfloat16 rounding of the result."""
+    g = gen.er_graph(501, 3000, 7, "gauss")
+    po = oracle.maxcut_sdp(g)
+    p = _almbm().Problem.maxcut(g.n, g.ei, g.ej, g.w, precision=prec, r_max=128, lanczos_kmax=0, device=DEV)
+    rng = np.random.default_rng(r)
+    R = p.factor(rng.standard_normal((g.n, r)))
+    y = rng.standard_normal(g.n)
+    f_o, G_o, a_o, _ = oracle.objective_grad(po, R.double().cpu().numpy(), y, 0.7)
+    f, G, Av = p.objective_grad(R, torch.from_numpy(y).to(DEV), 0.7)
+    assert rel(G.double().cpu(), G_o) <= tol and rel(Av.cpu(), a_o) <= 2e-5
