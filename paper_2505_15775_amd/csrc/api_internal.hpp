@@ -12,7 +12,7 @@ namespace almbm {
 alm_bm_status set_error(alm_bm_status s, const std::string& msg);
 
 // Default grid of the row kernels for n rows: one block per 64 rows, at least
-// 8 and at most 4096 blocks, a multiple of 8 (one share per XCD).
+// 8 and at most 1024 blocks, a multiple of 8 (one share per XCD).
 int row_blocks(long n);
 
 }  // namespace almbm

@@ -18,8 +18,8 @@ using namespace almbm;
 
 namespace {
 
-// Largest grid row_blocks() returns, hence the most partial-sum rows a call
-// needs; every n in 1..2^31-1 maps to at most this many blocks.
+// Partial-sum rows held: no fewer than the largest grid row_blocks() returns
+// for any n in 1..2^31-1.
 constexpr int kScratchBlocks = 4096;
 constexpr size_t kPartDoubles = (size_t)kScratchBlocks * NUM_P;
 constexpr size_t kScalarDoubles = (sizeof(DevScalars) + sizeof(double) - 1) / sizeof(double);
