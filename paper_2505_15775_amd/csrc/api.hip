@@ -85,7 +85,9 @@ struct alm_bm_problem {
   double* lalpha = nullptr;
   double* lbeta = nullptr;
   double* lpart = nullptr;
+  double* lpartb = nullptr;
   double* lpart2 = nullptr;
+  double* lw2 = nullptr;
   double* lv = nullptr;
   double* ls = nullptr;
   double* lscal = nullptr;
@@ -561,6 +563,7 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   if (p->kmax > 0) {
     CK(dalloc_t(p, &p->Q, (size_t)n * (p->kmax + 1)));
     CK(dalloc_t(p, &p->lw, n));
+    CK(dalloc_t(p, &p->lw2, n));
     CK(dalloc_t(p, &p->lv, n));
     CK(dalloc_t(p, &p->lh1, p->kmax + 1));
     CK(dalloc_t(p, &p->lh2, p->kmax + 1));
@@ -569,7 +572,8 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
     CK(dalloc_t(p, &p->ls, p->kmax + 1));
     CK(dalloc_t(p, &p->lscal, 8));
     CK(dalloc_t(p, &p->lpart, (size_t)p->lnb * (p->kmax + 1)));
-    CK(dalloc_t(p, &p->lpart2, (size_t)p->lnb));
+    CK(dalloc_t(p, &p->lpartb, (size_t)p->lnb * (p->kmax + 1)));
+    CK(dalloc_t(p, &p->lpart2, (size_t)p->lnb * 2));
     CK(dalloc_t(p, &p->bk_h, (size_t)(p->kmax + 1) * (p->kmax + 1)));
     CK(dalloc_t(p, &p->bk_colsum, (size_t)(p->kmax + 1)));
     CK(dalloc_t(p, &p->bk_coef, (size_t)(p->kmax + 1) * kMaxBlockQ));
@@ -1238,7 +1242,6 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   const long n = d.n;
   const long ldq = n;
   const int nb = p->lnb;
-  const int pstride = p->kmax + 1;
   kmax = std::min(kmax, p->kmax);
   if (kmax < 1) return fail(ALM_BM_ERR_INVALID_ARG, "lanczos: no Lanczos workspace (lanczos_kmax = 0)");
   kmax = (int)std::min<long>(kmax, n);
@@ -1257,18 +1260,19 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   std::vector<double> ha(kmax + 1), hb(kmax + 1), z;
   int m = 0;
   double theta = 0.0;
+  bool sums = false;
   const int check_every = n <= 4096 ? 4 : 8;
   for (int j = 0; j < kmax; ++j) {
-    const double* qj = p->Q + (long)j * ldq;
-    launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, p->sc_api, qj, p->lw, st);
-    launch_dots(n, j + 1, p->Q, ldq, p->lw, p->lpart, pstride, nb, p->lh1, st);
-    launch_sub(n, j + 1, p->Q, ldq, p->lh1, p->lw, p->lpart2, nb, st);
-    launch_dots(n, j + 1, p->Q, ldq, p->lw, p->lpart, pstride, nb, p->lh2, st);
-    launch_sub(n, j + 1, p->Q, ldq, p->lh2, p->lw, p->lpart2, nb, st);
-    launch_fin_ab(p->lpart2, nb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, st);
-    launch_scale(n, p->lw, p->lbeta + j, p->Q + (long)(j + 1) * ldq, p->lpart2, nb, qsum, st);
     const bool last = (j + 1 == kmax);
-    if (((j + 1) % check_every) == 0 || last) {
+    const bool check = ((j + 1) % check_every) == 0 || last;
+    double* wj = j & 1 ? p->lw2 : p->lw;  // Z q_j, then the next column before scaling
+    const LzStep step{j, p->lpart2, nb, p->lnb, p->lh1, p->lh2, p->lalpha, p->lbeta, sums};
+    launch_lz_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, step, j == 0 ? p->Q : (j & 1 ? p->lw : p->lw2),
+                 p->Q + (long)j * ldq, wj, nb, st);
+    launch_gs2(n, j + 1, p->Q, ldq, wj, p->lpart, p->lpartb, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
+    sums = !check && nb <= kLzFewBlocks;
+    if (!sums) launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, qsum, st);
+    if (check) {
       HIPCHK(hipMemcpyAsync(ha.data(), p->lalpha, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
       HIPCHK(hipMemcpyAsync(hb.data(), p->lbeta, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
@@ -1296,7 +1300,7 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   launch_combine(n, m, p->Q, ldq, p->ls, v, p->lpart2, nb, st);
   launch_fin_sum(p->lpart2, nb, p->lscal + 1, 1, st);
   launch_scale(n, v, p->lscal + 1, v, p->lpart2, nb, qsum, st);
-  launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, p->sc_api, v, p->lw, st);
+  launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, v, p->lw, st);
   launch_resid(n, p->lw, v, theta, nullptr, p->lpart2, nb, st);
   launch_fin_sum(p->lpart2, nb, p->lscal + 2, 1, st);
   double hres = 0.0;
@@ -1359,7 +1363,7 @@ static alm_bm_status block_krylov(alm_bm_problem* p, const double* y, int q, int
                                   hipStream_t st) {
   const auto& d = p->d;
   const long n = d.n, ldq = n;
-  const int nb = p->lnb, pstride = p->kmax + 1, ld = p->kmax + 1;
+  const int nb = p->lnb, ld = p->kmax + 1;
   kmax = std::min(kmax, p->kmax);
   const int m = (int)std::min<long>(kmax + 1, n);
   if (q < 1 || q > kMaxBlockQ) return fail(ALM_BM_ERR_INVALID_ARG, "block Lanczos: q must be in 1..8");
@@ -1367,9 +1371,8 @@ static alm_bm_status block_krylov(alm_bm_problem* p, const double* y, int q, int
   double* qsum = (d.j_coef != 0.0) ? &p->sc_api->qsum : nullptr;
   const int cons = d.cons_kind == ALM_BM_CONS_DIAG ? 0 : 1;
   // lw against columns 0..c-1 (two passes; partial ||lw||^2 left in lpart2)
-  auto second_pass = [&](int c) {
-    launch_dots(n, c, p->Q, ldq, p->lw, p->lpart, pstride, nb, p->lh2, st);
-    launch_sub(n, c, p->Q, ldq, p->lh2, p->lw, p->lpart2, nb, st);
+  auto orthogonalise = [&](int c) {
+    launch_gs2(n, c, p->Q, ldq, p->lw, p->lpart, p->lpartb, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
   };
   auto normalise_into = [&](int c) -> alm_bm_status {
     launch_fin_sum(p->lpart2, nb, p->lscal, 1, st);
@@ -1379,25 +1382,19 @@ static alm_bm_status block_krylov(alm_bm_problem* p, const double* y, int q, int
   };
   auto product = [&](int j) -> alm_bm_status {
     if (qsum) HIPCHK(hipMemcpyAsync(qsum, p->bk_colsum + j, sizeof(double), hipMemcpyDeviceToDevice, st));
-    launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, p->sc_api, p->Q + (long)j * ldq, p->lw, st);
+    launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, p->Q + (long)j * ldq, p->lw, st);
     return ALM_BM_OK;
   };
   for (int i = 0; i < q; ++i) {
     launch_rand(n, seed * 1000003ull + (uint64_t)i, p->lw, p->lpart2, nb, st);
-    if (i > 0) {
-      launch_dots(n, i, p->Q, ldq, p->lw, p->lpart, pstride, nb, p->lh1, st);
-      launch_sub(n, i, p->Q, ldq, p->lh1, p->lw, p->lpart2, nb, st);
-      second_pass(i);
-    }
+    if (i > 0) orthogonalise(i);
     STCHK(normalise_into(i));
   }
   for (int c = q; c < m; ++c) {
     const int j = c - q;
     STCHK(product(j));
-    launch_dots(n, c, p->Q, ldq, p->lw, p->lpart, pstride, nb, p->lh1, st);
+    orthogonalise(c);
     HIPCHK(hipMemcpyAsync(p->bk_h + (long)j * ld, p->lh1, c * sizeof(double), hipMemcpyDeviceToDevice, st));
-    launch_sub(n, c, p->Q, ldq, p->lh1, p->lw, p->lpart2, nb, st);
-    second_pass(c);
     launch_fin_sum(p->lpart2, nb, p->lscal, 1, st);
     // the new column's norm before scaling: H[c][j] (breakdown test)
     HIPCHK(hipMemcpyAsync(p->bk_h + (long)j * ld + c, p->lscal, sizeof(double), hipMemcpyDeviceToDevice, st));
@@ -1406,7 +1403,7 @@ static alm_bm_status block_krylov(alm_bm_problem* p, const double* y, int q, int
   }
   for (int j = m - q; j < m; ++j) {
     STCHK(product(j));
-    launch_dots(n, m, p->Q, ldq, p->lw, p->lpart, pstride, nb, p->lh1, st);
+    launch_dots(n, m, p->Q, ldq, p->lw, p->lpart, p->lnb, nb, p->lh1, st);
     HIPCHK(hipMemcpyAsync(p->bk_h + (long)j * ld, p->lh1, m * sizeof(double), hipMemcpyDeviceToDevice, st));
   }
   std::vector<double> Hd((size_t)ld * m), cs(m, 0.0);
@@ -1454,7 +1451,7 @@ static alm_bm_status block_krylov(alm_bm_problem* p, const double* y, int q, int
       double qs = 0.0;  // 1^T v for the -J term, from the columns' sums
       for (int i = 0; i < mm; ++i) qs += coef[(size_t)k * mm + i] * cs[i];
       if (qsum) HIPCHK(hipMemcpyAsync(qsum, &qs, sizeof(double), hipMemcpyHostToDevice, st));
-      launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, p->sc_api, V + (long)k * n, p->lw, st);
+      launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, V + (long)k * n, p->lw, st);
       launch_resid(n, p->lw, V + (long)k * n, theta[k], nullptr, p->lpart2, nb, st);
       launch_fin_sum(p->lpart2, nb, p->lscal + 2, 1, st);
       HIPCHK(hipMemcpyAsync(&(*resid)[k], p->lscal + 2, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -2321,7 +2318,8 @@ extern "C" alm_bm_status alm_bm_batch_create(int32_t count, const alm_bm_problem
   BH(hipMemset(p->sc_solve, 0, (size_t)count * sizeof(DevScalars)));
   p->lnb = nb;
   BK(balloc(b, (void**)&p->lpart, (size_t)nb * kp * sizeof(double)));
-  BK(balloc(b, (void**)&p->lpart2, (size_t)nb * sizeof(double)));
+  BK(balloc(b, (void**)&p->lpartb, (size_t)nb * kp * sizeof(double)));
+  BK(balloc(b, (void**)&p->lpart2, (size_t)nb * 2 * sizeof(double)));
   BK(balloc(b, (void**)&p->lh1, (size_t)count * kp * sizeof(double)));
   BK(balloc(b, (void**)&p->lh2, (size_t)count * kp * sizeof(double)));
   BK(balloc(b, (void**)&p->lalpha, (size_t)count * kp * sizeof(double)));
@@ -2461,14 +2459,12 @@ static alm_bm_status batch_lanczos_pass(alm_bm_batch* b, const double* y, int km
   std::vector<double> ha((size_t)count * kp), hb((size_t)count * kp);
   std::vector<std::vector<double>> z(count);
   for (int j = 0; j < kmax; ++j) {
-    const double* qj = p->Q + (long)j * ldq;
-    launch_slack_mv_tab(p->C64, y, qj, p->lw, ltab, nb, st);
-    launch_dots(n, j + 1, p->Q, ldq, p->lw, p->lpart, kp, nb, p->lh1, st, vb);
-    launch_sub(n, j + 1, p->Q, ldq, p->lh1, p->lw, p->lpart2, nb, st, vb);
-    launch_dots(n, j + 1, p->Q, ldq, p->lw, p->lpart, kp, nb, p->lh2, st, vb);
-    launch_sub(n, j + 1, p->Q, ldq, p->lh2, p->lw, p->lpart2, nb, st, vb);
-    launch_fin_ab(p->lpart2, nb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, st, vb);
-    launch_scale(n, p->lw, p->lbeta + j, p->Q + (long)(j + 1) * ldq, p->lpart2, nb, nullptr, st, vb, kp);
+    double* wj = j & 1 ? p->lw2 : p->lw;
+    const LzStep step{j, p->lpart2, nb, p->lnb, p->lh1, p->lh2, p->lalpha, p->lbeta, false};
+    launch_lz_mv(p->C64, 0, p->adj, y, 0.0, 0.0, nullptr, step, j == 0 ? p->Q : (j & 1 ? p->lw : p->lw2),
+                 p->Q + (long)j * ldq, wj, nb, st, vb);
+    launch_gs2(n, j + 1, p->Q, ldq, wj, p->lpart, p->lpartb, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st, vb);
+    launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, nullptr, st, vb);
     const bool last = (j + 1 == kmax);
     if (((j + 1) % 8) == 0 || last) {
       HIPCHK(hipMemcpyAsync(ha.data(), p->lalpha, ha.size() * sizeof(double), hipMemcpyDeviceToHost, st));
@@ -2527,7 +2523,7 @@ static alm_bm_status batch_lanczos_pass(alm_bm_batch* b, const double* y, int km
   launch_combine(n, mmax, p->Q, ldq, p->ls, v, p->lpart2, nb, st, vb, b->lm_dev);
   launch_fin_sum(p->lpart2, nb, p->lscal + 1, 1, st, vb, 4);
   launch_scale(n, v, p->lscal + 1, v, p->lpart2, nb, nullptr, st, vb, 4);
-  launch_slack_mv_tab(p->C64, y, v, p->lw, ltab, nb, st);
+  launch_slack_mv_tab(p->C64, y, v, p->lw, nb, st, vb);
   launch_resid(n, p->lw, v, 0.0, b->thetas_dev, p->lpart2, nb, st, vb);
   launch_fin_sum(p->lpart2, nb, p->lscal + 2, 1, st, vb, 4);
   std::vector<double> sc4((size_t)count * 4);

@@ -9,126 +9,215 @@ namespace almbm {
 
 constexpr int kSpmvLpr = 4;  // lanes per row in the slack product (avg degree ~ 8)
 
-// out_i = (Z(y) x)_i.  DIAG: (d_i - y_i) x_i + sum_k S_ik x_k.
-// TRACE_EDGES: (S x)_i + d_i x_i - j (1^T x) - c_tr y_0 x_i - 1/2 sum_{k~i} y_{1+e(ik)} x_k.
-__global__ void __launch_bounds__(kBlock)
-k_slack_mv(Cost<double> C, int cons_kind, EdgeAdj A, const double* __restrict__ y, double c_tr, double j_coef,
-           const DevScalars* __restrict__ sc, const double* __restrict__ x, double* __restrict__ out) {
-  constexpr int L = kSpmvLpr;
-  const long i = ((long)blockIdx.x * kBlock + threadIdx.x) / L;
-  const int lane = threadIdx.x % L;
-  if (i >= C.n) return;
-  double acc = 0.0;
-  long k0 = 0, k1 = 0;
-  if (C.ell > 0) {
-    k0 = i * (long)C.ell;
-    k1 = k0 + C.ell;
-  } else if (C.rp) {
-    k0 = C.rp[i];
-    k1 = C.rp[i + 1];
+// ---- Lanczos step ------------------------------------------------------------------
+//
+// One step on column j: k_lz_mv (q_j = w / beta and w' = Z q_j), then two
+// classical Gram-Schmidt passes: dots of w' with the basis, w' -= Q h together
+// with the dots of the second pass (one read of the basis for both), w' -= Q h
+// again with ||w'||^2.  Three reads of the basis per step, the two passes'
+// definition being the same as with four.  Partial sums per block at
+// part[c * pld + slot] (column-major, so that a column's finalizer reads
+// contiguously).
+
+// Projection coefficients of a column block: either reduced (h + inst * hstride)
+// or, when few blocks hold them, the partial sums themselves (part, nb of them
+// per column), which every block then adds in the same order, saving the
+// finalizer's launch; block 0 leaves the totals at out.
+struct LzCoef {
+  const double* h = nullptr;
+  int hstride = 0;
+  const double* part = nullptr;
+  int nb = 0;
+  int pld = 0;
+  double* out = nullptr;
+};
+
+__device__ __forceinline__ double sum_strided4(const double* __restrict__ p, int nb) {
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  int b = 0;
+  for (; b + 4 <= nb; b += 4) {
+    a0 += p[b];
+    a1 += p[b + 1];
+    a2 += p[b + 2];
+    a3 += p[b + 3];
   }
-  if (C.nh > 0 && k1 - k0 > C.hthr) {  // hub row: sum precomputed by k_hub_rows
-    if (lane == 0) acc = C.hsum[hub_index(C, i)];
-  } else {
-    for (long k = k0 + lane; k < k1; k += L) acc += C.cv[k] * x[C.ci[k]];
-  }
-  if (cons_kind == 1) {
-    const int a0 = A.rp[i], a1 = A.rp[i + 1];
-    for (int k = a0 + lane; k < a1; k += L) acc -= 0.5 * y[1 + A.eid[k]] * x[A.ci[k]];
-  }
-  acc = group_sum<L>(acc);
-  if (lane == 0) {
-    const double xi = x[i];
-    double d = C.dg ? C.dg[i] : 0.0;
-    if (cons_kind == 0) d -= y[i];
-    else d -= c_tr * y[0];
-    double v = acc + d * xi;
-    if (j_coef != 0.0) v -= j_coef * sc->qsum;
-    out[i] = v;
-  }
+  for (; b < nb; ++b) a0 += p[b];
+  return (a0 + a1) + (a2 + a3);
 }
 
-// The same product over the rows of a block table (batched mode: only the
-// blocks of the instances still running).
-__global__ void __launch_bounds__(kBlock)
-k_slack_mv_tab(Cost<double> C, const double* __restrict__ y, const double* __restrict__ x, double* __restrict__ out,
-               BlockTab tab) {
-  constexpr int L = kSpmvLpr;
-  constexpr int RPB = kBlock / L;
-  const Rows ch = rows_of(C.n, tab);
-  const int lane = threadIdx.x % L;
-  for (long base = ch.lo; base < ch.hi; base += RPB) {
-    const long i = base + threadIdx.x / L;
-    double acc = 0.0;
-    if (i < ch.hi) {
-      const long k0 = C.rp ? C.rp[i] : 0, k1 = C.rp ? C.rp[i + 1] : 0;
-      for (long k = k0 + lane; k < k1; k += L) acc += C.cv[k] * x[C.ci[k]];
+// hs[c] (shared) for c < ncol, zero up to the next multiple of 16.
+__device__ __forceinline__ void load_coef(const LzCoef& hc, int inst, int ncol, double* __restrict__ hs) {
+  for (int c = threadIdx.x; c < (ncol + 15) / 16 * 16; c += kBlock) {
+    double x = 0.0;
+    if (c < ncol) {
+      x = hc.part ? sum_strided4(hc.part + (long)c * hc.pld, hc.nb) : hc.h[(long)inst * hc.hstride + c];
+      if (hc.part && blockIdx.x == 0) hc.out[c] = x;
     }
-    acc = group_sum<L>(acc);
-    if (i < ch.hi && lane == 0) out[i] = acc + ((C.dg ? C.dg[i] : 0.0) - y[i]) * x[i];
+    hs[c] = x;
   }
+  __syncthreads();
 }
 
-// partials[b][c] = sum over the block's rows of Q[c][i] * w[i], c < ncol.
-// Wave w of the block handles columns c = w, w+4, ...; lanes stride the rows.
+// SUB: w -= Q h.  DOTS: per-block partial sums of q_c . w (after SUB) into part;
+// otherwise of ||w||^2 and sum w into part[slot], part[pld + slot].  A thread
+// owns a row and holds its entries of all ncol <= NC columns at once, so a wave
+// has ncol 512-byte loads in flight; the columns' dots are summed over the wave
+// by halving, which leaves column l / (64 / NC) in lane l.  Bound by HBM: over a
+// 56-column pass at n = 1e6 the dots run at 5.2 TB/s and SUB with DOTS at 4.7
+// TB/s, where column-per-wave dots and row-per-thread subtraction on 248 blocks
+// ran at 3.0 and 3.5 TB/s and read the basis once more.
+template <int NC, bool SUB, bool DOTS>
 __global__ void __launch_bounds__(kBlock)
-k_dots(long n, int ncol, const double* __restrict__ Q, long ldq, const double* __restrict__ w,
-       double* __restrict__ part, int pstride, BlockTab tab) {
+k_lz_proj(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef hc, double* __restrict__ w,
+          double* __restrict__ part, int pld, BlockTab tab) {
   const Rows ch = rows_of(n, tab);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-  for (int c = wave; c < ncol; c += kBlock / kWave) {
-    const double* q = Q + (long)c * ldq;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    long i = ch.lo + lane;
-    for (; i + 3 * kWave < ch.hi; i += 4 * kWave) {
-      a0 += q[i] * w[i];
-      a1 += q[i + kWave] * w[i + kWave];
-      a2 += q[i + 2 * kWave] * w[i + 2 * kWave];
-      a3 += q[i + 3 * kWave] * w[i + 3 * kWave];
+  __shared__ double hs[SUB ? NC : 1];
+  if constexpr (SUB) load_coef(hc, ch.inst, ncol, hs);
+  double acc = 0.0, nrm = 0.0, sum = 0.0;
+  for (long base = ch.lo; base < ch.hi; base += kBlock) {
+    const long i = base + threadIdx.x;
+    const bool in = i < ch.hi;
+    double q[NC];
+    double v = in ? w[i] : 0.0;
+#pragma unroll
+    for (int g = 0; g < NC; g += 8) {
+#pragma unroll
+      for (int c = g; c < g + 8; ++c) q[c] = 0.0;
+      if (g < ncol && in) {
+#pragma unroll
+        for (int c = g; c < g + 8; ++c) q[c] = Q[(long)(c < ncol ? c : ncol - 1) * ldq + i];
+      }
     }
-    for (; i < ch.hi; i += kWave) a0 += q[i] * w[i];
-    double a = wave_sum((a0 + a1) + (a2 + a3));
-    if (lane == 0) part[part_slot(tab) * pstride + c] = a;
+    if constexpr (SUB) {
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int g = 0; g < NC; g += 8) {
+        if (g < ncol) {
+#pragma unroll
+          for (int c = g; c < g + 8; ++c) s[c % 4] += q[c] * hs[c];
+        }
+        __builtin_amdgcn_sched_barrier(0);  // eight coefficients from LDS at a time, not NC of them in registers
+      }
+      v -= (s[0] + s[1]) + (s[2] + s[3]);
+      if (in) w[i] = v;
+      if (!in) v = 0.0;
+    }
+    if constexpr (DOTS) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) q[c] *= v;
+      acc += wave_sum_many<NC>(q, lane);
+    } else {
+      nrm += v * v;
+      sum += v;
+    }
+  }
+  if constexpr (DOTS) {
+    __shared__ double red[kBlock / kWave][NC];
+    constexpr int W = kWave / NC;
+    if (lane % W == 0) red[wave][lane / W] = acc;
+    __syncthreads();
+    for (int c = threadIdx.x; c < ncol; c += kBlock) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < kBlock / kWave; ++k) t += red[k][c];
+      part[(long)c * pld + part_slot(tab)] = t;
+    }
+  } else {
+    double two[2] = {nrm, sum};
+    __shared__ double out[2];
+    block_sum_store<2>(two, out);
+    __syncthreads();
+    if (threadIdx.x < 2) part[(long)threadIdx.x * pld + part_slot(tab)] = out[threadIdx.x];
+  }
+}
+
+// The same for more than 64 columns: the columns go by in chunks of CH, and
+// SUB + DOTS reads them twice (the second time the block's tile is in L2 or the
+// Infinity Cache).
+template <bool SUB, bool DOTS>
+__global__ void __launch_bounds__(kBlock)
+k_lz_proj_wide(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef hc, double* __restrict__ w,
+               double* __restrict__ part, int pld, BlockTab tab) {
+  constexpr int CH = 32, CS = 16;  // columns in flight per thread: dots, subtraction
+  constexpr int MAXC = 512 + CS;
+  const Rows ch = rows_of(n, tab);
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  __shared__ double hs[SUB ? MAXC : 1];
+  __shared__ double red[DOTS ? kBlock / kWave : 1][DOTS ? MAXC + CH : 1];
+  if constexpr (SUB) load_coef(hc, ch.inst, ncol, hs);
+  if constexpr (DOTS) {
+    for (int c = lane; c < MAXC + CH; c += kWave) red[wave][c] = 0.0;
+  }
+  double nrm = 0.0, sum = 0.0;
+  for (long base = ch.lo; base < ch.hi; base += kBlock) {
+    const long i = base + threadIdx.x;
+    const bool in = i < ch.hi;
+    double v = in ? w[i] : 0.0;
+    if constexpr (SUB) {
+      double s[4] = {0.0, 0.0, 0.0, 0.0};
+      if (in) {
+        for (int c0 = 0; c0 < ncol; c0 += CS) {
+          double q[CS];
+#pragma unroll
+          for (int c = 0; c < CS; ++c) q[c] = Q[(long)(c0 + c < ncol ? c0 + c : ncol - 1) * ldq + i];
+#pragma unroll
+          for (int c = 0; c < CS; ++c) s[c % 4] += q[c] * hs[c0 + c];
+        }
+        v -= (s[0] + s[1]) + (s[2] + s[3]);
+        w[i] = v;
+      }
+    }
+    if constexpr (DOTS) {
+      for (int c0 = 0; c0 < ncol; c0 += CH) {
+        double q[CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) q[c] = in ? Q[(long)(c0 + c < ncol ? c0 + c : ncol - 1) * ldq + i] * v : 0.0;
+        const double x = wave_sum_many<CH>(q, lane);
+        if (lane % (kWave / CH) == 0) red[wave][c0 + lane / (kWave / CH)] += x;
+      }
+    } else {
+      nrm += v * v;
+      sum += v;
+    }
+  }
+  if constexpr (DOTS) {
+    __syncthreads();
+    for (int c = threadIdx.x; c < ncol; c += kBlock) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < kBlock / kWave; ++k) t += red[k][c];
+      part[(long)c * pld + part_slot(tab)] = t;
+    }
+  } else {
+    double two[2] = {nrm, sum};
+    __shared__ double out[2];
+    block_sum_store<2>(two, out);
+    __syncthreads();
+    if (threadIdx.x < 2) part[(long)threadIdx.x * pld + part_slot(tab)] = out[threadIdx.x];
   }
 }
 
 // h[q][c] = sum of the block partials of column c over instance q's blocks
 // (grid: columns x instances, fixed order).
 __global__ void __launch_bounds__(kBlock)
-k_fin_dots(const double* __restrict__ part, int nb, int pstride, int ncol, double* __restrict__ h, int hstride,
+k_fin_dots(const double* __restrict__ part, int nb, int pld, int ncol, double* __restrict__ h, int hstride,
            BlockTab tab) {
   const int c = blockIdx.x, q = blockIdx.y;
   if (c >= ncol) return;
   int b0, b1;
   inst_blocks(tab, q, nb, b0, b1);
   double acc[1] = {0.0};
-  for (int b = b0 + threadIdx.x; b < b1; b += kBlock) acc[0] += part[(long)b * pstride + c];
+  for (int b = b0 + threadIdx.x; b < b1; b += kBlock) acc[0] += part[(long)c * pld + b];
   block_sum_store<1>(acc, h + (long)q * hstride + c);
 }
 
-// w_i -= sum_c Q[c][i] h[c]; partial ||w||^2 per block.
-__global__ void __launch_bounds__(kBlock)
-k_sub(long n, int ncol, const double* __restrict__ Q, long ldq, const double* __restrict__ h, int hstride,
-      double* __restrict__ w, double* __restrict__ part, BlockTab tab) {
-  const Rows ch = rows_of(n, tab);
-  __shared__ double hs[512 + 1];
-  for (int c = threadIdx.x; c < ncol; c += kBlock) hs[c] = h[(long)ch.inst * hstride + c];
-  __syncthreads();
-  double acc[1] = {0.0};
-  for (long i = ch.lo + threadIdx.x; i < ch.hi; i += kBlock) {
-    double v = w[i];
-    for (int c = 0; c < ncol; ++c) v -= Q[(long)c * ldq + i] * hs[c];
-    w[i] = v;
-    acc[0] += v * v;
-  }
-  block_sum_store<1>(acc, part + part_slot(tab));
-}
-
 // Tridiagonal entries after the two projections: alpha_j = h1[j] + h2[j],
-// beta_j = ||w||.
+// beta_j = ||w||; qsum (nullable): 1^T w / beta_j, the sum of the next column.
 __global__ void __launch_bounds__(kBlock)
-k_fin_ab(const double* __restrict__ part, int nb, const double* __restrict__ h1, const double* __restrict__ h2,
-         int hstride, int j, double* __restrict__ alpha, double* __restrict__ beta, int astride, BlockTab tab) {
+k_fin_ab(const double* __restrict__ part, int nb, int pld, const double* __restrict__ h1,
+         const double* __restrict__ h2, int hstride, int j, double* __restrict__ alpha, double* __restrict__ beta,
+         int astride, double* __restrict__ qsum, BlockTab tab) {
   const int q = blockIdx.x;
   int b0, b1;
   inst_blocks(tab, q, nb, b0, b1);
@@ -136,17 +225,120 @@ k_fin_ab(const double* __restrict__ part, int nb, const double* __restrict__ h1,
   h2 += (long)q * hstride;
   alpha += (long)q * astride;
   beta += (long)q * astride;
-  __shared__ double red[kBlock / kWave];
-  double a = 0.0;
-  for (int b = b0 + threadIdx.x; b < b1; b += kBlock) a += part[b];
-  a = wave_sum(a);
-  if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = a;
+  double acc[2] = {0.0, 0.0};
+  for (int b = b0 + threadIdx.x; b < b1; b += kBlock) {
+    acc[0] += part[b];
+    acc[1] += part[(long)pld + b];
+  }
+  __shared__ double tot[2];
+  block_sum_store<2>(acc, tot);
   __syncthreads();
   if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int w = 0; w < kBlock / kWave; ++w) t += red[w];
     alpha[j] = h1[j] + h2[j];
-    beta[j] = sqrt(t);
+    const double bj = sqrt(tot[0]);
+    beta[j] = bj;
+    if (qsum) *qsum = bj > 0.0 ? tot[1] / bj : 0.0;
+  }
+}
+
+// Scaling of the incoming vector of k_lz_mv: none (part and beta null: w is q_j
+// already and qsum its sum), beta at beta + inst * bstride with qsum given, or
+// from nb partial sums of ||w||^2 and of w, which every block adds alike; block
+// 0 then also writes the tridiagonal entries of step j - 1.
+struct LzScale {
+  const double* beta = nullptr;
+  int bstride = 0;
+  const double* part = nullptr;
+  int nb = 0;
+  int pld = 0;
+  const double* h1 = nullptr;
+  const double* h2 = nullptr;
+  double* alpha_out = nullptr;  // entry j - 1
+  double* beta_out = nullptr;
+  int jm1 = 0;
+};
+
+// q = w / beta stored (when scaled), out = Z(y) q, gathering w and scaling each
+// entry as it comes (the same product as from q):
+// DIAG: (d_i - y_i) q_i + sum_k S_ik q_k.
+// TRACE_EDGES: (S q)_i + d_i q_i - j (1^T q) - c_tr y_0 q_i - 1/2 sum_{k~i} y_{1+e(ik)} q_k.
+// L lanes per row, U entries of the row in flight per lane, so that a row of up
+// to 16 entries costs one trip through the index and gather latencies.  Bound
+// by the gathers: n = 1e6, 8e6 entries (8 MB vector, two L2 slices' worth): 109
+// us one entry at a time, 101 us with four (79e9 gathers/s); non-temporal index
+// and value loads made it 125 us (they no longer come from the Infinity Cache).
+__global__ void __launch_bounds__(kBlock)
+k_lz_mv(Cost<double> C, int cons_kind, EdgeAdj A, const double* __restrict__ y, double c_tr, double j_coef,
+        const double* __restrict__ qsum_in, LzScale sc, const double* __restrict__ w, double* __restrict__ qcol,
+        double* __restrict__ out, BlockTab tab) {
+  constexpr int L = kSpmvLpr;
+  constexpr int U = 4;
+  constexpr int RPB = kBlock / L;
+  const Rows ch = rows_of(C.n, tab);
+  const int lane = threadIdx.x % L;
+  double inv = 1.0, qsum = (j_coef != 0.0 && qsum_in) ? *qsum_in : 0.0;
+  const bool scaled = sc.part || sc.beta;
+  if (sc.part) {
+    const double b2 = sum_strided4(sc.part, sc.nb);
+    const double beta = sqrt(b2);
+    inv = beta > 0.0 ? 1.0 / beta : 0.0;
+    if (j_coef != 0.0) qsum = beta > 0.0 ? sum_strided4(sc.part + sc.pld, sc.nb) / beta : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *sc.alpha_out = sc.h1[sc.jm1] + sc.h2[sc.jm1];
+      *sc.beta_out = beta;
+    }
+  } else if (sc.beta) {
+    const double beta = sc.beta[(long)ch.inst * sc.bstride];
+    inv = beta > 0.0 ? 1.0 / beta : 0.0;
+  }
+  for (long base = ch.lo; base < ch.hi; base += RPB) {
+    const long i = base + threadIdx.x / L;
+    const bool in = i < ch.hi;
+    double acc = 0.0;
+    if (in) {
+      long k0 = 0, k1 = 0;
+      if (C.ell > 0) {
+        k0 = i * (long)C.ell;
+        k1 = k0 + C.ell;
+      } else if (C.rp) {
+        k0 = C.rp[i];
+        k1 = C.rp[i + 1];
+      }
+      if (C.nh > 0 && k1 - k0 > C.hthr) {  // hub row: sum of the unscaled vector precomputed by k_hub_rows
+        if (lane == 0) acc = C.hsum[hub_index(C, i)] * inv;
+      } else {
+        for (long k = k0 + lane; k < k1; k += L * U) {
+          int j[U];
+          double c[U], x[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const long kk = k + u * L;
+            j[u] = kk < k1 ? C.ci[kk] : (int)i;
+            c[u] = kk < k1 ? C.cv[kk] : 0.0;
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) x[u] = w[j[u]];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (k + u * L < k1) acc += c[u] * (x[u] * inv);
+        }
+      }
+      if (cons_kind == 1) {
+        const int a0 = A.rp[i], a1 = A.rp[i + 1];
+        for (int k = a0 + lane; k < a1; k += L) acc -= 0.5 * y[1 + A.eid[k]] * (w[A.ci[k]] * inv);
+      }
+    }
+    acc = group_sum<L>(acc);
+    if (in && lane == 0) {
+      const double xi = w[i] * inv;
+      if (scaled) qcol[i] = xi;
+      double d = C.dg ? C.dg[i] : 0.0;
+      if (cons_kind == 0) d -= y[i];
+      else d -= c_tr * y[0];
+      double v = acc + d * xi;
+      if (j_coef != 0.0) v -= j_coef * qsum;
+      out[i] = v;
+    }
   }
 }
 
@@ -388,38 +580,107 @@ void launch_gram4(long n, int q, const double* V, double* part, int nb, hipStrea
   hipLaunchKernelGGL(k_gram4, dim3(nb), dim3(kBlock), 0, st, n, q, V, part);
 }
 
+// Blocks of the vector kernels: 256 rows each for small n (so that the columns of
+// a step are loaded in one trip), 1024 rows beyond, at most 1024.
 int vec_blocks(long n) {
-  long nb = (n + kBlock * 16 - 1) / (kBlock * 16);
+  long nb = n <= 65536 ? (n + kBlock - 1) / kBlock : (n + kBlock * 4 - 1) / (kBlock * 4);
   if (nb < 8) nb = 8;
   if (nb > 1024) nb = 1024;
   return (int)((nb + 7) / 8 * 8);
 }
 
-void launch_slack_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr,
-                     double j_coef, const DevScalars* sc, const double* x, double* out, hipStream_t st) {
-  if (C.nh > 0) launch_hub_rows<double>(C, 1, 0, x, C.hsum, nullptr, 0, st);
-  const long threads = C.n * kSpmvLpr;
-  const int nb = (int)((threads + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL(k_slack_mv, dim3(nb), dim3(kBlock), 0, st, C, cons_kind, A, y, c_tr, j_coef, sc, x, out);
+template <bool SUB, bool DOTS>
+static void launch_proj(long n, int ncol, const double* Q, long ldq, const LzCoef& hc, double* w, double* part,
+                        int pld, int nb, hipStream_t st, const BlockTab& tab) {
+#define ALMBM_PROJ(K) hipLaunchKernelGGL((K), dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, hc, w, part, pld, tab)
+  if constexpr (!DOTS) {  // nothing to keep from the subtraction
+    ALMBM_PROJ((k_lz_proj_wide<SUB, DOTS>));
+    return;
+  }
+  if (ncol <= 16) ALMBM_PROJ((k_lz_proj<16, SUB, DOTS>));
+  else if (ncol <= 32) ALMBM_PROJ((k_lz_proj<32, SUB, DOTS>));
+  else if (ncol <= 64) ALMBM_PROJ((k_lz_proj<64, SUB, DOTS>));
+  else ALMBM_PROJ((k_lz_proj_wide<SUB, DOTS>));
+#undef ALMBM_PROJ
 }
-void launch_slack_mv_tab(const Cost<double>& C, const double* y, const double* x, double* out, const BlockTab& tab,
-                         int nb, hipStream_t st) {
-  hipLaunchKernelGGL(k_slack_mv_tab, dim3(nb), dim3(kBlock), 0, st, C, y, x, out, tab);
+
+// Partial sums of few blocks are left to the next kernel, which adds them itself.
+static bool lz_consumer_sums(const VecBatch& vb, int nb) { return !vb.tab.inst && nb <= kLzFewBlocks; }
+
+static LzCoef lz_coef(double* h, const double* part, int pld, int nb, const VecBatch& vb) {
+  LzCoef hc;
+  if (lz_consumer_sums(vb, nb)) {
+    hc.part = part;
+    hc.nb = nb;
+    hc.pld = pld;
+    hc.out = h;
+  } else {
+    hc.h = h;
+    hc.hstride = vb.hstride;
+  }
+  return hc;
 }
-void launch_dots(long n, int ncol, const double* Q, long ldq, const double* w, double* part, int pstride, int nb,
-                 double* h, hipStream_t st, const VecBatch& vb) {
-  hipLaunchKernelGGL(k_dots, dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, w, part, pstride, vb.tab);
-  hipLaunchKernelGGL(k_fin_dots, dim3(ncol, vb.count), dim3(kBlock), 0, st, part, nb, pstride, ncol, h, vb.hstride,
+
+static void fin_dots(int ncol, const double* part, int pld, int nb, double* h, hipStream_t st, const VecBatch& vb) {
+  hipLaunchKernelGGL(k_fin_dots, dim3(ncol, vb.count), dim3(kBlock), 0, st, part, nb, pld, ncol, h, vb.hstride,
                      vb.tab);
 }
-void launch_sub(long n, int ncol, const double* Q, long ldq, const double* h, double* w, double* part, int nb,
-                hipStream_t st, const VecBatch& vb) {
-  hipLaunchKernelGGL(k_sub, dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, h, vb.hstride, w, part, vb.tab);
+
+void launch_dots(long n, int ncol, const double* Q, long ldq, double* w, double* part, int pld, int nb, double* h,
+                 hipStream_t st, const VecBatch& vb) {
+  launch_proj<false, true>(n, ncol, Q, ldq, LzCoef{}, w, part, pld, nb, st, vb.tab);
+  fin_dots(ncol, part, pld, nb, h, st, vb);
 }
-void launch_fin_ab(const double* part, int nb, const double* h1, const double* h2, int j, double* alpha, double* beta,
-                   hipStream_t st, const VecBatch& vb) {
-  hipLaunchKernelGGL(k_fin_ab, dim3(vb.count), dim3(kBlock), 0, st, part, nb, h1, h2, vb.hstride, j, alpha, beta,
-                     vb.astride, vb.tab);
+
+void launch_gs2(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_b, double* part_n,
+                int pld, int nb, double* h1, double* h2, hipStream_t st, const VecBatch& vb) {
+  const bool few = lz_consumer_sums(vb, nb);
+  launch_proj<false, true>(n, ncol, Q, ldq, LzCoef{}, w, part, pld, nb, st, vb.tab);
+  if (!few) fin_dots(ncol, part, pld, nb, h1, st, vb);
+  launch_proj<true, true>(n, ncol, Q, ldq, lz_coef(h1, part, pld, nb, vb), w, part_b, pld, nb, st, vb.tab);
+  if (!few) fin_dots(ncol, part_b, pld, nb, h2, st, vb);
+  launch_proj<true, false>(n, ncol, Q, ldq, lz_coef(h2, part_b, pld, nb, vb), w, part_n, pld, nb, st, vb.tab);
+}
+
+void launch_fin_ab(const double* part, int nb, int pld, const double* h1, const double* h2, int j, double* alpha,
+                   double* beta, double* qsum, hipStream_t st, const VecBatch& vb) {
+  hipLaunchKernelGGL(k_fin_ab, dim3(vb.count), dim3(kBlock), 0, st, part, nb, pld, h1, h2, vb.hstride, j, alpha, beta,
+                     vb.astride, qsum, vb.tab);
+}
+
+void launch_lz_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr, double j_coef,
+                  const double* qsum, const LzStep& s, const double* w, double* qcol, double* out, int nb,
+                  hipStream_t st, const VecBatch& vb) {
+  if (C.nh > 0) launch_hub_rows<double>(C, 1, 0, w, C.hsum, nullptr, 0, st);
+  LzScale sc;  // s.j = 0: w is the column itself
+  if (s.j > 0 && s.sums && lz_consumer_sums(vb, s.nb)) {
+    sc.part = s.part;
+    sc.nb = s.nb;
+    sc.pld = s.pld;
+    sc.h1 = s.h1;
+    sc.h2 = s.h2;
+    sc.alpha_out = s.alpha + s.j - 1;
+    sc.beta_out = s.beta + s.j - 1;
+    sc.jm1 = s.j - 1;
+  } else if (s.j > 0) {
+    sc.beta = s.beta + s.j - 1;
+    sc.bstride = vb.astride;
+  }
+  if (!vb.tab.inst) {
+    long g = (C.n + kBlock / kSpmvLpr - 1) / (kBlock / kSpmvLpr);
+    g = g < 8 ? 8 : (g > 8192 ? 8192 : g);
+    nb = (int)((g + 7) / 8 * 8);
+  }
+  hipLaunchKernelGGL(k_lz_mv, dim3(nb), dim3(kBlock), 0, st, C, cons_kind, A, y, c_tr, j_coef, qsum, sc, w, qcol, out,
+                     vb.tab);
+}
+void launch_slack_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr,
+                     double j_coef, const double* qsum, const double* x, double* out, hipStream_t st) {
+  launch_lz_mv(C, cons_kind, A, y, c_tr, j_coef, qsum, LzStep{}, x, nullptr, out, 0, st);
+}
+void launch_slack_mv_tab(const Cost<double>& C, const double* y, const double* x, double* out, int nb, hipStream_t st,
+                         const VecBatch& vb) {
+  launch_lz_mv(C, 0, EdgeAdj{}, y, 0.0, 0.0, nullptr, LzStep{}, x, nullptr, out, nb, st, vb);
 }
 void launch_scale(long n, const double* w, const double* beta, double* q, double* part, int nb, double* qsum,
                   hipStream_t st, const VecBatch& vb, int bstride) {

@@ -111,16 +111,43 @@ template <typename S, typename D>
 void launch_convert(long len, const S* src, D* dst, hipStream_t st);
 
 int vec_blocks(long n);
+// out = Z(y) x; qsum: 1^T x where the cost has a -J term.
 void launch_slack_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr,
-                     double j_coef, const DevScalars* sc, const double* x, double* out, hipStream_t st);
-void launch_slack_mv_tab(const Cost<double>& C, const double* y, const double* x, double* out, const BlockTab& tab,
-                         int nb, hipStream_t st);
-void launch_dots(long n, int ncol, const double* Q, long ldq, const double* w, double* part, int pstride, int nb,
-                 double* h, hipStream_t st, const VecBatch& vb = VecBatch{});
-void launch_sub(long n, int ncol, const double* Q, long ldq, const double* h, double* w, double* part, int nb,
-                hipStream_t st, const VecBatch& vb = VecBatch{});
-void launch_fin_ab(const double* part, int nb, const double* h1, const double* h2, int j, double* alpha, double* beta,
-                   hipStream_t st, const VecBatch& vb = VecBatch{});
+                     double j_coef, const double* qsum, const double* x, double* out, hipStream_t st);
+void launch_slack_mv_tab(const Cost<double>& C, const double* y, const double* x, double* out, int nb, hipStream_t st,
+                         const VecBatch& vb);
+// A step of the Lanczos recurrence.  The vector kernels leave partial sums per
+// block at part[c * pld + slot]; up to kLzFewBlocks of them are added by the
+// kernel that needs the total instead of by a finalizer of their own (single
+// instances: at 64 blocks, n = 16384, every block adds 64 values per column;
+// beyond, a finalizer costs less than the repeated sums).
+constexpr int kLzFewBlocks = 64;
+struct LzStep {
+  int j;               // column of this step
+  const double* part;  // partial sums of ||w||^2 and of w (launch_gs2's part_n)
+  int nb;
+  int pld;
+  const double* h1;    // projections of step j - 1
+  const double* h2;
+  double* alpha;       // tridiagonal entries
+  double* beta;
+  bool sums;           // step j - 1 ended without launch_fin_ab
+};
+// out = Z(y) q_j with q_j = w / beta_{j-1} stored at qcol; for j = 0 w is q_0.
+// qsum: 1^T q_j where the cost has a -J term (launch_fin_ab's, or q_0's).
+void launch_lz_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr, double j_coef,
+                  const double* qsum, const LzStep& s, const double* w, double* qcol, double* out, int nb,
+                  hipStream_t st, const VecBatch& vb = VecBatch{});
+// h = Q^T w (first ncol columns).
+void launch_dots(long n, int ncol, const double* Q, long ldq, double* w, double* part, int pld, int nb, double* h,
+                 hipStream_t st, const VecBatch& vb = VecBatch{});
+// Two classical Gram-Schmidt passes of w against the first ncol columns:
+// coefficients h1, h2; partial sums of ||w||^2 and of w in part_n (2 x pld).
+// part, part_b: ncol x pld.
+void launch_gs2(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_b, double* part_n,
+                int pld, int nb, double* h1, double* h2, hipStream_t st, const VecBatch& vb = VecBatch{});
+void launch_fin_ab(const double* part, int nb, int pld, const double* h1, const double* h2, int j, double* alpha,
+                   double* beta, double* qsum, hipStream_t st, const VecBatch& vb = VecBatch{});
 void launch_scale(long n, const double* w, const double* beta, double* q, double* part, int nb, double* qsum,
                   hipStream_t st, const VecBatch& vb = VecBatch{}, int bstride = 0);
 void launch_gather_flags(const DevScalars* sc, int count, int32_t* out, hipStream_t st);

@@ -98,3 +98,36 @@ def test_odd_ranks_wide_partial_rows(r, prec, tol):
     f_o, G_o, a_o, _ = oracle.objective_grad(po, R.double().cpu().numpy(), y, 0.7)
     f, G, Av = p.objective_grad(R, torch.from_numpy(y).to(DEV), 0.7)
     assert rel(G.double().cpu(), G_o) <= tol and rel(Av.cpu(), a_o) <= 2e-5
+
+
+@pytest.mark.parametrize("n,kmax", [(40, 39), (300, 120), (2000, 17), (2000, 33), (2000, 70), (16384, 40), (16400, 70),
+                                    (66000, 20)])
+def test_lanczos_step_shapes(n, kmax):
+    """Column counts on both sides of 16, 32 and 64, block counts on both sides of the 64 whose partial sums the
+    consumer adds, and rows that leave partial blocks, against the same recurrence in NumPy: after m steps theta is
+    the smallest Ritz value of the same Krylov space (FP64, full reorthogonalisation: 1e-9 of the spectrum's size)."""
+    g = gen.er_graph(n, 4 * n if n > 100 else 100, 3, "gauss")
+    po = oracle.maxcut_sdp(g)
+    p = _almbm().Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=4, lanczos_kmax=kmax, device=DEV)
+    y = np.random.default_rng(n).standard_normal(n)
+    theta, v, resid, iters = p.lanczos_min_eig(torch.from_numpy(y).to(DEV), max_iter=kmax, tol=1e30, seed=5)
+    m = min(kmax, 4 if n <= 4096 else 8)
+    assert iters == m
+    zmat = lambda x: oracle.cost_apply(po, x[:, None])[:, 0] - y * x  # noqa: E731
+    vh = v.cpu().numpy()
+    assert abs(np.linalg.norm(vh) - 1) <= 1e-12
+    scale = np.abs(y).max() + np.abs(g.w).max() * 8
+    assert abs(vh @ zmat(vh) - theta) <= 1e-12 * scale
+    assert abs(np.linalg.norm(zmat(vh) - theta * vh) - resid) <= 1e-10 * scale
+    theta, v, resid, iters = p.lanczos_min_eig(torch.from_numpy(y).to(DEV), max_iter=kmax, tol=0.0, seed=5)
+    vh = v.cpu().numpy()
+    assert abs(vh @ zmat(vh) - theta) <= 1e-11 * scale
+    assert abs(np.linalg.norm(zmat(vh) - theta * vh) - resid) <= 1e-9 * scale
+    if n <= 2000 and kmax >= 33:  # four passes of enough columns find the end of the spectrum
+        lam = oracle.min_eig(po, y)
+        assert lam - 1e-10 * scale <= theta <= lam + max(resid, 1e-10 * scale)
+    th, V, rs, basis = p.lanczos_block(torch.from_numpy(y).to(DEV), 3, max_iter=kmax, seed=2)
+    Vh = V.cpu().numpy()
+    assert np.abs(Vh.T @ Vh - np.eye(3)).max() <= 1e-10
+    for k in range(3):
+        assert abs(np.linalg.norm(zmat(Vh[:, k]) - th[k] * Vh[:, k]) - rs[k]) <= 1e-9 * scale
