@@ -113,9 +113,14 @@ __device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type, M>& A, 
   }
 }
 
-// Without a table the grid strides over all len elements.  With a table each
-// block takes the elements of its rows, [xbase + lo r, xbase + hi r) of its
-// instance (stored at width r), with the instance's own state and stop flag.
+// Without a table the vectors are shared out to vgrid virtual blocks (element
+// chunk q to thread q mod (vgrid kBlock)) and each block runs the virtual blocks
+// blockIdx.x, blockIdx.x + gridDim.x, ....  A virtual thread sums its chunks in
+// the arithmetic type and its sums are added in FP64, so that the rounding of
+// float sums depends on vgrid, a function of n, and not on the blocks launched.
+// With a table each block takes the elements of its rows, [xbase + lo r,
+// xbase + hi r) of its instance (stored at width r), with the instance's own
+// state and stop flag.
 //
 // Bound by HBM streaming (2 M + 3 vectors).  M bounds the pairs at compile
 // time: with the memory of 3 that solves use by default 19 accumulators remain
@@ -125,19 +130,20 @@ __device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type, M>& A, 
 template <typename T, int M>
 __global__ void __launch_bounds__(kBlock)
 k_lbfgs_dots(long len, int r, const T* __restrict__ G, LbfgsRing<RingT<T>> lb, double* __restrict__ part,
-             const DevScalars* __restrict__ sc_base, BlockTab tab) {
+             const DevScalars* __restrict__ sc_base, BlockTab tab, int vgrid) {
   using V = typename Acc<T>::type;
   using R = RingT<T>;
   constexpr int N = FlatVec<T>::N;
-  long a = 0, e = len, t0 = (long)blockIdx.x * kBlock + threadIdx.x, tstride = (long)gridDim.x * kBlock;
-  int inst = 0;
+  long a = 0, e = len;
+  int inst = 0, vb0 = blockIdx.x, vstep = gridDim.x;
   if (tab.inst) {
     inst = tab.inst[blockIdx.x];
     const long xb = row_base(tab, inst);
     a = xb + (long)tab.lo[blockIdx.x] * r;
     e = xb + (long)tab.hi[blockIdx.x] * r;
-    t0 = threadIdx.x;
-    tstride = kBlock;
+    vb0 = 0;
+    vgrid = 1;
+    vstep = 1;
   }
   if (sc_base[inst].flag) return;
   const LbfgsState* S = lb.s + inst;
@@ -153,28 +159,34 @@ k_lbfgs_dots(long len, int r, const T* __restrict__ G, LbfgsRing<RingT<T>> lb, d
     ea[a] = lb.e + (long)sl * lb.stride;
     ya[a] = lb.y + (long)sl * lb.stride;
   }
-  DotAcc<V, M> A;
-#pragma unroll
-  for (int a = 0; a <= M; ++a) A.gE[a] = A.gY[a] = A.kE[a] = A.kY[a] = V(0);
-#pragma unroll
-  for (int a = 0; a < M; ++a) A.eY[a] = V(0);
-  // element-wise head up to N-element alignment, N-element chunks, element-wise tail
-  const long pad = (N - a % N) % N;
-  const long a_al = a + pad < e ? a + pad : e;
-  for (long idx = a + t0; idx < a_al; idx += tstride) dots_chunk<T, 1, M>(A, idx, G, yk, ek, ea, ya, cnt, have);
-  const long nvec = (e - a_al) / N;
-  for (long q = t0; q < nvec; q += tstride) dots_chunk<T, N, M>(A, a_al + q * N, G, yk, ek, ea, ya, cnt, have);
-  for (long idx = a_al + nvec * N + t0; idx < e; idx += tstride)
-    dots_chunk<T, 1, M>(A, idx, G, yk, ek, ea, ya, cnt, have);
   constexpr int ND = lbfgs_dot_slots(M);
   double acc[ND];
 #pragma unroll
-  for (int a = 0; a <= M; ++a) {
-    acc[a] = (double)A.gE[a];
-    acc[M + 1 + a] = (double)A.gY[a];
-    acc[2 * (M + 1) + a] = (double)A.kE[a];
-    acc[3 * (M + 1) + a] = (double)A.kY[a];
-    acc[4 * (M + 1) + a] = a < M ? (double)A.eY[a] : 0.0;
+  for (int k = 0; k < ND; ++k) acc[k] = 0.0;
+  // element-wise head up to N-element alignment, N-element chunks, element-wise tail
+  const long pad = (N - a % N) % N;
+  const long a_al = a + pad < e ? a + pad : e;
+  const long nvec = (e - a_al) / N;
+  const long tstride = (long)vgrid * kBlock;
+  for (int vb = vb0; vb < vgrid; vb += vstep) {
+    const long t0 = (long)vb * kBlock + threadIdx.x;
+    DotAcc<V, M> A;
+#pragma unroll
+    for (int k = 0; k <= M; ++k) A.gE[k] = A.gY[k] = A.kE[k] = A.kY[k] = V(0);
+#pragma unroll
+    for (int k = 0; k < M; ++k) A.eY[k] = V(0);
+    for (long idx = a + t0; idx < a_al; idx += tstride) dots_chunk<T, 1, M>(A, idx, G, yk, ek, ea, ya, cnt, have);
+    for (long q = t0; q < nvec; q += tstride) dots_chunk<T, N, M>(A, a_al + q * N, G, yk, ek, ea, ya, cnt, have);
+    for (long idx = a_al + nvec * N + t0; idx < e; idx += tstride)
+      dots_chunk<T, 1, M>(A, idx, G, yk, ek, ea, ya, cnt, have);
+#pragma unroll
+    for (int k = 0; k <= M; ++k) {
+      acc[k] += (double)A.gE[k];
+      acc[M + 1 + k] += (double)A.gY[k];
+      acc[2 * (M + 1) + k] += (double)A.kE[k];
+      acc[3 * (M + 1) + k] += (double)A.kY[k];
+      if (k < M) acc[4 * (M + 1) + k] += (double)A.eY[k];
+    }
   }
   block_sum_many<ND>(acc, part + part_slot(tab) * ND);
 }
@@ -461,22 +473,25 @@ void launch_lbfgs_reset(LbfgsState* s, int m, hipStream_t st, int count) {
   hipLaunchKernelGGL(k_lbfgs_reset, dim3(count), dim3(64), 0, st, s, m);
 }
 
-// Blocks of the inner-product pass over len elements without a table: four
-// vector chunks per thread and at most eight blocks per CU, so that the block
-// sums and the finalizer's rows stay few.
-template <typename T> static int dots_blocks(long len, int cap) {
-  const long nb = (len / FlatVec<T>::N + 4 * kBlock - 1) / (4 * kBlock);
-  return (int)std::min<long>(std::min(cap, 2048), std::max<long>(8, nb));
-}
-
+// Without a table: one virtual block per 64 rows, up to 4096, on blocks of at
+// least four vector chunks per thread and at most eight blocks per CU, so that
+// the block sums and the finalizer's rows stay few.
 template <typename T>
 int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
                       const DevScalars* sc, hipStream_t st, const BlockTab& tab) {
-  if (!tab.inst) nb = dots_blocks<T>(len, nb);
+  int vgrid = 1;
+  if (!tab.inst) {
+    const long v = std::min<long>(4096, std::max<long>(8, (len / r + 63) / 64));
+    vgrid = (int)((v + 7) / 8 * 8);
+    const long b = (len / FlatVec<T>::N + 4 * kBlock - 1) / (4 * kBlock);
+    nb = (int)std::min<long>({(long)nb, (long)vgrid, std::max<long>(8, b)});
+    if (sizeof(typename Acc<T>::type) == 8) vgrid = nb;  // FP64 sums need no virtual blocks
+  }
   if (m <= 3)
-    hipLaunchKernelGGL((k_lbfgs_dots<T, 3>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab);
+    hipLaunchKernelGGL((k_lbfgs_dots<T, 3>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab, vgrid);
   else
-    hipLaunchKernelGGL((k_lbfgs_dots<T, kMaxLbfgs>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab);
+    hipLaunchKernelGGL((k_lbfgs_dots<T, kMaxLbfgs>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab,
+                       vgrid);
   return nb;
 }
 
