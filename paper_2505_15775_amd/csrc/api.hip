@@ -804,7 +804,8 @@ extern "C" alm_bm_status alm_bm_dual_update(alm_bm_problem* p, const double* Av,
 extern "C" alm_bm_status alm_bm_ws_features(alm_bm_problem* p, float* feats, float* scratch, hipStream_t st) {
   if (!p || !feats || !scratch) return fail(ALM_BM_ERR_INVALID_ARG, "ws_features: null argument");
   if (p->d.cons_kind != ALM_BM_CONS_DIAG) return fail(ALM_BM_ERR_UNSUPPORTED, "ws_features: DIAG family only");
-  launch_ws_features(p->C64, feats, scratch, st);
+  // the pass's 8-byte pairs need twice the caller's scratch: the handle's Av (n doubles) holds them
+  launch_ws_features(p->C64, feats, reinterpret_cast<float2*>(p->Av), st);
   HIPCHK(hipGetLastError());
   return ALM_BM_OK;
 }

@@ -173,7 +173,8 @@ void launch_resid(long n, const double* z, const double* v, double theta, const 
 void launch_quartic_norm(long n, int cons_kind, const EdgeAdj& A, const double* x, double* part, int nb,
                          hipStream_t st, const VecBatch& vb = VecBatch{});
 
-void launch_ws_features(const Cost<double>& C, float* F, float* ldeg, hipStream_t st);
+// pair: n float2 of scratch.
+void launch_ws_features(const Cost<double>& C, float* F, float2* pair, hipStream_t st);
 int ws_param_count(int nin, int h);
 bool launch_ws_forward(const float* P, int nin, int h, const float* mu, const float* isd, long n, const float* X,
                        double* out, hipStream_t st);

@@ -131,3 +131,48 @@ def test_lanczos_step_shapes(n, kmax):
     assert np.abs(Vh.T @ Vh - np.eye(3)).max() <= 1e-10
     for k in range(3):
         assert abs(np.linalg.norm(zmat(Vh[:, k]) - th[k] * Vh[:, k]) - rs[k]) <= 1e-9 * scale
+
+
+@pytest.mark.parametrize("h", [16, 32, 64])
+@pytest.mark.parametrize("nin,n,nblocks", [(8, 1, 1), (8, 31, 3), (5, 32, 1), (8, 33, 2), (1, 129, 4), (4, 1000, 7),
+                                           (8, 4097, 512), (3, 5000, 64)])
+def test_warm_start_network_tiles(h, nin, n, nblocks):
+    """Tiles of 32 vertices with every kind of remainder, narrow inputs and blocks without rows, against FP64
+    autograd.  FP32 products of at most 64 terms in two layers (and sums over n rows for the gradient): 1e-5."""
+    from paper_2505_15775_amd import warmstart
+
+    g = torch.Generator().manual_seed(n + h)
+    model = warmstart.WarmStartModel(nin=nin, h=h, device=DEV, seed=n)
+    model.params += 0.1 * torch.randn(model.params.shape, generator=g).to(DEV)
+    model.mu = torch.randn(8, generator=g).to(DEV)
+    model.inv_sd = (0.5 + torch.rand(8, generator=g)).to(DEV)
+    X, T = torch.randn((n, nin), generator=g).to(DEV), torch.randn(n, generator=g).to(DEV)
+    par = model.params.double().requires_grad_()
+    x, o, lay = (X.double() - model.mu[:nin].double()) * model.inv_sd[:nin].double(), 0, []
+    for k in (nin * h, h, h * h, h, h, 1):
+        lay.append(par[o:o + k])
+        o += k
+    z = torch.relu(x @ lay[0].view(nin, h) + lay[1])
+    out = torch.relu(z @ lay[2].view(h, h) + lay[3]) @ lay[4] + lay[5]
+    loss_o = ((out - T.double()) ** 2).mean()
+    loss_o.backward()
+
+    class Rows:
+        pass
+
+    prob = Rows()
+    prob.n = n
+    y = model.predict_y0(prob, X)
+    assert rel(y.cpu(), out.detach().cpu().numpy()) <= 1e-5
+    loss, grad = model.loss_grad(X, T, nblocks=nblocks)
+    assert abs(loss.item() - loss_o.item()) <= 1e-5 * loss_o.item()
+    assert rel(grad.double().cpu(), par.grad.cpu().numpy()) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [1, 2, 127, 128, 2049, 70001])
+def test_warm_start_pool_counts(n):
+    """Column means over row counts around the blocks' shares (FP64 sums of FP32 values)."""
+    from paper_2505_15775_amd import warmstart
+
+    F = torch.randn((n, 8), generator=torch.Generator().manual_seed(n)).to(DEV)
+    np.testing.assert_allclose(warmstart.pooled(F), F.double().mean(0).cpu().numpy(), rtol=1e-12, atol=1e-13)
