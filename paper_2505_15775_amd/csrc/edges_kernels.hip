@@ -470,25 +470,30 @@ k_fin_edges3(const double* __restrict__ part, int nb, int r, DevScalars* __restr
 
 // ---- launchers -----------------------------------------------------------------
 
-// Tile (lanes, columns per lane) for a rank r.  Up to r = 8 one or two lanes
-// hold a whole row: an edge or a neighbour per lane keeps the edge arrays'
-// loads dense and needs (almost) no shuffles.
+// Tile (lanes, columns per lane) for a rank r.  In FP64, up to r = 8 one or two
+// lanes hold a whole row: an edge or a neighbour per lane keeps the edge arrays'
+// loads dense and needs (almost) no shuffles.  The float types keep more lanes
+// per row, whose sums of few products round like a tree rather than a chain.
 #define ALMBM_DISPATCH_EDGES(T, FN, ...)                                \
   do {                                                                  \
-    if (r <= 4) FN<T, 1, 4>(__VA_ARGS__);                               \
-    else if (r <= 8) FN<T, 2, 4>(__VA_ARGS__);                          \
-    else if constexpr (sizeof(T) == 8) {                                \
-      if (r <= 16) FN<T, 8, 2>(__VA_ARGS__);                            \
+    if constexpr (sizeof(T) == 8) {                                     \
+      if (r <= 4) FN<T, 1, 4>(__VA_ARGS__);                             \
+      else if (r <= 8) FN<T, 2, 4>(__VA_ARGS__);                        \
+      else if (r <= 16) FN<T, 8, 2>(__VA_ARGS__);                       \
       else if (r <= 32) FN<T, 8, 4>(__VA_ARGS__);                       \
       else if (r <= 64) FN<T, 16, 4>(__VA_ARGS__);                      \
       else FN<T, 32, 4>(__VA_ARGS__);                                   \
     } else if constexpr (sizeof(T) == 4) {                              \
-      if (r <= 16) FN<T, 4, 4>(__VA_ARGS__);                            \
+      if (r <= 4) FN<T, 4, 1>(__VA_ARGS__);                             \
+      else if (r <= 8) FN<T, 4, 2>(__VA_ARGS__);                        \
+      else if (r <= 16) FN<T, 4, 4>(__VA_ARGS__);                       \
       else if (r <= 32) { if (variant == 1) FN<T, 4, 8>(__VA_ARGS__); else FN<T, 8, 4>(__VA_ARGS__); } \
       else if (r <= 64) FN<T, 16, 4>(__VA_ARGS__);                      \
       else FN<T, 32, 4>(__VA_ARGS__);                                   \
     } else {                                                            \
-      if (r <= 16) FN<T, 2, 8>(__VA_ARGS__);                            \
+      if (r <= 4) FN<T, 2, 2>(__VA_ARGS__);                             \
+      else if (r <= 8) FN<T, 2, 4>(__VA_ARGS__);                        \
+      else if (r <= 16) FN<T, 2, 8>(__VA_ARGS__);                       \
       else if (r <= 32) FN<T, 4, 8>(__VA_ARGS__);                       \
       else if (r <= 64) FN<T, 8, 8>(__VA_ARGS__);                       \
       else FN<T, 16, 8>(__VA_ARGS__);                                   \
@@ -518,14 +523,14 @@ static void p2_split(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int
                        c_tr, j_coef, G_in, G, part, sc, ncs);
 }
 // A wave per row when the average row has 8 neighbours for each of its 64 / LPR
-// groups.  With one or two lanes per neighbour (r <= 8) half a neighbour per
+// groups.  With one or two lanes per neighbour (FP64, r <= 8) half a neighbour per
 // group is enough: the alternative there is one lane walking a row alone, its
 // loads 64 rows apart.
 template <typename T, int LPR, int VEC>
 static void p2_cfg(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, const T* R, const double* wE,
                    double c_tr, double j_coef, const T* G_in, T* G, double* part, const DevScalars* sc, int nblk,
                    hipStream_t st, int ncs) {
-  const float least = LPR <= 2 ? 32.f : 8.f * (kWave / LPR);
+  const float least = LPR <= 2 && sizeof(T) == 8 ? 32.f : 8.f * (kWave / LPR);
   const bool split = A.avg_deg >= least, hass = C.rp || C.ell > 0;
 #define ALMBM_P2(S_, HASS_) \
   p2_split<T, LPR, VEC, S_, HASS_>(C, A, r, R, wE, c_tr, j_coef, G_in, G, part, sc, nblk, st, ncs)
