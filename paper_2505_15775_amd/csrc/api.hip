@@ -102,6 +102,7 @@ struct alm_bm_problem {
   double* hub_sum64 = nullptr;
   float* hub_sum32 = nullptr;
   long hub_cap = 0;
+  int32_t hubs = 0;               // hub rows at the current threshold
   LbfgsState* lbs = nullptr;      // L-BFGS state and rings (lbfgs_memory_max + 1 slots each)
   void* lb_e = nullptr;
   void* lb_y = nullptr;
@@ -163,15 +164,21 @@ static int32_t hub_threshold(long nnz, long n) {
 // in place after a device synchronisation (no allocation).
 static alm_bm_status build_hubs(alm_bm_problem* p, int32_t min_degree, bool reserve) {
   const auto& d = p->d;
-  for (auto* c : {&p->C64.nh, &p->C32.nh}) *c = 0;
+  for (auto* c : {&p->C64.nh, &p->C32.nh, &p->hubs}) *c = 0;
+  p->C64.skewed = p->C32.skewed = false;
   if (d.cons_kind != ALM_BM_CONS_DIAG || d.ell_width != 0 || d.nnz == 0 || min_degree < 0) return ALM_BM_OK;
   const long n = d.n;
   std::vector<int32_t> hrp(n + 1);
   HIPCHK(hipMemcpy(hrp.data(), d.row_ptr, (n + 1) * sizeof(int32_t), hipMemcpyDeviceToHost));
   const int32_t thr = min_degree == 0 ? hub_threshold(d.nnz, n) : min_degree;
   std::vector<int32_t> hubs;
+  long hub_nnz = 0, longest = 0;
   for (long i = 0; i < n; ++i)
-    if (hrp[i + 1] - hrp[i] > thr) hubs.push_back((int32_t)i);
+    if (const long k = hrp[i + 1] - hrp[i]; k > thr) {
+      hubs.push_back((int32_t)i);
+      hub_nnz += k;
+      longest = std::max(longest, k);
+    }
   const long nh = (long)hubs.size();
   if (reserve) {
     p->hub_cap = nh;
@@ -188,11 +195,18 @@ static alm_bm_status build_hubs(alm_bm_problem* p, int32_t min_degree, bool rese
   }
   if (nh == 0) return ALM_BM_OK;
   HIPCHK(hipMemcpy(p->hub_list, hubs.data(), nh * sizeof(int32_t), hipMemcpyHostToDevice));
+  p->hubs = (int32_t)nh;
+  p->C64.skewed = p->C32.skewed = 10 * hub_nnz > d.nnz;
   p->C64.hthr = thr;
   p->C64.hrow = p->hub_list;
   p->C64.hsum = p->hub_sum64;
   p->C64.hsum2 = p->hub_sum64 + nh * d.r_max;
-  p->C64.nh = (int32_t)nh;
+  // The default threshold also catches the few longest rows of a Poisson degree
+  // distribution (n = 193 176, average 18: rows of 37..45 entries).  Walking
+  // those with one lane group costs less than a launch before every product
+  // (5 us of a 235 us L-BFGS step, twice); FP64 products then have no hubs.
+  const bool few = min_degree == 0 && 100 * hub_nnz < d.nnz && longest <= 4L * thr;
+  p->C64.nh = few ? 0 : (int32_t)nh;
   if (d.precision != ALM_BM_F64) {
     p->C32.hthr = thr;
     p->C32.hrow = p->hub_list;
@@ -538,6 +552,11 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   // ---- workspace
   p->nblk = row_blocks(n);
   p->max_blocks = std::max(p->nblk, max_row_blocks(n));
+  // Skewed row lengths: more blocks to even out the long ones, and a count that is no
+  // power of two (R-MAT row lengths follow the bits of the row number, which would
+  // line up with the XCD a block runs on).  R-MAT 2^18, r = 16, FP64 evaluation:
+  // 157 us with 1024 blocks, 162 with 2048, 136 with 1536; at most n / 64 of them.
+  if (p->C64.skewed && p->nblk == 1024) p->nblk = (int)std::min<long>(1536, (n + 511) / 512 * 8);
   // long edge-family rows (each split over a whole wave) need more, shorter blocks to fill the chip
   if (d.cons_kind == ALM_BM_CONS_TRACE_EDGES && p->adj.avg_deg >= 32.f) p->nblk = std::min(1024, max_row_blocks(n));
   const size_t es = esize(d.precision);
@@ -550,7 +569,7 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   CK(dalloc(p, &p->Qbuf, (size_t)n * d.r_max * (d.precision == ALM_BM_F64 ? 8 : 4)));
   CK(dalloc_t(p, &p->Av, d.m));
   CK(dalloc_t(p, &p->ybuf, d.m));
-  p->lnb = vec_blocks(n);
+  p->lnb = vec_blocks(n, p->C64.nh > 0);
   CK(dalloc_t(p, &p->part_vec, (size_t)std::max(p->lnb, dual_blocks(d.m)) * 2 + 16));
   {
     hipError_t e = hipHostMalloc((void**)&p->sc_host, sizeof(DevScalars), hipHostMallocDefault);
@@ -922,7 +941,7 @@ extern "C" alm_bm_status alm_bm_set_hub_threshold(alm_bm_problem* p, int32_t min
   if (!p) return fail(ALM_BM_ERR_INVALID_ARG, "set_hub_threshold: null handle");
   if (p->tab.inst) return fail(ALM_BM_ERR_UNSUPPORTED, "set_hub_threshold: not on a batch");
   STCHK(build_hubs(p, min_degree, false));
-  if (hubs_out) *hubs_out = p->C64.nh;
+  if (hubs_out) *hubs_out = p->hubs;
   return ALM_BM_OK;
 }
 
@@ -1262,17 +1281,25 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   int m = 0;
   double theta = 0.0;
   bool sums = false;
+  const bool ordered = p->C64.nh > 0;  // hub rows (DIAG family)
   const int check_every = n <= 4096 ? 4 : 8;
   for (int j = 0; j < kmax; ++j) {
     const bool last = (j + 1 == kmax);
     const bool check = ((j + 1) % check_every) == 0 || last;
-    double* wj = j & 1 ? p->lw2 : p->lw;  // Z q_j, then the next column before scaling
-    const LzStep step{j, p->lpart2, nb, p->lnb, p->lh1, p->lh2, p->lalpha, p->lbeta, sums};
-    launch_lz_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, step, j == 0 ? p->Q : (j & 1 ? p->lw : p->lw2),
-                 p->Q + (long)j * ldq, wj, nb, st);
-    launch_gs2(n, j + 1, p->Q, ldq, wj, p->lpart, p->lpartb, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
-    sums = !check && nb <= kLzFewBlocks;
-    if (!sums) launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, qsum, st);
+    if (ordered) {
+      launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, p->Q + (long)j * ldq, p->lw, st);
+      launch_gs2_ordered(n, j + 1, p->Q, ldq, p->lw, p->lpart, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
+      launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, nullptr, st);
+      launch_scale(n, p->lw, p->lbeta + j, p->Q + (long)(j + 1) * ldq, p->lpart2, nb, nullptr, st);
+    } else {
+      double* wj = j & 1 ? p->lw2 : p->lw;  // Z q_j, then the next column before scaling
+      const LzStep step{j, p->lpart2, nb, p->lnb, p->lh1, p->lh2, p->lalpha, p->lbeta, sums};
+      launch_lz_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, step,
+                   j == 0 ? p->Q : (j & 1 ? p->lw : p->lw2), p->Q + (long)j * ldq, wj, nb, st);
+      launch_gs2(n, j + 1, p->Q, ldq, wj, p->lpart, p->lpartb, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
+      sums = !check && nb <= kLzFewBlocks;
+      if (!sums) launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, qsum, st);
+    }
     if (check) {
       HIPCHK(hipMemcpyAsync(ha.data(), p->lalpha, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
       HIPCHK(hipMemcpyAsync(hb.data(), p->lbeta, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));

@@ -252,14 +252,16 @@ __device__ __forceinline__ void fin_rows(const double* __restrict__ part, int ro
 // Rows owned by this block: the row range is split into gridDim.x contiguous
 // chunks and blocks are renumbered so that the blocks the hardware sends to one
 // XCD (blockIdx % 8 equal) own one contiguous eighth of the rows; neighbour rows
-// of banded or mesh-like patterns then stay in that XCD's L2.
+// of banded or mesh-like patterns then stay in that XCD's L2.  With spread the
+// blocks keep their order, so that consecutive chunks go to different XCDs:
+// where the row lengths are skewed, the long rows often sit together.
 struct RowChunk {
   long lo, hi;
 };
-__device__ __forceinline__ RowChunk row_chunk(long n) {
+__device__ __forceinline__ RowChunk row_chunk(long n, bool spread = false) {
   const long nb = gridDim.x;
   long vb = blockIdx.x;
-  if (nb % kNumXcd == 0) {
+  if (nb % kNumXcd == 0 && !spread) {
     const long per = nb / kNumXcd;
     vb = (blockIdx.x % kNumXcd) * per + blockIdx.x / kNumXcd;
   }

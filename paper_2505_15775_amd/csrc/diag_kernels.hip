@@ -22,7 +22,7 @@ k_objgrad_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ R,
                T* __restrict__ G, double* __restrict__ Av, double* __restrict__ part,
                const DevScalars* __restrict__ sc_base, int refresh_every, BlockTab tab, LbfgsRing<RingT<T>> lb) {
   using V = typename Acc<T>::type;
-  const Rows ch = rows_of(C.n, tab);
+  const Rows ch = rows_of(C.n, tab, C.skewed);
   const DevScalars* sc = sc_base ? sc_base + ch.inst : nullptr;
   if (sc && sc->flag) return;
   // inside the inner loop this full pass runs only on refresh iterations
@@ -111,7 +111,7 @@ k_quad_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ G,
   const int lane = threadIdx.x % LPR;
   const int slot = threadIdx.x / LPR;
   double acc[1] = {0.0};
-  const RowChunk ch = row_chunk(C.n);
+  const RowChunk ch = row_chunk(C.n, C.skewed);
   for (long base = ch.lo; base < ch.hi; base += RPB) {
     const long i = base + slot;
     if (i >= ch.hi) break;
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(kBlock)
 k_quadq_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ G, typename Acc<T>::type* __restrict__ Q,
              double* __restrict__ part, const DevScalars* __restrict__ sc_base, BlockTab tab, LbfgsRing<T> lb) {
   using V = typename Acc<T>::type;
-  const Rows ch = rows_of(C.n, tab);
+  const Rows ch = rows_of(C.n, tab, C.skewed);
   if (sc_base && sc_base[ch.inst].flag) return;
   if (lb.s) G = lb.e + (long)lb.s[ch.inst].cur * lb.stride;  // L-BFGS: the product of the direction E
   constexpr int RPB = kBlock / LPR;
@@ -286,7 +286,7 @@ k_ls_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ R, const T
   acc.zero();
   Cost<V> CG = C;  // the product C G reads its hub sums from hsum2
   CG.hsum = C.hsum2;
-  const RowChunk ch = row_chunk(C.n);
+  const RowChunk ch = row_chunk(C.n, C.skewed);
   for (long base = ch.lo; base < ch.hi; base += RPB) {
     const long i = base + slot;
     if (i >= ch.hi) break;
@@ -336,12 +336,39 @@ k_ls_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ R, const T
 
 // ---- launchers -----------------------------------------------------------------
 
+// p += sum of S_ik X_k over the U entries k, k + step, ... (those below k1) of a
+// hub row, in that order, with all U gathers in flight.
+template <typename T, int LPR, int VEC, bool FULL, int U>
+__device__ __forceinline__ void hub_chunk(const Cost<typename Acc<T>::type>& C, long i, long k, long k1, int step, int r,
+                                          int lane, const T* __restrict__ X, typename Acc<T>::type (&p)[VEC]) {
+  using V = typename Acc<T>::type;
+  int j[U];
+  V c[U], x[U][VEC];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const long kk = k + (long)u * step;
+    const bool in = kk < k1;
+    j[u] = in ? C.ci[kk] : (int)i;
+    c[u] = in ? C.cv[kk] : V(0);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) load_frag<T, VEC, FULL>(X + (long)j[u] * r, lane, r, x[u]);
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) p[v] += c[u] * x[u][v];
+}
+
 // Neighbour sums of the hub rows (see Cost): out[h, :] = sum_k S_ik X_k for
 // i = hrow[h], without the diagonal term.  One block per hub: its kBlock/LPR
-// lane groups take every (kBlock/LPR)-th entry of the row with kUnroll gathers
-// in flight each, and the groups' sums are added in group order, so the result
-// does not depend on timing.  The same early exits as the row kernel that
-// consumes the sums (converged flag, non-refresh iterations).
+// lane groups take every (kBlock/LPR)-th entry of the row, and the groups' sums
+// are added in group order, so the result does not depend on timing.  The
+// largest hub is a serial chain of gather latencies in one block and bounds the
+// kernel on small graphs, so while more than two rounds of kUnroll entries per
+// group remain, kHubUnroll are in flight: R-MAT 2^18 (1.9e6 edges), r = 16,
+// FP64: 179 us with four entries always, 72 us.  The same early exits as the row kernel that consumes the sums
+// (converged flag, non-refresh iterations).
+constexpr int kHubUnroll = 16;
 template <typename T, int LPR, int VEC, bool FULL>
 __global__ void __launch_bounds__(kBlock)
 k_hub_rows(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ X, typename Acc<T>::type* __restrict__ out,
@@ -351,37 +378,30 @@ k_hub_rows(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ X, typena
   if (sc && refresh_every > 1 && (sc->iter % refresh_every) != 0) return;
   if (lb.s) X = lb.e + (long)lb.s->cur * lb.stride;  // L-BFGS line-search product: the direction E
   constexpr int NG = kBlock / LPR;
-  constexpr int U = kUnroll;
   const int lane = threadIdx.x % LPR;
   const int grp = threadIdx.x / LPR;
   __shared__ V buf[NG][LPR * VEC];
   for (long h = blockIdx.x; h < C.nh; h += gridDim.x) {
     const long i = C.hrow[h];
-    const long k0 = C.rp[i], k1 = C.rp[i + 1];
+    const long k1 = C.rp[i + 1];
     V p[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) p[v] = V(0);
-    for (long k = k0 + grp; k < k1; k += (long)NG * U) {
-      V x[U][VEC];
-      V c[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const long kk = k + (long)u * NG;
-        const bool in = kk < k1;
-        const int j = in ? C.ci[kk] : (int)i;
-        c[u] = in ? C.cv[kk] : V(0);
-        load_frag<T, VEC, FULL>(X + (long)j * r, lane, r, x[u]);
+    for (long kb = C.rp[i]; kb < k1;) {  // the same trips for every group
+      if (k1 - kb > 2L * NG * kUnroll) {
+        hub_chunk<T, LPR, VEC, FULL, kHubUnroll>(C, i, kb + grp, k1, NG, r, lane, X, p);
+        kb += (long)NG * kHubUnroll;
+      } else {
+        hub_chunk<T, LPR, VEC, FULL, kUnroll>(C, i, kb + grp, k1, NG, r, lane, X, p);
+        kb += (long)NG * kUnroll;
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) p[v] += c[u] * x[u][v];
     }
 #pragma unroll
     for (int v = 0; v < VEC; ++v) buf[grp][lane * VEC + v] = p[v];
     __syncthreads();
     for (int c = threadIdx.x; c < r; c += kBlock) {
       V s = V(0);
+#pragma unroll 8
       for (int g = 0; g < NG; ++g) s += buf[g][c];
       out[h * r + c] = s;
     }

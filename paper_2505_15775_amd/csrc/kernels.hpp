@@ -119,6 +119,7 @@ template <typename V> struct Cost {
   const int32_t* hrow = nullptr;
   V* hsum = nullptr;
   V* hsum2 = nullptr;
+  bool skewed = false;  // the hub rows hold much of the pattern: see row_chunk's spread
 };
 
 // Position of hub row i in C.hrow (i must be a hub).
@@ -172,9 +173,9 @@ struct Rows {
   int inst;
 };
 
-__device__ __forceinline__ Rows rows_of(long n, const BlockTab& t) {
+__device__ __forceinline__ Rows rows_of(long n, const BlockTab& t, bool spread = false) {
   if (!t.inst) {
-    const RowChunk c = row_chunk(n);
+    const RowChunk c = row_chunk(n, spread);
     return {c.lo, c.hi, 0};
   }
   return {(long)t.lo[blockIdx.x], (long)t.hi[blockIdx.x], t.inst[blockIdx.x]};

@@ -198,6 +198,64 @@ k_lz_proj_wide(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef 
   }
 }
 
+// The same projections with every sum in a fixed order of its own (costs with hub
+// rows, launch_gs2_ordered): a wave per column and row chunk, four running sums
+// per lane; the subtraction column by column; the norm over row chunks.
+__global__ void __launch_bounds__(kBlock)
+k_dots_ordered(long n, int ncol, const double* __restrict__ Q, long ldq, const double* __restrict__ w,
+               double* __restrict__ part, int pld) {
+  const RowChunk ch = row_chunk(n);
+  const int lane = threadIdx.x % kWave;
+  const int c = blockIdx.y * (kBlock / kWave) + threadIdx.x / kWave;
+  if (c >= ncol) return;
+  const double* q = Q + (long)c * ldq;
+  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  long i = ch.lo + lane;
+#pragma unroll 4
+  for (; i + 3 * kWave < ch.hi; i += 4 * kWave) {
+    a0 += q[i] * w[i];
+    a1 += q[i + kWave] * w[i + kWave];
+    a2 += q[i + 2 * kWave] * w[i + 2 * kWave];
+    a3 += q[i + 3 * kWave] * w[i + 3 * kWave];
+  }
+  for (; i < ch.hi; i += kWave) a0 += q[i] * w[i];
+  const double a = wave_sum((a0 + a1) + (a2 + a3));
+  if (lane == 0) part[(long)c * pld + blockIdx.x] = a;
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_sub_ordered(long n, int ncol, const double* __restrict__ Q, long ldq, const double* __restrict__ h,
+              double* __restrict__ w) {
+  constexpr int CS = 16;
+  __shared__ double hs[512 + CS];
+  LzCoef hc;
+  hc.h = h;
+  load_coef(hc, 0, ncol, hs);
+  const long i = (long)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  double v = w[i];
+  for (int c0 = 0; c0 < ncol; c0 += CS) {
+    double q[CS];
+#pragma unroll
+    for (int c = 0; c < CS; ++c) q[c] = Q[(long)(c0 + c < ncol ? c0 + c : ncol - 1) * ldq + i];
+#pragma unroll
+    for (int c = 0; c < CS; ++c) v -= q[c] * hs[c0 + c];
+  }
+  w[i] = v;
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_norm_ordered(long n, const double* __restrict__ w, double* __restrict__ part, int pld) {
+  const RowChunk ch = row_chunk(n);
+  double acc[1] = {0.0};
+  for (long i = ch.lo + threadIdx.x; i < ch.hi; i += kBlock) {
+    const double v = w[i];
+    acc[0] += v * v;
+  }
+  block_sum_store<1>(acc, part + blockIdx.x);
+  if (threadIdx.x == 0) part[(long)pld + blockIdx.x] = 0.0;  // the sum of w is for -J terms only
+}
+
 // h[q][c] = sum of the block partials of column c over instance q's blocks
 // (grid: columns x instances, fixed order).
 __global__ void __launch_bounds__(kBlock)
@@ -274,7 +332,7 @@ k_lz_mv(Cost<double> C, int cons_kind, EdgeAdj A, const double* __restrict__ y, 
   constexpr int L = kSpmvLpr;
   constexpr int U = 4;
   constexpr int RPB = kBlock / L;
-  const Rows ch = rows_of(C.n, tab);
+  const Rows ch = rows_of(C.n, tab, C.skewed);
   const int lane = threadIdx.x % L;
   double inv = 1.0, qsum = (j_coef != 0.0 && qsum_in) ? *qsum_in : 0.0;
   const bool scaled = sc.part || sc.beta;
@@ -581,8 +639,14 @@ void launch_gram4(long n, int q, const double* V, double* part, int nb, hipStrea
 }
 
 // Blocks of the vector kernels: 256 rows each for small n (so that the columns of
-// a step are loaded in one trip), 1024 rows beyond, at most 1024.
-int vec_blocks(long n) {
+// a step are loaded in one trip), 1024 rows beyond, at most 1024.  For the
+// ordered steps chunks of 4096 rows, at least 8.
+int vec_blocks(long n, bool ordered) {
+  if (ordered) {
+    long nb = (n + kBlock * 16 - 1) / (kBlock * 16);
+    nb = nb < 8 ? 8 : (nb > 1024 ? 1024 : nb);
+    return (int)((nb + 7) / 8 * 8);
+  }
   long nb = n <= 65536 ? (n + kBlock - 1) / kBlock : (n + kBlock * 4 - 1) / (kBlock * 4);
   if (nb < 8) nb = 8;
   if (nb > 1024) nb = 1024;
@@ -640,6 +704,18 @@ void launch_gs2(long n, int ncol, const double* Q, long ldq, double* w, double* 
   launch_proj<true, true>(n, ncol, Q, ldq, lz_coef(h1, part, pld, nb, vb), w, part_b, pld, nb, st, vb.tab);
   if (!few) fin_dots(ncol, part_b, pld, nb, h2, st, vb);
   launch_proj<true, false>(n, ncol, Q, ldq, lz_coef(h2, part_b, pld, nb, vb), w, part_n, pld, nb, st, vb.tab);
+}
+
+void launch_gs2_ordered(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_n, int pld,
+                        int nb, double* h1, double* h2, hipStream_t st) {
+  const dim3 cols(nb, (ncol + kBlock / kWave - 1) / (kBlock / kWave));
+  const int rows = (int)((n + kBlock - 1) / kBlock);
+  for (double* h : {h1, h2}) {
+    hipLaunchKernelGGL(k_dots_ordered, cols, dim3(kBlock), 0, st, n, ncol, Q, ldq, w, part, pld);
+    fin_dots(ncol, part, pld, nb, h, st, VecBatch{});
+    hipLaunchKernelGGL(k_sub_ordered, dim3(rows), dim3(kBlock), 0, st, n, ncol, Q, ldq, h, w);
+  }
+  hipLaunchKernelGGL(k_norm_ordered, dim3(nb), dim3(kBlock), 0, st, n, w, part_n, pld);
 }
 
 void launch_fin_ab(const double* part, int nb, int pld, const double* h1, const double* h2, int j, double* alpha,

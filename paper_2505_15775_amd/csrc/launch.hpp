@@ -110,7 +110,7 @@ void launch_relayout(long n, int ss, int nc, int rd, const T* src, T* dst, const
 template <typename S, typename D>
 void launch_convert(long len, const S* src, D* dst, hipStream_t st);
 
-int vec_blocks(long n);
+int vec_blocks(long n, bool ordered = false);
 // out = Z(y) x; qsum: 1^T x where the cost has a -J term.
 void launch_slack_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr,
                      double j_coef, const double* qsum, const double* x, double* out, hipStream_t st);
@@ -146,6 +146,15 @@ void launch_dots(long n, int ncol, const double* Q, long ldq, double* w, double*
 // part, part_b: ncol x pld.
 void launch_gs2(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_b, double* part_n,
                 int pld, int nb, double* h1, double* h2, hipStream_t st, const VecBatch& vb = VecBatch{});
+// launch_gs2 with sums whose order follows from n and nb alone (single
+// instances).  Costs with hub rows take it: their largest eigenvalues are far
+// from the rest, and a pass restarted from a Ritz vector, in which those
+// directions are only rounding noise, brings the noise back to size one, so
+// that a different order of sums gives another residual (R-MAT 2^13, four
+// passes: 5 % apart; 1e-13 on Poisson degrees).  The order is the price of a
+// fourth read of the basis.
+void launch_gs2_ordered(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_n, int pld,
+                        int nb, double* h1, double* h2, hipStream_t st);
 void launch_fin_ab(const double* part, int nb, int pld, const double* h1, const double* h2, int j, double* alpha,
                    double* beta, double* qsum, hipStream_t st, const VecBatch& vb = VecBatch{});
 void launch_scale(long n, const double* w, const double* beta, double* q, double* part, int nb, double* qsum,

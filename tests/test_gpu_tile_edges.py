@@ -176,3 +176,31 @@ def test_warm_start_pool_counts(n):
 
     F = torch.randn((n, 8), generator=torch.Generator().manual_seed(n)).to(DEV)
     np.testing.assert_allclose(warmstart.pooled(F), F.double().mean(0).cpu().numpy(), rtol=1e-12, atol=1e-13)
+
+
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-13), ("f32", 1e-5), ("bf16", 1e-2)])
+@pytest.mark.parametrize("r", [1, 7, 16, 48])
+def test_hub_rows_of_every_trip_count(prec, tol, r):
+    """Hub rows on both sides of the wide and narrow trips of the hub kernel (its groups take 4 or 16 entries each),
+    with a cost skewed enough to spread the row chunks.  Sums of up to 9000 products per row: FP64 1e-13, float 1e-5
+    of the largest row, bfloat16 factors exact on input."""
+    rng = np.random.default_rng(r)
+    degs = [33, 64, 127, 129, 255, 256, 257, 511, 513, 1023, 1025, 2049, 4097, 9000]
+    n = 20000
+    ei = np.concatenate([np.full(d, h) for h, d in enumerate(degs)])
+    ej = np.concatenate([np.sort(rng.choice(n - 100, size=d, replace=False)) + 100 for d in degs])
+    g = gen.Graph(n, ei, ej, rng.standard_normal(ei.size))
+    po = oracle.maxcut_sdp(g)
+    p = _almbm().Problem.maxcut(g.n, g.ei, g.ej, g.w, precision=prec, r_max=48, lanczos_kmax=30, device=DEV)
+    assert p.set_hub_threshold(0) == len(degs)
+    X = p.factor(rng.standard_normal((n, r)))
+    P_o = oracle.cost_apply(po, X.double().cpu().numpy())
+    P = p.cost_apply(X).double().cpu().numpy()
+    assert np.abs(P - P_o).max() <= tol * np.abs(P_o).max()
+    if prec == "f64":
+        y = rng.standard_normal(n)
+        theta, v, resid, iters = p.lanczos_min_eig(torch.from_numpy(y).to(DEV), max_iter=30, tol=0.0, seed=5)
+        vh = v.cpu().numpy()
+        z = oracle.cost_apply(po, vh[:, None])[:, 0] - y * vh
+        scale = np.abs(P_o).max() + 5
+        assert abs(vh @ z - theta) <= 1e-12 * scale and abs(np.linalg.norm(z - theta * vh) - resid) <= 1e-10 * scale
