@@ -50,8 +50,8 @@
  *     descriptor (r_max, lanczos_kmax, rank_block_max, lbfgs_memory_max,
  *     hub_min_degree; BF16 handles also reserve the float factor of the
  *     precision ladder).  No other call allocates device memory, except that
- *     alm_bm_solve, alm_bm_inner_solve and alm_bm_batch_solve instantiate HIP
- *     graphs of their inner loops (runtime-owned).
+ *     alm_bm_batch_solve instantiates HIP graphs of its inner loop
+ *     (runtime-owned).
  */
 #ifndef ALM_BM_H
 #define ALM_BM_H
@@ -148,7 +148,9 @@ typedef struct {
   int32_t lanczos_kmax;      /* 0 -> the handle's lanczos_kmax                        */
   double lanczos_tol_rel;    /* 0.1    Ritz residual <= 0.1 eps (1 + ||C||_F)         */
   uint64_t seed;             /* 1      Lanczos start vector                            */
-  int32_t graph_unroll;      /* 8      inner iterations per captured HIP graph; 0 = no graph */
+  int32_t graph_unroll;      /* 8      inner iterations enqueued between two looks at the
+                                stop flag (0: one); batched solves replay a captured
+                                HIP graph of that many once a running set lasts   */
   int32_t verbose;           /* 0      1: one line per outer iteration on stderr      */
   double time_limit_s;       /* 0      > 0: stop (NOT_CONVERGED) after this wall time  */
   int32_t bf16_promote;      /* 1      BF16 handle: ladder to float storage when stalled */

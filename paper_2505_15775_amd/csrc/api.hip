@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cfloat>
 #include <chrono>
 #include <cmath>
@@ -10,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "alm_bm.h"
@@ -91,6 +93,8 @@ struct alm_bm_problem {
   double* lv = nullptr;
   double* ls = nullptr;
   double* lscal = nullptr;
+  double* lz_host = nullptr;      // pinned: two buffers of kmax + 1 alpha, kmax + 1 beta
+  hipEvent_t lz_ev[2] = {};
   std::vector<void*> allocs;
   double* bk_h = nullptr;         // block Krylov: (kmax+1)^2 projected matrix, column sums, Ritz coefficients
   double* bk_colsum = nullptr;
@@ -141,6 +145,12 @@ static void free_all(alm_bm_problem* p) {
   p->ss = nullptr;
   if (p->sc_host) (void)hipHostFree(p->sc_host);
   p->sc_host = nullptr;
+  if (p->lz_host) (void)hipHostFree(p->lz_host);
+  p->lz_host = nullptr;
+  for (hipEvent_t& e : p->lz_ev) {
+    if (e) (void)hipEventDestroy(e);
+    e = nullptr;
+  }
 }
 
 template <typename T> static const Cost<typename Acc<T>::type>& cost_of(const alm_bm_problem* p);
@@ -590,6 +600,9 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
     CK(dalloc_t(p, &p->lbeta, p->kmax + 1));
     CK(dalloc_t(p, &p->ls, p->kmax + 1));
     CK(dalloc_t(p, &p->lscal, 8));
+    if (hipHostMalloc((void**)&p->lz_host, (size_t)(p->kmax + 1) * 4 * sizeof(double), hipHostMallocDefault) != hipSuccess)
+      return bail(fail(ALM_BM_ERR_OOM, "hipHostMalloc failed"));
+    for (hipEvent_t& e : p->lz_ev) HK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     CK(dalloc_t(p, &p->lpart, (size_t)p->lnb * (p->kmax + 1)));
     CK(dalloc_t(p, &p->lpartb, (size_t)p->lnb * (p->kmax + 1)));
     CK(dalloc_t(p, &p->lpart2, (size_t)p->lnb * 2));
@@ -664,9 +677,11 @@ static void enqueue_objgrad(alm_bm_problem* p, int r, const T* R, const double* 
 // stop test, line-search product Q = C G, step choice.  One sparse product per
 // step except on refresh steps.
 // TRACE_EDGES family: full evaluation, stop test, line search, update.
+// step: its number from the start of the subproblem, which leaves out the pass
+// that would do nothing in it.
 template <typename T>
 static void enqueue_inner_step(alm_bm_problem* p, int r, T* R, const double* y, double sigma, T* G, int refresh,
-                               hipStream_t st) {
+                               hipStream_t st, int step) {
   using V = typename Acc<T>::type;
   const auto& d = p->d;
   DevScalars* sc = p->sc_solve;
@@ -674,10 +689,12 @@ static void enqueue_inner_step(alm_bm_problem* p, int r, T* R, const double* y, 
     V* Q = static_cast<V*>(p->Qbuf);
     using S = RingT<T>;
     const LbfgsRing<S> lb = lbfgs_ring<S>(p);  // empty: gradient descent
-    launch_upd_eval_diag<T>(d.n, r, p->variant, R, G, Q, y, d.b, sigma, p->Av, p->part, sc, refresh, p->tab, p->nblk,
-                            st, lb);
-    launch_objgrad_diag<T>(cost_of<T>(p), r, p->variant, R, y, d.b, sigma, G, p->Av, p->part, sc, refresh, p->tab,
-                           p->nblk, st, lb);
+    if (step != 0)
+      launch_upd_eval_diag<T>(d.n, r, p->variant, R, G, Q, y, d.b, sigma, p->Av, p->part, sc, refresh, p->tab, p->nblk,
+                              st, lb);
+    if (refresh <= 1 || step % refresh == 0)
+      launch_objgrad_diag<T>(cost_of<T>(p), r, p->variant, R, y, d.b, sigma, G, p->Av, p->part, sc, refresh, p->tab,
+                             p->nblk, st, lb);
     launch_fin_objgrad(p->part, p->nblk, sc, sigma, 1, nullptr, st, p->tab, p->count);
     if (lb.s) {
       // L-BFGS: the direction E = H G and its line-search totals replace G's;
@@ -1248,6 +1265,9 @@ extern "C" alm_bm_status alm_bm_psd_step(int32_t q, const double* theta, const d
   return ALM_BM_OK;
 }
 
+// Rows up to which a Lanczos pass runs ahead of its checks (lanczos_pass).
+constexpr long kLzAheadRows = 65536;
+
 struct LanczosOut {
   double theta = 0.0;
   double resid = 0.0;
@@ -1283,6 +1303,40 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   bool sums = false;
   const bool ordered = p->C64.nh > 0;  // hub rows (DIAG family)
   const int check_every = n <= 4096 ? 4 : 8;
+  // Small problems: the next steps are enqueued before the host looks at a check,
+  // so that the device does not wait for the tridiagonal eigenproblem (about 60
+  // us with the copies, every 4 steps of 20 us at n = 2000).  Steps enqueued
+  // past the one that ends the pass are not used; at most 8 of 30 us at 65536
+  // rows, they cost less than the waits of the checks before, beyond more.
+  const bool ahead = n <= kLzAheadRows;
+  int slot = 0, pending = 0;  // pending: steps of the check not yet looked at
+  auto host_a = [&](int s) { return p->lz_host + (size_t)s * 2 * (p->kmax + 1); };
+  auto host_b = [&](int s) { return host_a(s) + (p->kmax + 1); };
+  // the check after `steps` steps, whose entries are on their way to buffer s
+  auto look = [&](int s, int steps, bool last, bool& done) -> alm_bm_status {
+    HIPCHK(hipEventSynchronize(p->lz_ev[s]));
+    std::copy(host_a(s), host_a(s) + steps, ha.begin());
+    std::copy(host_b(s), host_b(s) + steps, hb.begin());
+    double anorm = 0.0;
+    for (int i = 0; i < steps; ++i) anorm = std::max(anorm, std::fabs(ha[i]) + std::fabs(hb[i]));
+    for (int i = 0; i < steps; ++i)
+      if (!std::isfinite(ha[i]) || !std::isfinite(hb[i])) return fail(ALM_BM_ERR_NUMERIC, "lanczos: NaN/Inf");
+    // an (almost) invariant subspace ends the recurrence
+    int mm = steps;
+    bool breakdown = false;
+    for (int i = 0; i < steps; ++i)
+      if (hb[i] <= 1e-13 * std::max(anorm, 1e-300)) {
+        mm = i + 1;
+        breakdown = true;
+        break;
+      }
+    theta = tri_min_eig(ha, hb, mm);
+    tri_eigvec(ha, hb, mm, theta, z);
+    m = mm;
+    const double est = breakdown ? 0.0 : std::fabs(hb[mm - 1] * z[mm - 1]);
+    done = breakdown || est <= tol || last;
+    return ALM_BM_OK;
+  };
   for (int j = 0; j < kmax; ++j) {
     const bool last = (j + 1 == kmax);
     const bool check = ((j + 1) % check_every) == 0 || last;
@@ -1301,27 +1355,21 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
       if (!sums) launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, qsum, st);
     }
     if (check) {
-      HIPCHK(hipMemcpyAsync(ha.data(), p->lalpha, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-      HIPCHK(hipMemcpyAsync(hb.data(), p->lbeta, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-      HIPCHK(hipStreamSynchronize(st));
-      double anorm = 0.0;
-      for (int i = 0; i <= j; ++i) anorm = std::max(anorm, std::fabs(ha[i]) + std::fabs(hb[i]));
-      for (int i = 0; i <= j; ++i)
-        if (!std::isfinite(ha[i]) || !std::isfinite(hb[i])) return fail(ALM_BM_ERR_NUMERIC, "lanczos: NaN/Inf");
-      // an (almost) invariant subspace ends the recurrence
-      int mm = j + 1;
-      bool breakdown = false;
-      for (int i = 0; i <= j; ++i)
-        if (hb[i] <= 1e-13 * std::max(anorm, 1e-300)) {
-          mm = i + 1;
-          breakdown = true;
-          break;
-        }
-      theta = tri_min_eig(ha, hb, mm);
-      tri_eigvec(ha, hb, mm, theta, z);
-      m = mm;
-      const double est = breakdown ? 0.0 : std::fabs(hb[mm - 1] * z[mm - 1]);
-      if (breakdown || est <= tol || last) break;
+      HIPCHK(hipMemcpyAsync(host_a(slot), p->lalpha, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(host_b(slot), p->lbeta, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipEventRecord(p->lz_ev[slot], st));
+      bool done = false;
+      if (pending > 0) {
+        STCHK(look(1 - slot, pending, false, done));
+        if (done) break;
+      }
+      pending = j + 1;
+      slot = 1 - slot;
+      if (last || !ahead) {
+        STCHK(look(1 - slot, pending, last, done));
+        pending = 0;
+        if (done) break;
+      }
     }
   }
   HIPCHK(hipMemcpyAsync(p->ls, z.data(), m * sizeof(double), hipMemcpyHostToDevice, st));
@@ -1597,20 +1645,18 @@ extern "C" alm_bm_status alm_bm_kkt(alm_bm_problem* p, int32_t r, const void* R,
 
 namespace {
 
+// The captured step of a batched solve, made after kBatchPlainChunks runs of
+// plain launches with the same running set and widths (the two take the same
+// time; the plain ones cost no capture).
+constexpr int kBatchPlainChunks = 4;
 struct GraphCache {
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
-  int r = -1;
-  int refresh = -1;
-  int lb_m = -1;
-  const void* R = nullptr;
   void reset() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (graph) (void)hipGraphDestroy(graph);
     exec = nullptr;
     graph = nullptr;
-    r = -1;
-    R = nullptr;
   }
   ~GraphCache() { reset(); }
 };
@@ -1630,40 +1676,30 @@ int bp_rank_cap(long m) {
 
 template <typename T>
 static alm_bm_status inner_solve(alm_bm_problem* p, int r, T* R, const double* y, double sigma, double tol,
-                                 const alm_bm_options& o, GraphCache& gc, hipStream_t st, int& iters, int& flag) {
+                                 const alm_bm_options& o, hipStream_t st, int& iters, int& flag) {
   T* G = static_cast<T*>(p->G);
   const int refresh = o.refresh_every > 0 ? o.refresh_every : default_refresh(sizeof(T) == 8 ? ALM_BM_F64
                                                                   : (sizeof(T) == 4 ? ALM_BM_F32 : ALM_BM_BF16));
   launch_inner_reset(p->sc_solve, tol, o.max_inner, (int)o.step_rule, o.eta_fixed, st);
   if (p->lb_m > 0) launch_lbfgs_reset(p->lbs, p->lb_m, st);  // each subproblem starts with an empty memory
-  const int U = std::max(0, o.graph_unroll);
+  // Steps are enqueued graph_unroll at a time between two looks at the stop flag,
+  // none past the last one possible (step max_inner + 1 stops).  They are plain
+  // launches: the host knows the step's number and leaves out the pass that
+  // would do nothing in it, and a captured graph of the same steps was slower at
+  // every size (n = 2000, r = 8: 26 against 23 us per step; n = 1e6, r = 16,
+  // FP32: 182 against 178), before counting its capture (about 0.3 ms a call).
+  const int U = std::max(1, o.graph_unroll);
   int32_t hflag = 0;
-  const int max_launch = o.max_inner + 2;
   int launched = 0;
   while (true) {
-    if (U > 0) {
-      if (gc.r != r || gc.R != (const void*)R || gc.refresh != refresh || gc.lb_m != p->lb_m) {
-        gc.reset();
-        HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        for (int u = 0; u < U; ++u) enqueue_inner_step<T>(p, r, R, y, sigma, G, refresh, st);
-        HIPCHK(hipStreamEndCapture(st, &gc.graph));
-        HIPCHK(hipGraphInstantiate(&gc.exec, gc.graph, nullptr, nullptr, 0));
-        gc.r = r;
-        gc.R = R;
-        gc.refresh = refresh;
-        gc.lb_m = p->lb_m;
-      }
-      HIPCHK(hipGraphLaunch(gc.exec, st));
-      launched += U;
-    } else {
-      enqueue_inner_step<T>(p, r, R, y, sigma, G, refresh, st);
-      launched += 1;
-    }
+    const int steps = std::min(U, o.max_inner + 1 - launched);
+    if (steps <= 0) return fail(ALM_BM_ERR_HIP, "inner loop did not reach its stop flag");
+    for (int u = 0; u < steps; ++u) enqueue_inner_step<T>(p, r, R, y, sigma, G, refresh, st, launched + u);
+    launched += steps;
     HIPCHK(hipMemcpyAsync(&p->sc_host->flag, &p->sc_solve->flag, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     hflag = p->sc_host->flag;
     if (hflag != 0) break;
-    if (launched > max_launch + U) return fail(ALM_BM_ERR_HIP, "inner loop did not reach its stop flag");
   }
   HIPCHK(hipGetLastError());
   iters = p->sc_host->iter;
@@ -1746,8 +1782,8 @@ extern "C" alm_bm_status alm_bm_block_moments(alm_bm_problem* p, int32_t q, cons
 // the qv x qv PSD subproblem, and the columns of V S^{1/2} are appended to R.
 template <typename T>
 static alm_bm_status block_rank_step(alm_bm_problem* p, T* R, int& r, int& w, int r_cap, int rank_block,
-                                     double sigma, int kmax, double tau_rank, uint64_t seed, GraphCache& gc,
-                                     int& added, hipStream_t st) {
+                                     double sigma, int kmax, double tau_rank, uint64_t seed, int& added,
+                                     hipStream_t st) {
   const auto& d = p->d;
   const long n = d.n;
   added = 0;
@@ -1792,7 +1828,6 @@ static alm_bm_status block_rank_step(alm_bm_problem* p, T* R, int& r, int& w, in
       launch_relayout<T>(n, w, r, w2, R, Rt, p->lw, 1.0, st);
       HIPCHK(hipMemcpyAsync(R, Rt, (size_t)n * w2 * sizeof(T), hipMemcpyDeviceToDevice, st));
       w = w2;
-      gc.reset();
     }
     r += 1;
   }
@@ -1812,7 +1847,6 @@ static alm_bm_status solve_impl(alm_bm_problem* p, const alm_bm_options& o, T* R
   if (o.r_cap > 0) r_cap = std::min(r_cap, o.r_cap);
   const int kmax = o.lanczos_kmax > 0 ? std::min(o.lanczos_kmax, p->kmax) : p->kmax;
   const double ltol = o.lanczos_tol_rel * o.eps_kkt * (1.0 + p->cnorm);
-  GraphCache gc;
   stalled = false;
   std::vector<double> pinf_hist;
   for (int k = k_start; k < o.max_outer; ++k) {
@@ -1821,7 +1855,7 @@ static alm_bm_status solve_impl(alm_bm_problem* p, const alm_bm_options& o, T* R
     tol_prev = tol;
     acc.inner_tol = tol;
     int iters = 0, flag = 0;
-    STCHK(inner_solve<T>(p, w, R, y, sigma, tol, o, gc, st, iters, flag));
+    STCHK(inner_solve<T>(p, w, R, y, sigma, tol, o, st, iters, flag));
     acc.inner_total += iters;
     // w = y - sigma (A(RR^T) - b) into ybuf (Av is current: the last pass ran at the final R)
     launch_dual(d.m, p->Av, d.b, y, p->ybuf, sigma, p->part_vec, p->sc_solve, p->bnorm, nullptr, st,
@@ -1848,7 +1882,7 @@ static alm_bm_status solve_impl(alm_bm_problem* p, const alm_bm_options& o, T* R
     if (o.rank_policy == ALM_BM_RANK_ADAPT && gate && lo.theta < -tau_k && r < r_cap && o.rank_block > 1) {
       int added = 0;
       STCHK(block_rank_step<T>(p, R, r, w, r_cap, o.rank_block, sigma, kmax, tau_k,
-                               o.seed * 1000003ull + (uint64_t)k + 3333333ull, gc, added, st));
+                               o.seed * 1000003ull + (uint64_t)k + 3333333ull, added, st));
       if (added > 0) {
         expanded = true;
         acc.expansions += 1;
@@ -1875,7 +1909,6 @@ static alm_bm_status solve_impl(alm_bm_problem* p, const alm_bm_options& o, T* R
           launch_relayout<T>(n, w, r, w2, R, Rt, p->lv, std::sqrt(s), st);
           HIPCHK(hipMemcpyAsync(R, Rt, (size_t)n * w2 * sizeof(T), hipMemcpyDeviceToDevice, st));
           w = w2;
-          gc.reset();
         }
         r += 1;
         expanded = true;
@@ -1927,7 +1960,6 @@ static alm_bm_status solve_impl(alm_bm_problem* p, const alm_bm_options& o, T* R
       sigma = std::min(o.sigma_max, sigma * o.sigma_growth);
       acc.sigma_final = sigma;
       acc.sigma_increases += 1;
-      gc.reset();  // the captured inner loop holds sigma as a kernel argument
     }
     if (o.time_limit_s > 0.0 && now_s() - t0 > o.time_limit_s) return ALM_BM_NOT_CONVERGED;
     if (stop_on_stall) {
@@ -1966,9 +1998,8 @@ extern "C" alm_bm_status alm_bm_inner_solve(alm_bm_problem* p, const alm_bm_opti
   STCHK(check_inner(p, o, lb_m));
   InnerScope inner_scope(p, lb_m);
   int iters = 0, flag = 0;
-  GraphCache gc;
   alm_bm_status s = with_storage(p->d.precision, [&]<typename T>() {
-    return inner_solve<T>(p, r, static_cast<T*>(R), y, o.sigma, tol, o, gc, st, iters, flag);
+    return inner_solve<T>(p, r, static_cast<T*>(R), y, o.sigma, tol, o, st, iters, flag);
   });
   if (s < 0) return s;
   HIPCHK(hipMemcpyAsync(p->sc_host, p->sc_solve, sizeof(DevScalars), hipMemcpyDeviceToHost, st));
@@ -2371,6 +2402,24 @@ extern "C" alm_bm_status alm_bm_batch_create(int32_t count, const alm_bm_problem
 
 namespace {
 
+// f(0), ..., f(count - 1), each once, over up to eight threads (one per four
+// calls).  f must not throw and its calls must not share what they write.
+template <typename F> void host_parallel(int count, F&& f) {
+  const int nt = std::min({8, (int)std::thread::hardware_concurrency(), count / 4});
+  std::atomic<int> next{0};
+  auto work = [&]() {
+    for (int t = next++; t < count; t = next++) f(t);
+  };
+  std::vector<std::thread> pool;
+  try {
+    for (int t = 1; t < nt; ++t) pool.emplace_back(work);
+  } catch (...) {
+    // fewer threads then: the caller's own takes what is left
+  }
+  work();
+  for (std::thread& t : pool) t.join();
+}
+
 struct BatchLanczos {
   std::vector<double> theta, resid;
   std::vector<int> m;
@@ -2498,13 +2547,21 @@ static alm_bm_status batch_lanczos_pass(alm_bm_batch* b, const double* y, int km
       HIPCHK(hipMemcpyAsync(ha.data(), p->lalpha, ha.size() * sizeof(double), hipMemcpyDeviceToHost, st));
       HIPCHK(hipMemcpyAsync(hb.data(), p->lbeta, hb.size() * sizeof(double), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
-      bool dropped = false;
-      for (int q = 0; q < count; ++q) {
-        if (done[q]) continue;
-        std::vector<double> a(ha.begin() + (long)q * kp, ha.begin() + (long)q * kp + j + 1);
-        std::vector<double> bt(hb.begin() + (long)q * kp, hb.begin() + (long)q * kp + j + 1);
+      // the instances' tridiagonal eigenproblems, over the host's threads (24
+      // instances took 0.4 ms of every 1 ms between two checks on one)
+      std::vector<int> todo;
+      for (int q = 0; q < count; ++q)
+        if (!done[q]) todo.push_back(q);
+      std::vector<char> ends(count, 0), bad(count, 0);
+      host_parallel((int)todo.size(), [&](int t) {
+        const int q = todo[t];
+        const std::vector<double> a(ha.begin() + (long)q * kp, ha.begin() + (long)q * kp + j + 1);
+        const std::vector<double> bt(hb.begin() + (long)q * kp, hb.begin() + (long)q * kp + j + 1);
         for (int i = 0; i <= j; ++i)
-          if (!std::isfinite(a[i]) || !std::isfinite(bt[i])) return fail(ALM_BM_ERR_NUMERIC, "batch lanczos: NaN/Inf");
+          if (!std::isfinite(a[i]) || !std::isfinite(bt[i])) {
+            bad[q] = 1;
+            return;
+          }
         double anorm = 0.0;
         for (int i = 0; i <= j; ++i) anorm = std::max(anorm, std::fabs(a[i]) + std::fabs(bt[i]));
         int mm = j + 1;
@@ -2520,7 +2577,12 @@ static alm_bm_status batch_lanczos_pass(alm_bm_batch* b, const double* y, int km
         out.theta[q] = th;
         out.m[q] = mm;
         const double est = breakdown ? 0.0 : std::fabs(bt[mm - 1] * z[q][mm - 1]);
-        if (breakdown || est <= tol[q] || mm >= b->kmax[q] || mm >= (int)(b->off[q + 1] - b->off[q])) {
+        ends[q] = breakdown || est <= tol[q] || mm >= b->kmax[q] || mm >= (int)(b->off[q + 1] - b->off[q]);
+      });
+      bool dropped = false;
+      for (int q : todo) {
+        if (bad[q]) return fail(ALM_BM_ERR_NUMERIC, "batch lanczos: NaN/Inf");
+        if (ends[q]) {
           done[q] = 1;
           ++ndone;
           dropped = true;
@@ -2658,9 +2720,12 @@ static BlockTab batch_class_tab(const alm_bm_batch* b, int c) {
 }
 
 // One inner step of every running instance: each row kernel once per width.
+// step: its number from the start of the subproblem, which leaves out the pass
+// that would do nothing in it; -1: any step (the captured graph), every pass
+// deciding on the device.
 template <typename T>
 static void batch_enqueue_step(alm_bm_batch* b, T* R, const double* y, double sigma, T* G, int refresh,
-                               hipStream_t st) {
+                               hipStream_t st, int step = -1) {
   using V = typename Acc<T>::type;
   alm_bm_problem* p = b->p;
   const auto& d = p->d;
@@ -2668,10 +2733,11 @@ static void batch_enqueue_step(alm_bm_batch* b, T* R, const double* y, double si
   V* Q = static_cast<V*>(p->Qbuf);
   using S = RingT<T>;
   const LbfgsRing<S> lb = lbfgs_ring<S>(p);  // empty: gradient descent
-  for (int c = 0; c < b->nclass; ++c)
+  for (int c = 0; c < b->nclass && step != 0; ++c)
     launch_upd_eval_diag<T>(d.n, b->c_w[c], b->c_var[c], R, G, Q, y, d.b, sigma, p->Av, p->part, sc, refresh,
                             batch_class_tab(b, c), b->c_nb[c], st, lb);
-  for (int c = 0; c < b->nclass; ++c)
+  const bool full = step < 0 || refresh <= 1 || step % refresh == 0;
+  for (int c = 0; c < b->nclass && full; ++c)
     launch_objgrad_diag<T>(cost_of<T>(p), b->c_w[c], b->c_var[c], R, y, d.b, sigma, G, p->Av, p->part, sc, refresh,
                            batch_class_tab(b, c), b->c_nb[c], st, lb);
   launch_fin_objgrad(p->part, p->nblk, sc, sigma, 1, nullptr, st, p->tab, p->count);
@@ -2749,7 +2815,7 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
   // running set: both are rebuilt when either changed since they were made.
   std::vector<int> tab_w, gr_w;
   std::vector<int32_t> tab_active, gr_active;
-  int captures = 0;
+  int captures = 0, chunks = 0;
   std::vector<int32_t> fl(2 * count);
   int nactive = count;
   for (int k = 0; k < o.max_outer && nactive > 0; ++k) {
@@ -2765,15 +2831,11 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
       tab_w = w;
       tab_active = active;
     }
-    if (!gc.exec || w != gr_w || active != gr_active) {
+    if (w != gr_w || active != gr_active) {
       gc.reset();
-      HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-      for (int u = 0; u < U; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st);
-      HIPCHK(hipStreamEndCapture(st, &gc.graph));
-      HIPCHK(hipGraphInstantiate(&gc.exec, gc.graph, nullptr, nullptr, 0));
       gr_w = w;
       gr_active = active;
-      ++captures;
+      chunks = 0;
     }
     HIPCHK(hipMemcpyAsync(b->tols_dev, tolv.data(), count * sizeof(double), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->active_dev, active.data(), count * sizeof(int32_t), hipMemcpyHostToDevice, st));
@@ -2782,8 +2844,24 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
     if (p->lb_m > 0) launch_lbfgs_reset(p->lbs, p->lb_m, st, count);  // empty memories
     int launched = 0;
     while (true) {
-      HIPCHK(hipGraphLaunch(gc.exec, st));
-      launched += U;
+      // A running set and its widths first take plain launches (which know the
+      // step's number); a set that lasts is worth the capture of its step.
+      const int steps = std::min(U, o.max_inner + 1 - launched);
+      if (steps <= 0) return fail(ALM_BM_ERR_HIP, "batch inner loop did not reach its stop flags");
+      if (steps < U || chunks < kBatchPlainChunks) {
+        for (int u = 0; u < steps; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st, launched + u);
+      } else {
+        if (!gc.exec) {
+          HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+          for (int u = 0; u < U; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st);
+          HIPCHK(hipStreamEndCapture(st, &gc.graph));
+          HIPCHK(hipGraphInstantiate(&gc.exec, gc.graph, nullptr, nullptr, 0));
+          ++captures;
+        }
+        HIPCHK(hipGraphLaunch(gc.exec, st));
+      }
+      launched += steps;
+      ++chunks;
       launch_gather_flags(p->sc_solve, count, b->flags_dev, st);
       HIPCHK(hipMemcpyAsync(fl.data(), b->flags_dev, 2 * count * sizeof(int32_t), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
@@ -2791,7 +2869,6 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
       for (int q = 0; q < count; ++q)
         if (fl[2 * q] == 0) all = false;
       if (all) break;
-      if (launched > o.max_inner + 2 * U + 2) return fail(ALM_BM_ERR_HIP, "batch inner loop did not reach its stop flags");
     }
     for (int q = 0; q < count; ++q)
       if (active[q]) res[q].inner_total += fl[2 * q + 1];
