@@ -375,12 +375,18 @@ extern "C" void alm_bm_abi_sizes(int64_t* out) {
 
 // --------------------------------------------------------------------- create / destroy
 
-// 64 rows a block, at most four blocks per CU.  More blocks only add partial
-// rows for the one-block finalizers: over n = 2e4..1e7, degrees 8..20, all
-// storage types, gradient-descent steps with 1024 blocks took 0.93..1.00 of the
-// time with 4096 (the two-round imbalance of 1536 and 3072 cost 2..14 %).
+// At most four blocks per CU: more only add partial rows for the one-block
+// finalizers (over n = 2e4..1e7, degrees 8..20, all storage types, gradient-descent
+// steps with 1024 blocks took 0.93..1.00 of the time with 4096; the two-round
+// imbalance of 1536 and 3072 cost 2..14 %).  64 rows a block up to there, but 16
+// while that gives fewer than two blocks per CU: a small pass lasts as long as one
+// block's trips over its rows, each a chain of dependent loads.  63 steps with 64
+// and with 16 rows a block: n = 2000, r = 8, FP64 1.54 -> 1.30 ms; n = 4000, r = 64,
+// FP64 2.76 -> 1.65; n = 16000, r = 32, FP32 (512 blocks) 2.02 -> 1.80.
 int almbm::row_blocks(long n) {
-  long nb = (n + 63) / 64;
+  long nb = (n + 15) / 16;
+  if (nb > 512) nb = 512;
+  if (nb < (n + 63) / 64) nb = (n + 63) / 64;
   if (nb < 8) nb = 8;
   if (nb > 1024) nb = 1024;
   return (int)((nb + 7) / 8 * 8);

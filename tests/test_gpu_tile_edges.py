@@ -42,6 +42,23 @@ def test_objective_over_partial_row_counts(blocks):
     np.testing.assert_allclose(k.cpu().numpy(), k_o, rtol=1e-10, atol=1e-10 * float(np.max(np.abs(k_o))))
 
 
+@pytest.mark.parametrize("n", [2, 7, 127, 129, 1000, 8191, 8193, 32767, 32769, 70001])
+@pytest.mark.parametrize("r", [3, 16])
+def test_objective_over_default_grids(n, r):
+    """Sizes around the lines of the default grid (16 rows a block up to 512 blocks, 64 rows a block above).  FP64
+    sums of n r products: 1e-12 relative covers any order."""
+    g = gen.er_graph(n, min(3 * n, n * (n - 1) // 2), n, "gauss")
+    po = oracle.maxcut_sdp(g)
+    p = _almbm().Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=16, lanczos_kmax=0, device=DEV)
+    rng = np.random.default_rng(n + r)
+    R, y = rng.standard_normal((n, r)), rng.standard_normal(n)
+    f_o, G_o, a_o, _ = oracle.objective_grad(po, R, y, 1.3)
+    for _ in range(2):
+        f, G, Av = p.objective_grad(p.factor(R), torch.from_numpy(y).to(DEV), 1.3)
+        assert abs(f.item() - f_o) <= 1e-12 * abs(f_o) + 1e-10
+        assert rel(G.cpu(), G_o) <= 1e-12 and rel(Av.cpu(), a_o) <= 1e-12
+
+
 @pytest.mark.parametrize("r", [1, 3, 4, 5, 8, 11, 16, 17, 32, 40, 64, 100, 128])
 @pytest.mark.parametrize("shape", ["long", "short", "one_edge"])
 def test_edge_family_tiles_against_oracle(shape, r):
