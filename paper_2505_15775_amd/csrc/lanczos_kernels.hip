@@ -325,6 +325,8 @@ struct LzScale {
 // by the gathers: n = 1e6, 8e6 entries (8 MB vector, two L2 slices' worth): 109
 // us one entry at a time, 101 us with four (79e9 gathers/s); non-temporal index
 // and value loads made it 125 us (they no longer come from the Infinity Cache).
+// A batch of 24 instances, n = 275 113 together, 5.0e6 entries (vectors of 320 KB at
+// most, from the L2): 43 us with 256 rows a block, 34 us with 64.
 __global__ void __launch_bounds__(kBlock)
 k_lz_mv(Cost<double> C, int cons_kind, EdgeAdj A, const double* __restrict__ y, double c_tr, double j_coef,
         const double* __restrict__ qsum_in, LzScale sc, const double* __restrict__ w, double* __restrict__ qcol,
@@ -341,7 +343,7 @@ k_lz_mv(Cost<double> C, int cons_kind, EdgeAdj A, const double* __restrict__ y, 
     const double beta = sqrt(b2);
     inv = beta > 0.0 ? 1.0 / beta : 0.0;
     if (j_coef != 0.0) qsum = beta > 0.0 ? sum_strided4(sc.part + sc.pld, sc.nb) / beta : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
       *sc.alpha_out = sc.h1[sc.jm1] + sc.h2[sc.jm1];
       *sc.beta_out = beta;
     }
@@ -349,7 +351,7 @@ k_lz_mv(Cost<double> C, int cons_kind, EdgeAdj A, const double* __restrict__ y, 
     const double beta = sc.beta[(long)ch.inst * sc.bstride];
     inv = beta > 0.0 ? 1.0 / beta : 0.0;
   }
-  for (long base = ch.lo; base < ch.hi; base += RPB) {
+  for (long base = ch.lo + (long)blockIdx.y * RPB; base < ch.hi; base += (long)gridDim.y * RPB) {
     const long i = base + threadIdx.x / L;
     const bool in = i < ch.hi;
     double acc = 0.0;
@@ -742,12 +744,19 @@ void launch_lz_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const 
     sc.beta = s.beta + s.j - 1;
     sc.bstride = vb.astride;
   }
+  // one trip of the rows per block; with a table, whose blocks have many more rows,
+  // by sharing each of its entries among grid.y blocks (no partial sums depend on it)
+  constexpr long kRows = kBlock / kSpmvLpr;
+  int ny = 1;
   if (!vb.tab.inst) {
-    long g = (C.n + kBlock / kSpmvLpr - 1) / (kBlock / kSpmvLpr);
+    long g = (C.n + kRows - 1) / kRows;
     g = g < 8 ? 8 : (g > 8192 ? 8192 : g);
     nb = (int)((g + 7) / 8 * 8);
+  } else {
+    const long g = (C.n + nb * kRows - 1) / (nb * kRows);
+    ny = (int)(g < 1 ? 1 : (g > 8 ? 8 : g));
   }
-  hipLaunchKernelGGL(k_lz_mv, dim3(nb), dim3(kBlock), 0, st, C, cons_kind, A, y, c_tr, j_coef, qsum, sc, w, qcol, out,
+  hipLaunchKernelGGL(k_lz_mv, dim3(nb, ny), dim3(kBlock), 0, st, C, cons_kind, A, y, c_tr, j_coef, qsum, sc, w, qcol, out,
                      vb.tab);
 }
 void launch_slack_mv(const Cost<double>& C, int cons_kind, const EdgeAdj& A, const double* y, double c_tr,
