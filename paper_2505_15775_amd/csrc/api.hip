@@ -93,7 +93,7 @@ struct alm_bm_problem {
   double* lv = nullptr;
   double* ls = nullptr;
   double* lscal = nullptr;
-  double* lz_host = nullptr;      // pinned: two buffers of kmax + 1 alpha, kmax + 1 beta
+  double* lz_host = nullptr;      // behind sc_host: two buffers of kmax + 1 alpha, kmax + 1 beta
   hipEvent_t lz_ev[2] = {};
   std::vector<void*> allocs;
   double* bk_h = nullptr;         // block Krylov: (kmax+1)^2 projected matrix, column sums, Ritz coefficients
@@ -145,7 +145,6 @@ static void free_all(alm_bm_problem* p) {
   p->ss = nullptr;
   if (p->sc_host) (void)hipHostFree(p->sc_host);
   p->sc_host = nullptr;
-  if (p->lz_host) (void)hipHostFree(p->lz_host);
   p->lz_host = nullptr;
   for (hipEvent_t& e : p->lz_ev) {
     if (e) (void)hipEventDestroy(e);
@@ -588,30 +587,37 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   p->lnb = vec_blocks(n, p->C64.nh > 0);
   CK(dalloc_t(p, &p->part_vec, (size_t)std::max(p->lnb, dual_blocks(d.m)) * 2 + 16));
   {
-    hipError_t e = hipHostMalloc((void**)&p->sc_host, sizeof(DevScalars), hipHostMallocDefault);
+    const size_t lz = d.lanczos_kmax > 0 ? (size_t)(d.lanczos_kmax + 1) * 4 * sizeof(double) : 0;
+    hipError_t e = hipHostMalloc((void**)&p->sc_host, sizeof(DevScalars) + lz, hipHostMallocDefault);
     if (e != hipSuccess) return bail(fail(ALM_BM_ERR_OOM, "hipHostMalloc failed"));
     std::memset(p->sc_host, 0, sizeof(DevScalars));
+    p->lz_host = reinterpret_cast<double*>(p->sc_host + 1);
   }
   HK(hipMemcpy(p->sc_api, p->sc_host, sizeof(DevScalars), hipMemcpyHostToDevice));
   HK(hipMemcpy(p->sc_solve, p->sc_host, sizeof(DevScalars), hipMemcpyHostToDevice));
   p->kmax = d.lanczos_kmax;
   if (p->kmax > 0) {
     CK(dalloc_t(p, &p->Q, (size_t)n * (p->kmax + 1)));
-    CK(dalloc_t(p, &p->lw, n));
-    CK(dalloc_t(p, &p->lw2, n));
-    CK(dalloc_t(p, &p->lv, n));
-    CK(dalloc_t(p, &p->lh1, p->kmax + 1));
-    CK(dalloc_t(p, &p->lh2, p->kmax + 1));
-    CK(dalloc_t(p, &p->lalpha, p->kmax + 1));
-    CK(dalloc_t(p, &p->lbeta, p->kmax + 1));
-    CK(dalloc_t(p, &p->ls, p->kmax + 1));
-    CK(dalloc_t(p, &p->lscal, 8));
-    if (hipHostMalloc((void**)&p->lz_host, (size_t)(p->kmax + 1) * 4 * sizeof(double), hipHostMallocDefault) != hipSuccess)
-      return bail(fail(ALM_BM_ERR_OOM, "hipHostMalloc failed"));
+    // few allocations rather than one per array: each costs its time at creation and at destruction
+    auto padded = [](size_t k) { return (k + 31) / 32 * 32; };
+    const size_t nv = padded(n), kv = padded(p->kmax + 1), pv = padded((size_t)p->lnb * (p->kmax + 1));
+    double* q = nullptr;
+    CK(dalloc_t(p, &q, 3 * nv));
+    for (double** v : {&p->lw, &p->lw2, &p->lv}) {
+      *v = q;
+      q += nv;
+    }
+    CK(dalloc_t(p, &q, 5 * kv + 8));
+    for (double** v : {&p->lh1, &p->lh2, &p->lalpha, &p->lbeta, &p->ls, &p->lscal}) {
+      *v = q;
+      q += kv;
+    }
+    CK(dalloc_t(p, &q, 2 * pv + (size_t)p->lnb * 2));
+    for (double** v : {&p->lpart, &p->lpartb, &p->lpart2}) {
+      *v = q;
+      q += pv;
+    }
     for (hipEvent_t& e : p->lz_ev) HK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    CK(dalloc_t(p, &p->lpart, (size_t)p->lnb * (p->kmax + 1)));
-    CK(dalloc_t(p, &p->lpartb, (size_t)p->lnb * (p->kmax + 1)));
-    CK(dalloc_t(p, &p->lpart2, (size_t)p->lnb * 2));
     CK(dalloc_t(p, &p->bk_h, (size_t)(p->kmax + 1) * (p->kmax + 1)));
     CK(dalloc_t(p, &p->bk_colsum, (size_t)(p->kmax + 1)));
     CK(dalloc_t(p, &p->bk_coef, (size_t)(p->kmax + 1) * kMaxBlockQ));
