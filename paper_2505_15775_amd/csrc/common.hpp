@@ -210,17 +210,18 @@ __device__ __forceinline__ void block_sum_many(const double (&acc)[NS], double* 
 // A the largest multiple of ns up to kFin, so that loads are coalesced and a
 // thread stays on one column; kFinUnroll of them are in flight per thread.  A
 // wave then adds each column's A / ns threads.  Fixed order, independent of
-// timing.  Bound by the latency of one CU's loads: 4096 x 15 doubles took 18 us
+// timing, and the same for any THREADS, the threads of the block that runs it (fewer
+// take several of the kFin threads' shares).  Bound by the latency of one CU's loads: 4096 x 15 doubles took 18 us
 // with 256 threads walking rows (15 strided loads a row, 15 block reductions by
 // shuffles) and take 11 us this way.  Every thread of the block must call it.
 constexpr int kFin = 1024;
 constexpr int kFinUnroll = 16;
+template <int THREADS = kFin>
 __device__ __forceinline__ void fin_table(const double* __restrict__ part, int rows, int ns, double* __restrict__ out) {
   const int A = kFin / ns * ns;
   __shared__ double buf[kFin];
-  const int t = threadIdx.x;
   const long len = (long)rows * ns;
-  if (t < A) {
+  for (int t = threadIdx.x; t < A; t += THREADS) {
     double a = 0.0;
     for (long k = t; k < len; k += (long)kFinUnroll * A) {
       double v[kFinUnroll];
@@ -235,8 +236,8 @@ __device__ __forceinline__ void fin_table(const double* __restrict__ part, int r
     buf[t] = a;
   }
   __syncthreads();
-  const int lane = t % kWave, wave = t / kWave;
-  for (int s = wave; s < ns; s += kFin / kWave) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  for (int s = wave; s < ns; s += THREADS / kWave) {
     double a = 0.0;
     for (int g = lane; g < A / ns; g += kWave) a += buf[g * ns + s];
     a = wave_sum(a);
@@ -244,9 +245,9 @@ __device__ __forceinline__ void fin_table(const double* __restrict__ part, int r
   }
   __syncthreads();
 }
-template <int NS>
+template <int NS, int THREADS = kFin>
 __device__ __forceinline__ void fin_rows(const double* __restrict__ part, int rows, double* __restrict__ out) {
-  fin_table(part, rows, NS, out);
+  fin_table<THREADS>(part, rows, NS, out);
 }
 
 // Rows owned by this block: the row range is split into gridDim.x contiguous
@@ -258,8 +259,8 @@ __device__ __forceinline__ void fin_rows(const double* __restrict__ part, int ro
 struct RowChunk {
   long lo, hi;
 };
-__device__ __forceinline__ RowChunk row_chunk(long n, bool spread = false) {
-  const long nb = gridDim.x;
+__device__ __forceinline__ RowChunk row_chunk(long n, bool spread = false, int blocks = 0) {
+  const long nb = blocks ? blocks : gridDim.x;  // the first `blocks` of the grid
   long vb = blockIdx.x;
   if (nb % kNumXcd == 0 && !spread) {
     const long per = nb / kNumXcd;

@@ -10,6 +10,7 @@
 // work is a sparse gather at ~2r flop per 12 B of matrix plus r*sizeof(T) of
 // gathered row, far below the vector ALU balance, so the kernels are bound by
 // HBM/Infinity-Cache bandwidth.
+#include "finalize.hpp"
 #include "spmm_row.hpp"
 
 namespace almbm {
@@ -133,10 +134,11 @@ k_quad_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ G,
 template <typename T, int LPR, int VEC, bool FULL>
 __global__ void __launch_bounds__(kBlock)
 k_quadq_diag(Cost<typename Acc<T>::type> C, int r, const T* __restrict__ G, typename Acc<T>::type* __restrict__ Q,
-             double* __restrict__ part, const DevScalars* __restrict__ sc_base, BlockTab tab, LbfgsRing<T> lb) {
+             double* __restrict__ part, const DevScalars* sc_base, BlockTab tab, LbfgsRing<T> lb, SideFin side) {
   using V = typename Acc<T>::type;
-  const Rows ch = rows_of(C.n, tab, C.skewed);
-  if (sc_base && sc_base[ch.inst].flag) return;
+  if (run_side_fin(side)) return;
+  const Rows ch = rows_of(C.n, tab, C.skewed, gridDim.x - (side.part ? 1 : 0));
+  if (sc_base && block_stopped(sc_base + ch.inst)) return;
   if (lb.s) G = lb.e + (long)lb.s[ch.inst].cur * lb.stride;  // L-BFGS: the product of the direction E
   constexpr int RPB = kBlock / LPR;
   const int lane = threadIdx.x % LPR;
@@ -437,13 +439,14 @@ static void launch_objgrad_cfg(const Cost<typename Acc<T>::type>& C, int r, cons
 template <typename T, int LPR, int VEC>
 static void launch_quadq_cfg(const Cost<typename Acc<T>::type>& C, int r, const T* G, typename Acc<T>::type* Q,
                              double* part, const DevScalars* sc, const BlockTab& tab, int nblk, hipStream_t st,
-                             const LbfgsRing<T>& lb) {
+                             const LbfgsRing<T>& lb, const SideFin& side) {
+  const dim3 grid(nblk + (side.part ? 1 : 0));
   if (r == LPR * VEC)
-    hipLaunchKernelGGL((k_quadq_diag<T, LPR, VEC, true>), dim3(nblk), dim3(kBlock), 0, st, C, r, G, Q, part, sc, tab,
-                       lb);
+    hipLaunchKernelGGL((k_quadq_diag<T, LPR, VEC, true>), grid, dim3(kBlock), 0, st, C, r, G, Q, part, sc, tab, lb,
+                       side);
   else
-    hipLaunchKernelGGL((k_quadq_diag<T, LPR, VEC, false>), dim3(nblk), dim3(kBlock), 0, st, C, r, G, Q, part, sc,
-                       tab, lb);
+    hipLaunchKernelGGL((k_quadq_diag<T, LPR, VEC, false>), grid, dim3(kBlock), 0, st, C, r, G, Q, part, sc, tab, lb,
+                       side);
 }
 
 template <typename T, int LPR, int VEC>
@@ -499,9 +502,9 @@ void launch_objgrad_diag(const Cost<typename Acc<T>::type>& C, int r, int varian
 template <typename T>
 void launch_quadq_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, const T* G,
                        typename Acc<T>::type* Q, double* part, const DevScalars* sc, const BlockTab& tab, int nblk,
-                       hipStream_t st, const LbfgsRing<T>& lb) {
+                       hipStream_t st, const LbfgsRing<T>& lb, const SideFin& side) {
   launch_hub_rows<T>(C, r, variant, G, C.hsum, sc, 0, st, lb);
-  ALMBM_DISPATCH_DIAG(T, launch_quadq_cfg, C, r, G, Q, part, sc, tab, nblk, st, lb);
+  ALMBM_DISPATCH_DIAG(T, launch_quadq_cfg, C, r, G, Q, part, sc, tab, nblk, st, lb, side);
 }
 
 template <typename T>
@@ -534,7 +537,7 @@ void launch_ls_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, co
                                        const BlockTab&, int, hipStream_t, const LbfgsRing<RingT<T>>&);    \
   template void launch_quadq_diag<T>(const Cost<Acc<T>::type>&, int, int, const T*, Acc<T>::type*, double*, \
                                      const DevScalars*, const BlockTab&, int, hipStream_t,                 \
-                                     const LbfgsRing<T>&);                                                 \
+                                     const LbfgsRing<T>&, const SideFin&);                                 \
   template void launch_upd_eval_diag<T>(long, int, int, T*, T*, const Acc<T>::type*, const double*,          \
                                         const double*, double, double*, double*, const DevScalars*, int,     \
                                         const BlockTab&, int, hipStream_t, const LbfgsRing<RingT<T>>&);     \

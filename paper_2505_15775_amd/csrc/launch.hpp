@@ -22,7 +22,7 @@ void launch_objgrad_diag(const Cost<typename Acc<T>::type>& C, int r, int varian
 template <typename T>
 void launch_quadq_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, const T* G,
                        typename Acc<T>::type* Q, double* part, const DevScalars* sc, const BlockTab& tab, int nblk,
-                       hipStream_t st, const LbfgsRing<T>& lb = LbfgsRing<T>{});
+                       hipStream_t st, const LbfgsRing<T>& lb = LbfgsRing<T>{}, const SideFin& side = SideFin{});
 template <typename T>
 void launch_upd_eval_diag(long n, int r, int variant, T* R, T* G, const typename Acc<T>::type* Q, const double* y,
                           const double* b, double sigma, double* Av, double* part, const DevScalars* sc,
@@ -37,7 +37,8 @@ void launch_lbfgs_reset(LbfgsState* s, int m, hipStream_t st, int count = 1);
 // nb blocks; returns the blocks launched.
 template <typename T>
 int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
-                      const DevScalars* sc, hipStream_t st, const BlockTab& tab = BlockTab{});
+                      const DevScalars* sc, hipStream_t st, const BlockTab& tab = BlockTab{},
+                      const SideFin& side = SideFin{});
 // Pair update and the coefficients of the next direction (one block per
 // instance) from the partials of nb blocks.
 void launch_fin_lbfgs(const double* part, int nb, int m, const DevScalars* sc, LbfgsState* s, hipStream_t st,

@@ -16,6 +16,7 @@
 // Pure streaming kernels: no gathers, no MFMA.
 #include <algorithm>
 
+#include "finalize.hpp"
 #include "spmm_row.hpp"
 
 namespace almbm {
@@ -130,12 +131,13 @@ __device__ __forceinline__ void dots_chunk(DotAcc<typename Acc<T>::type, M>& A, 
 template <typename T, int M>
 __global__ void __launch_bounds__(kBlock)
 k_lbfgs_dots(long len, int r, const T* __restrict__ G, LbfgsRing<RingT<T>> lb, double* __restrict__ part,
-             const DevScalars* __restrict__ sc_base, BlockTab tab, int vgrid) {
+             const DevScalars* sc_base, BlockTab tab, int vgrid, SideFin side) {
+  if (run_side_fin(side)) return;
   using V = typename Acc<T>::type;
   using R = RingT<T>;
   constexpr int N = FlatVec<T>::N;
   long a = 0, e = len;
-  int inst = 0, vb0 = blockIdx.x, vstep = gridDim.x;
+  int inst = 0, vb0 = blockIdx.x, vstep = gridDim.x - (side.part ? 1 : 0);
   if (tab.inst) {
     inst = tab.inst[blockIdx.x];
     const long xb = row_base(tab, inst);
@@ -145,7 +147,7 @@ k_lbfgs_dots(long len, int r, const T* __restrict__ G, LbfgsRing<RingT<T>> lb, d
     vgrid = 1;
     vstep = 1;
   }
-  if (sc_base[inst].flag) return;
+  if (block_stopped(sc_base + inst)) return;
   const LbfgsState* S = lb.s + inst;
   const int cnt = S->cnt;
   const bool have = S->have != 0;
@@ -459,12 +461,7 @@ k_fin_lsdir(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc
   inst_blocks(tab, blockIdx.x, nb, b0, b1);
   __shared__ double tot[NUM_P];
   fin_rows<NUM_P>(part + (long)b0 * NUM_P, b1 - b0, tot);
-  if (threadIdx.x != 0) return;
-  constexpr int K = 10;
-  const int sl[K] = {P_GG, P_GP, P_YA1, P_YA2, P_EA1, P_EA2, P_A1A1, P_A1A2, P_A2A2, P_RG};
-#pragma unroll
-  for (int k = 0; k < K; ++k) sc->tot[sl[k]] = tot[sl[k]];
-  S->ee = tot[P_GG];
+  if (threadIdx.x == 0) finish_lsdir(tot, sc, S);
 }
 
 // ---- launchers ---------------------------------------------------------------------
@@ -478,7 +475,7 @@ void launch_lbfgs_reset(LbfgsState* s, int m, hipStream_t st, int count) {
 // the block sums and the finalizer's rows stay few.
 template <typename T>
 int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
-                      const DevScalars* sc, hipStream_t st, const BlockTab& tab) {
+                      const DevScalars* sc, hipStream_t st, const BlockTab& tab, const SideFin& side) {
   int vgrid = 1;
   if (!tab.inst) {
     const long v = std::min<long>(4096, std::max<long>(8, (len / r + 63) / 64));
@@ -487,11 +484,12 @@ int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<
     nb = (int)std::min<long>({(long)nb, (long)vgrid, std::max<long>(8, b)});
     if (sizeof(typename Acc<T>::type) == 8) vgrid = nb;  // FP64 sums need no virtual blocks
   }
+  const dim3 grid(nb + (side.part ? 1 : 0));
   if (m <= 3)
-    hipLaunchKernelGGL((k_lbfgs_dots<T, 3>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab, vgrid);
+    hipLaunchKernelGGL((k_lbfgs_dots<T, 3>), grid, dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab, vgrid, side);
   else
-    hipLaunchKernelGGL((k_lbfgs_dots<T, kMaxLbfgs>), dim3(nb), dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab,
-                       vgrid);
+    hipLaunchKernelGGL((k_lbfgs_dots<T, kMaxLbfgs>), grid, dim3(kBlock), 0, st, len, r, G, lb, part, sc, tab, vgrid,
+                       side);
   return nb;
 }
 
@@ -529,7 +527,7 @@ void launch_fin_lsdir(const double* part, int nb, DevScalars* sc, LbfgsState* s,
 
 #define ALMBM_LBFGS_INST(T)                                                                               \
   template int launch_lbfgs_dots<T>(long, int, int, const T*, const LbfgsRing<RingT<T>>&, double*, int,    \
-                                    const DevScalars*, hipStream_t, const BlockTab&);                      \
+                                    const DevScalars*, hipStream_t, const BlockTab&, const SideFin&);      \
   template void launch_lbfgs_combine<T>(long, int, int, const T*, const T*, const double*, const double*,   \
                                         double, const double*, const LbfgsRing<RingT<T>>&, double*,          \
                                         const DevScalars*, int, hipStream_t, const BlockTab&);

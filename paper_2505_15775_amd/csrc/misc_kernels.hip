@@ -2,7 +2,7 @@
 // rule, the factor update and the FP64 dual update.
 #include <math.h>
 
-#include "kernels.hpp"
+#include "finalize.hpp"
 #include "quartic.hpp"
 
 namespace almbm {
@@ -11,10 +11,8 @@ __device__ __forceinline__ bool finite(double x) { return isfinite(x); }
 
 // ---- finalize kernels (one block) ------------------------------------------------
 
-// Objective totals of the DIAG family.  mode 0: API call, writes *f_out.
-// mode 1: inner loop step 1 -- after max_inner steps stop (flag 2), else the
-// stop test ||G|| ||R|| <= tol (1 + |<C,RR^T>|) (flag 1), else count the step.
-// One block per instance (blockIdx.x; a single instance without a table).
+// Objective totals of the DIAG family (finish_objgrad).  One block per instance
+// (blockIdx.x; a single instance without a table).
 __global__ void __launch_bounds__(kFin)
 k_fin_objgrad(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc_base, double sigma, int mode,
               double* __restrict__ f_out, BlockTab tab) {
@@ -26,22 +24,7 @@ k_fin_objgrad(const double* __restrict__ part, int nb, DevScalars* __restrict__ 
   __shared__ double tot[NUM_P];
   fin_rows<NUM_P>(part + (long)b0 * NUM_P, b1 - b0, tot);
   if (threadIdx.x < NUM_P) sc->tot[threadIdx.x] = tot[threadIdx.x];
-  if (threadIdx.x != 0) return;
-  if (f_out) f_out += q;
-  const double f = tot[P_C0] + tot[P_YBMA] + 0.5 * sigma * tot[P_EE];
-  sc->f = f;
-  if (!finite(f) || !finite(tot[P_GG])) sc->numeric_error = 1;
-  if (f_out) *f_out = f;
-  if (mode == 1) {
-    const double lhs = sqrt(tot[P_GG]) * sqrt(tot[P_RR]);
-    if (sc->iter >= sc->max_inner) {
-      sc->flag = 2;
-    } else if (lhs <= sc->tol * (1.0 + fabs(tot[P_C0])) || !finite(lhs)) {
-      sc->flag = 1;
-    } else {
-      sc->iter += 1;
-    }
-  }
+  if (threadIdx.x == 0) finish_objgrad(tot, sc, sigma, mode, f_out ? f_out + q : nullptr);
 }
 
 // Step rule: reduce the <G, CG> partials into tot[P_C2], form the quartic and

@@ -221,3 +221,26 @@ def test_hub_rows_of_every_trip_count(prec, tol, r):
         z = oracle.cost_apply(po, vh[:, None])[:, 0] - y * vh
         scale = np.abs(P_o).max() + 5
         assert abs(vh @ z - theta) <= 1e-12 * scale and abs(np.linalg.norm(z - theta * vh) - resid) <= 1e-10 * scale
+
+
+@pytest.mark.parametrize("solver", ["gd", "lbfgs"])
+@pytest.mark.parametrize("tol,steps", [(0.0, 1), (0.0, 33), (2e-2, 200)])
+def test_inner_steps_around_the_side_block_grid(solver, tol, steps):
+    """512 blocks leave a step's totals to a block of the next pass, 520 to a kernel: the same sums in other groups,
+    so the same step count and stop reason and, over these FP64 paths, objectives to 1e-9 relative."""
+    m = _almbm()
+    g = gen.er_graph(9000, 40000, 5, "gauss")
+    out = []
+    for blocks in (512, 520):
+        p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=8, lanczos_kmax=0, lbfgs_memory_max=3,
+                             device=DEV)
+        p.set_tiles(0, blocks)
+        rng = np.random.default_rng(7)
+        R = p.factor(rng.standard_normal((g.n, 8)) / 3)
+        y = torch.zeros(g.n, dtype=torch.float64, device=DEV)
+        opts = dict(inner_solver=m._lib.INNER_LBFGS, lbfgs_memory=3) if solver == "lbfgs" else {}
+        out.append(p.inner_solve(R, y, tol, steps, sigma=1.0, **opts))
+        p.close()
+    (n0, flag0, f0), (n1, flag1, f1) = out
+    assert n0 == n1 and flag0 == flag1
+    assert abs(f0 - f1) <= 1e-9 * abs(f1)
