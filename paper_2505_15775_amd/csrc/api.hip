@@ -733,11 +733,14 @@ static void enqueue_inner_step(alm_bm_problem* p, int r, T* R, const double* y, 
     }
     launch_fin_step(p->part_c2, p->nblk, sc, sigma, 1, nullptr, nullptr, st, p->tab, p->count);
   } else {
-    enqueue_objgrad<T>(p, r, R, y, sigma, G, p->Av, sc, 1, nullptr, st);
-    if (step >= max_inner) return;
-    launch_edges_p3<T>(cost_of<T>(p), p->adj, r, p->variant, R, G, y, d.b, p->Av, p->part, sc, p->nblk, st,
-                       p->rho);
-    launch_fin_edges3(p->part, p->nblk, r, sc, y, d.b, sigma, d.trace_coef, d.j_coef, 1, nullptr, nullptr, st);
+    const bool last = step >= max_inner;
+    EdgeFin side;
+    launch_edges_eval<T>(cost_of<T>(p), p->adj, d.n, r, p->variant, R, y, d.b, sigma, d.trace_coef, d.j_coef, p->rho,
+                         p->Av, p->wE, nullptr, G, p->part, sc, p->nblk, 1, nullptr, st, last ? nullptr : &side);
+    if (last) return;
+    const double* part3 = launch_edges_p3<T>(cost_of<T>(p), p->adj, r, p->variant, R, G, y, d.b, p->Av, p->part, sc,
+                                             p->nblk, st, p->rho, side);
+    launch_fin_edges3(part3, p->nblk, r, sc, y, d.b, sigma, d.trace_coef, d.j_coef, 1, nullptr, nullptr, st);
     launch_update<T>((long)d.n * r, R, G, sc, 1, st);
   }
 }

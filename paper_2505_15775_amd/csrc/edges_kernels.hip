@@ -21,8 +21,9 @@
 // several edges in flight; consecutive groups read consecutive entries of the
 // edge arrays, and R_i of consecutive edges is mostly the same row and comes
 // from L1.  Pass 2 walks rows of the symmetric pattern.
-#include "spmm_row.hpp"
+#include "finalize.hpp"
 #include "quartic.hpp"
+#include "spmm_row.hpp"
 
 namespace almbm {
 
@@ -312,14 +313,17 @@ k_edges_p2(Cost<typename Acc<T>::type> C, EdgeAdj A, int r, const T* __restrict_
 // Finalize of passes 1 and 2, either one or both (a null table skips its half).
 // Pass 1: trace row, w_0, column sums; writes Av[0].  Pass 2: objective and
 // (mode 1) the inner stop test.
-__global__ void __launch_bounds__(kFin)
-k_fin_edges12(const double* __restrict__ part1, const double* __restrict__ part2, int nb, int ncs,
-              DevScalars* __restrict__ sc, const double* __restrict__ y, const double* __restrict__ b, double sigma,
-              double c_tr, double* __restrict__ Av, int mode, double* __restrict__ f_out) {
-  if (sc->flag) return;
+template <int THREADS>
+__device__ __forceinline__ void finish_edges12(const EdgeFin& F) {
+  DevScalars* sc = F.sc;
+  const int nb = F.nb, ncs = F.ncs;
+  const double *y = F.y, *b = F.b;
+  const double sigma = F.sigma, c_tr = F.c_tr;
+  double *Av = F.Av, *f_out = F.f_out;
+  const int mode = F.mode;
   __shared__ double t1[E1_N + kMaxR], t2[E2_N + kMaxR];
-  if (part1) {
-    fin_table(part1, nb, E1_N + ncs, t1);
+  if (F.part1) {
+    fin_table<THREADS>(F.part1, nb, E1_N + ncs, t1);
     if (threadIdx.x < ncs) sc->colsum[threadIdx.x] = t1[E1_N + threadIdx.x];
     if (threadIdx.x == 0) {
       const double rr = t1[E1_RR];
@@ -333,8 +337,8 @@ k_fin_edges12(const double* __restrict__ part1, const double* __restrict__ part2
       sc->tot[P_RR] = rr;
     }
   }
-  if (!part2) return;
-  fin_table(part2, nb, E2_N + ncs, t2);
+  if (!F.part2) return;
+  fin_table<THREADS>(F.part2, nb, E2_N + ncs, t2);
   if (threadIdx.x < ncs) sc->gcolsum[threadIdx.x] = t2[E2_N + threadIdx.x];
   if (threadIdx.x != 0) return;
   sc->tot[P_C0] = t2[E2_C0];
@@ -352,6 +356,10 @@ k_fin_edges12(const double* __restrict__ part1, const double* __restrict__ part2
     else sc->iter += 1;
   }
 }
+__global__ void __launch_bounds__(kFin) k_fin_edges12(EdgeFin F) {
+  if (F.sc->flag) return;
+  finish_edges12<kFin>(F);
+}
 
 // Pass 3: line-search partials over the edges and <G, (S + D) G>.  As pass 1,
 // with two rows (R_j, G_j) gathered per edge.  Completion n = 2e4, r = 3, FP64:
@@ -360,16 +368,21 @@ template <typename T, int LPR, int VEC, bool FULL>
 __global__ void __launch_bounds__(kBlock)
 k_edges_p3(Cost<typename Acc<T>::type> C, EdgeAdj A, int r, const T* __restrict__ R, const T* __restrict__ G,
            const double* __restrict__ y, const double* __restrict__ b, const double* __restrict__ Av,
-           double* __restrict__ part, const DevScalars* __restrict__ sc, double rho) {
+           double* __restrict__ part, const DevScalars* sc, double rho, EdgeFin side) {
   using V = typename Acc<T>::type;
-  if (sc->flag) return;
+  if (block_stopped(sc)) return;
+  const int nblk = gridDim.x - (side.part2 ? 1 : 0);
+  if ((int)blockIdx.x == nblk) {  // the finalizer of passes 1 and 2
+    finish_edges12<kBlock>(side);
+    return;
+  }
   constexpr int RPB = kBlock / LPR;
   constexpr int U = 2;
   const int lane = threadIdx.x % LPR;
   const int slot = threadIdx.x / LPR;
   SplitAcc<E3_N, 1> acc;  // every lane its own sums
   acc.zero();
-  const RowChunk ce = row_chunk(A.E);
+  const RowChunk ce = row_chunk(A.E, false, nblk);
   for (long base = ce.lo + slot; base < ce.hi; base += RPB * U) {
     EdgeLanes<U, LPR> ed(A, base, RPB, ce.hi, lane);
     double res[ed.M], ye[ed.M];
@@ -415,7 +428,7 @@ k_edges_p3(Cost<typename Acc<T>::type> C, EdgeAdj A, int r, const T* __restrict_
     }
   }
   if (C.rp || C.ell > 0 || C.dg) {
-    const RowChunk ch = row_chunk(C.n);
+    const RowChunk ch = row_chunk(C.n, false, nblk);
     for (long i = ch.lo + slot; i < ch.hi; i += RPB) {
       V gi[VEC], q[VEC];
       load_frag<T, VEC, FULL>(G + i * r, lane, r, gi);
@@ -543,39 +556,49 @@ static void p2_cfg(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r
 template <typename T, int LPR, int VEC>
 static void p3_cfg(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, const T* R, const T* G,
                    const double* y, const double* b, const double* Av, double* part, const DevScalars* sc, int nblk,
-                   hipStream_t st, double rho) {
+                   hipStream_t st, double rho, const EdgeFin& side) {
+  const dim3 grid(nblk + (side.part2 ? 1 : 0));
   if (r == LPR * VEC)
-    hipLaunchKernelGGL((k_edges_p3<T, LPR, VEC, true>), dim3(nblk), dim3(kBlock), 0, st, C, A, r, R, G, y, b, Av,
-                       part, sc, rho);
+    hipLaunchKernelGGL((k_edges_p3<T, LPR, VEC, true>), grid, dim3(kBlock), 0, st, C, A, r, R, G, y, b, Av,
+                       part, sc, rho, side);
   else
-    hipLaunchKernelGGL((k_edges_p3<T, LPR, VEC, false>), dim3(nblk), dim3(kBlock), 0, st, C, A, r, R, G, y, b, Av,
-                       part, sc, rho);
+    hipLaunchKernelGGL((k_edges_p3<T, LPR, VEC, false>), grid, dim3(kBlock), 0, st, C, A, r, R, G, y, b, Av,
+                       part, sc, rho, side);
 }
 
 template <typename T>
 void launch_edges_eval(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, long n, int r, int variant, const T* R,
                        const double* y, const double* b, double sigma, double c_tr, double j_coef, double rho,
                        double* Av, double* wE, const T* G_in, T* G, double* part, DevScalars* sc, int nblk, int mode,
-                       double* f_out, hipStream_t st) {
+                       double* f_out, hipStream_t st, EdgeFin* defer) {
   const int ncs = j_coef != 0.0 ? r : 0;
   ALMBM_DISPATCH_EDGES(T, p1_cfg, A, n, r, R, y, b, sigma, Av, wE, part, sc, nblk, st, rho, ncs);
   // pass 2 waits for the finalizer of pass 1 only for the trace row's w_0 and the
   // column sums; it may then reuse its table (part holds NUM_P + kMaxR per block)
   const bool wait = c_tr != 0.0 || ncs > 0;
   double* part2 = wait ? part : part + (long)nblk * E1_N;
-  if (wait)
-    hipLaunchKernelGGL(k_fin_edges12, dim3(1), dim3(kFin), 0, st, part, nullptr, nblk, ncs, sc, y, b, sigma, c_tr, Av,
-                       mode, nullptr);
+  EdgeFin fin{part, nullptr, nblk, ncs, sc, y, b, sigma, c_tr, Av, mode, nullptr};
+  if (wait) hipLaunchKernelGGL(k_fin_edges12, dim3(1), dim3(kFin), 0, st, fin);
   ALMBM_DISPATCH_EDGES(T, p2_cfg, C, A, r, R, wE, c_tr, j_coef, G_in, G, part2, sc, nblk, st, ncs);
-  hipLaunchKernelGGL(k_fin_edges12, dim3(1), dim3(kFin), 0, st, wait ? nullptr : part, part2, nblk, ncs, sc, y, b,
-                     sigma, c_tr, Av, mode, f_out);
+  fin.part1 = wait ? nullptr : part;
+  fin.part2 = part2;
+  fin.f_out = f_out;
+  if (defer)
+    *defer = fin;
+  else
+    hipLaunchKernelGGL(k_fin_edges12, dim3(1), dim3(kFin), 0, st, fin);
 }
 template <typename T>
-void launch_edges_p3(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, int variant, const T* R,
-                     const T* G, const double* y, const double* b, const double* Av, double* part,
-                     const DevScalars* sc, int nblk, hipStream_t st, double rho) {
-  ALMBM_DISPATCH_EDGES(T, p3_cfg, C, A, r, R, G, y, b, Av, part, sc, nblk, st, rho);
+double* launch_edges_p3(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, int variant, const T* R,
+                        const T* G, const double* y, const double* b, const double* Av, double* part,
+                        const DevScalars* sc, int nblk, hipStream_t st, double rho, const EdgeFin& side) {
+  // behind the rows of passes 1 and 2 that the side block reads: at most 4 + kMaxR of
+  // a block's NUM_P + kMaxR, and pass 3 has 8
+  if (side.part2) part += (side.part2 - part) + (long)nblk * (E2_N + side.ncs);
+  ALMBM_DISPATCH_EDGES(T, p3_cfg, C, A, r, R, G, y, b, Av, part, sc, nblk, st, rho, side);
+  return part;
 }
+static_assert(E1_N + E2_N + E3_N <= NUM_P + kMaxR && E2_N + kMaxR + E3_N <= NUM_P + kMaxR);
 void launch_fin_edges3(const double* part, int nb, int r, DevScalars* sc, const double* y, const double* b,
                        double sigma, double c_tr, double j_coef, int mode, double* coeffs_out, double* t_out,
                        hipStream_t st) {
@@ -586,10 +609,11 @@ void launch_fin_edges3(const double* part, int nb, int r, DevScalars* sc, const 
 #define ALMBM_INST_E(T)                                                                                          \
   template void launch_edges_eval<T>(const Cost<Acc<T>::type>&, const EdgeAdj&, long, int, int, const T*,        \
                                      const double*, const double*, double, double, double, double, double*,      \
-                                     double*, const T*, T*, double*, DevScalars*, int, int, double*, hipStream_t); \
-  template void launch_edges_p3<T>(const Cost<Acc<T>::type>&, const EdgeAdj&, int, int, const T*, const T*,       \
+                                     double*, const T*, T*, double*, DevScalars*, int, int, double*, hipStream_t, \
+                                     EdgeFin*);                                                                  \
+  template double* launch_edges_p3<T>(const Cost<Acc<T>::type>&, const EdgeAdj&, int, int, const T*, const T*,       \
                                    const double*, const double*, const double*, double*, const DevScalars*, int, \
-                                   hipStream_t, double);
+                                   hipStream_t, double, const EdgeFin&);
 
 ALMBM_INST_E(double)
 ALMBM_INST_E(float)

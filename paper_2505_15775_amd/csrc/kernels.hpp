@@ -204,6 +204,21 @@ struct SideFin {
   LbfgsState* ls = nullptr;
 };
 
+// Finalizer of the edge family's passes 1 and 2, either one or both (a null table
+// skips its half): a kernel of its own or, in the inner loop, a block of pass 3.
+struct EdgeFin {
+  const double* part1 = nullptr;
+  const double* part2 = nullptr;
+  int nb = 0, ncs = 0;
+  DevScalars* sc = nullptr;
+  const double* y = nullptr;
+  const double* b = nullptr;
+  double sigma = 0.0, c_tr = 0.0;
+  double* Av = nullptr;
+  int mode = 0;
+  double* f_out = nullptr;
+};
+
 // Block range of instance `q` for a finalize kernel (single mode: [0, nb)).
 __device__ __forceinline__ void inst_blocks(const BlockTab& t, int q, int nb, int& b0, int& b1) {
   if (!t.iblo) {

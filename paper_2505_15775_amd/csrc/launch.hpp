@@ -61,16 +61,20 @@ void launch_ls_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, co
 
 // Objective and gradient of the edge family at R (passes 1 and 2 and their
 // finalizers).  With G_in the direction is read instead of computed and G is
-// not written (line-search API).  mode and f_out as for launch_fin_objgrad.
+// not written (line-search API).  mode and f_out as for launch_fin_objgrad.  With
+// defer the last finalizer is left to launch_edges_p3.
 template <typename T>
 void launch_edges_eval(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, long n, int r, int variant, const T* R,
                        const double* y, const double* b, double sigma, double c_tr, double j_coef, double rho,
                        double* Av, double* wE, const T* G_in, T* G, double* part, DevScalars* sc, int nblk, int mode,
-                       double* f_out, hipStream_t st);
+                       double* f_out, hipStream_t st, EdgeFin* defer = nullptr);
+// side: a deferred finalizer, run by a block of pass 3.  Returns the table that pass 3
+// leaves its partial sums in.
 template <typename T>
-void launch_edges_p3(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, int variant, const T* R,
-                     const T* G, const double* y, const double* b, const double* Av, double* part,
-                     const DevScalars* sc, int nblk, hipStream_t st, double rho = 1.0);
+double* launch_edges_p3(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r, int variant, const T* R,
+                        const T* G, const double* y, const double* b, const double* Av, double* part,
+                        const DevScalars* sc, int nblk, hipStream_t st, double rho = 1.0,
+                        const EdgeFin& side = EdgeFin{});
 void launch_fin_edges3(const double* part, int nb, int r, DevScalars* sc, const double* y, const double* b,
                        double sigma, double c_tr, double j_coef, int mode, double* coeffs_out, double* t_out,
                        hipStream_t st);

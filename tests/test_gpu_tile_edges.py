@@ -244,3 +244,28 @@ def test_inner_steps_around_the_side_block_grid(solver, tol, steps):
     (n0, flag0, f0), (n1, flag1, f1) = out
     assert n0 == n1 and flag0 == flag1
     assert abs(f0 - f1) <= 1e-9 * abs(f1)
+
+
+@pytest.mark.parametrize("r", [3, 8, 33])
+@pytest.mark.parametrize("trace,j_coef", [(0.0, 0.0), (1.5, 0.0), (1.5, 0.5)])
+def test_edge_family_steps_against_single_calls(r, trace, j_coef):
+    """Inner steps, whose pass 3 finalizes passes 1 and 2, against the same steps made of objective, line search and
+    an update outside.  Six FP64 gradient steps: rounding of 1e-16 grows by far less than 1e6."""
+    rng = np.random.default_rng(r)
+    n, E = 900, 7001
+    iu, ju = np.triu_indices(n, 1)
+    pick = np.sort(rng.choice(iu.size, size=E, replace=False))
+    p = _almbm().Problem.edges(n, iu[pick], ju[pick], rng.standard_normal(E + 1), trace, j_coef=j_coef,
+                               cost_diag=rng.standard_normal(n), precision="f64", r_max=40, lanczos_kmax=0, device=DEV)
+    R0, y = rng.standard_normal((n, r)) / 3, torch.from_numpy(rng.standard_normal(E + 1)).to(DEV)
+    R = p.factor(R0)
+    done, flag, f = p.inner_solve(R, y, 0.0, 6, sigma=1.3)
+    S = p.factor(R0)
+    for _ in range(6):
+        _, G, _ = p.objective_grad(S, y, 1.3)
+        _, t = p.line_search(S, G, y, 1.3)
+        S = S - t * G
+    f_s, _, _ = p.objective_grad(S, y, 1.3)
+    assert (done, flag) == (6, 2)
+    assert rel(R.cpu(), S.cpu().numpy()) <= 1e-10
+    assert abs(f - f_s.item()) <= 1e-10 * abs(f)
