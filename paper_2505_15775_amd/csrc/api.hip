@@ -1304,12 +1304,19 @@ struct LanczosOut {
 
 // Lanczos on Z(y) with two classical Gram-Schmidt passes per step; the Ritz
 // vector for the smallest Ritz value goes to v (device, n).
+// ordered: every sum over a grid of the row count alone, the hub rows of the
+// default threshold included.  A pass that restarts from a Ritz vector, and a power-law
+// cost in its first, magnify the rounding of their sums by 1e6 and more, so where
+// the vector itself is the result its sums keep one order, whatever the kernels.
 static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, double tol, uint64_t seed,
-                                  bool restart, double* v, LanczosOut& out, hipStream_t st) {
+                                  bool restart, bool ordered, double* v, LanczosOut& out, hipStream_t st) {
   const auto& d = p->d;
   const long n = d.n;
   const long ldq = n;
-  const int nb = p->lnb;
+  ordered = ordered || p->C64.nh > 0;
+  const int nb = ordered ? vec_blocks(n, true) : p->lnb;
+  Cost<double> C = p->C64;
+  if (ordered) C.nh = p->hubs;
   kmax = std::min(kmax, p->kmax);
   if (kmax < 1) return fail(ALM_BM_ERR_INVALID_ARG, "lanczos: no Lanczos workspace (lanczos_kmax = 0)");
   kmax = (int)std::min<long>(kmax, n);
@@ -1329,7 +1336,6 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   int m = 0;
   double theta = 0.0;
   bool sums = false;
-  const bool ordered = p->C64.nh > 0;  // hub rows (DIAG family)
   const int check_every = n <= 4096 ? 4 : 8;
   // Small problems: the next steps are enqueued before the host looks at a check,
   // so that the device does not wait for the tridiagonal eigenproblem (about 60
@@ -1369,14 +1375,14 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
     const bool last = (j + 1 == kmax);
     const bool check = ((j + 1) % check_every) == 0 || last;
     if (ordered) {
-      launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, p->Q + (long)j * ldq, p->lw, st);
+      launch_slack_mv(C, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, p->Q + (long)j * ldq, p->lw, st);
       launch_gs2_ordered(n, j + 1, p->Q, ldq, p->lw, p->lpart, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
       launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, nullptr, st);
-      launch_scale(n, p->lw, p->lbeta + j, p->Q + (long)(j + 1) * ldq, p->lpart2, nb, nullptr, st);
+      launch_scale(n, p->lw, p->lbeta + j, p->Q + (long)(j + 1) * ldq, p->lpart2, nb, qsum, st);
     } else {
       double* wj = j & 1 ? p->lw2 : p->lw;  // Z q_j, then the next column before scaling
       const LzStep step{j, p->lpart2, nb, p->lnb, p->lh1, p->lh2, p->lalpha, p->lbeta, sums};
-      launch_lz_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, step,
+      launch_lz_mv(C, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, step,
                    j == 0 ? p->Q : (j & 1 ? p->lw : p->lw2), p->Q + (long)j * ldq, wj, nb, st);
       launch_gs2(n, j + 1, p->Q, ldq, wj, p->lpart, p->lpartb, p->lpart2, p->lnb, nb, p->lh1, p->lh2, st);
       sums = !check && nb <= kLzFewBlocks;
@@ -1404,7 +1410,7 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   launch_combine(n, m, p->Q, ldq, p->ls, v, p->lpart2, nb, st);
   launch_fin_sum(p->lpart2, nb, p->lscal + 1, 1, st);
   launch_scale(n, v, p->lscal + 1, v, p->lpart2, nb, qsum, st);
-  launch_slack_mv(p->C64, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, v, p->lw, st);
+  launch_slack_mv(C, cons, p->adj, y, d.trace_coef, d.j_coef, qsum, v, p->lw, st);
   launch_resid(n, p->lw, v, theta, nullptr, p->lpart2, nb, st);
   launch_fin_sum(p->lpart2, nb, p->lscal + 2, 1, st);
   double hres = 0.0;
@@ -1422,10 +1428,10 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
 // exceeds tol (a pass that stops at kmax without converging overestimates
 // lambda_min; the restarts keep the KKT test and the rank test honest).
 static alm_bm_status lanczos_run(alm_bm_problem* p, const double* y, int kmax, double tol, uint64_t seed, double* v,
-                                 LanczosOut& out, hipStream_t st, int restarts = 3) {
+                                 LanczosOut& out, hipStream_t st, int restarts = 3, bool ordered = false) {
   int total = 0;
   for (int rs = 0; rs <= restarts; ++rs) {
-    STCHK(lanczos_pass(p, y, kmax, tol, seed, rs > 0, v, out, st));
+    STCHK(lanczos_pass(p, y, kmax, tol, seed, rs > 0, ordered, v, out, st));
     total += out.iters;
     if (out.resid <= tol) break;
   }
@@ -1440,7 +1446,7 @@ extern "C" alm_bm_status alm_bm_lanczos_min_eig(alm_bm_problem* p, const double*
   if (max_iter < 1) return fail(ALM_BM_ERR_INVALID_ARG, "lanczos_min_eig: max_iter < 1");
   if (max_iter > p->kmax) return fail(ALM_BM_ERR_INVALID_ARG, "lanczos_min_eig: max_iter > lanczos_kmax");
   LanczosOut o;
-  STCHK(lanczos_run(p, y, max_iter, tol, seed, v ? v : p->lv, o, st));
+  STCHK(lanczos_run(p, y, max_iter, tol, seed, v ? v : p->lv, o, st, 3, true));
   HIPCHK(hipMemcpyAsync(theta, &o.theta, sizeof(double), hipMemcpyHostToDevice, st));
   if (resid) HIPCHK(hipMemcpyAsync(resid, &o.resid, sizeof(double), hipMemcpyHostToDevice, st));
   if (iters) HIPCHK(hipMemcpyAsync(iters, &o.iters, sizeof(int32_t), hipMemcpyHostToDevice, st));
