@@ -198,8 +198,8 @@ k_lz_proj_wide(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef 
   }
 }
 
-// The same projections with every sum in a fixed order of its own (costs with hub
-// rows, launch_gs2_ordered): a wave per column and row chunk, four running sums
+// The same projections with every sum in an order of the row count alone
+// (launch_gs2_ordered): a wave per column and row chunk, four running sums
 // per lane; the subtraction column by column; the norm over row chunks.
 __global__ void __launch_bounds__(kBlock)
 k_dots_ordered(long n, int ncol, const double* __restrict__ Q, long ldq, const double* __restrict__ w,
@@ -242,6 +242,87 @@ k_sub_ordered(long n, int ncol, const double* __restrict__ Q, long ldq, const do
     for (int c = 0; c < CS; ++c) v -= q[c] * hs[c0 + c];
   }
   w[i] = v;
+}
+
+// k_sub_ordered and the k_dots_ordered after it with one read of the basis, for up
+// to NC columns, bit for bit: a thread owns a row of each 256-row trip, so that wave
+// k's threads hold what the lanes' running sums a_k of k_dots_ordered hold, and the
+// rows of a last, partial trip go to a_0 in their order as there.  A thread keeps its
+// row's NC entries and NC sums in registers (one wave per SIMD for NC = 64, with all
+// loads of a trip in flight).  Bound by HBM: n = 1e6, 33 to 56 columns, 88 us (4.2
+// TB/s) against 58 + 85 us as two kernels.  One block per row chunk cannot fill the
+// chip with fewer than 128 of them (n = 5.2e5), where the two kernels stay.
+template <int NC>
+__global__ void __launch_bounds__(kBlock)
+k_sub_dots_ordered(long n, int ncol, const double* __restrict__ Q, long ldq, const double* __restrict__ h,
+                   double* __restrict__ w, double* __restrict__ part, int pld) {
+  constexpr int G = 16;  // columns added up together at the end
+  __shared__ double hs[NC];
+  __shared__ double vs[kBlock];
+  __shared__ double sm[kBlock / kWave][G][kWave];
+  LzCoef hc;
+  hc.h = h;
+  load_coef(hc, 0, ncol, hs);
+  const RowChunk ch = row_chunk(n);
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  double acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+  for (long base = ch.lo; base < ch.hi; base += kBlock) {
+    const long i = base + threadIdx.x;
+    const bool in = i < ch.hi;
+    double q[NC];
+    double v = in ? w[i] : 0.0;
+#pragma unroll
+    for (int g = 0; g < NC; g += 8) {
+#pragma unroll
+      for (int c = g; c < g + 8; ++c) q[c] = 0.0;
+      if (g < ncol && in) {
+#pragma unroll
+        for (int c = g; c < g + 8; ++c) q[c] = Q[(long)(c < ncol ? c : ncol - 1) * ldq + i];
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < NC; g += 8) {
+      if (g < ncol) {
+#pragma unroll
+        for (int c = g; c < g + 8; ++c) v -= q[c] * hs[c];
+      }
+      __builtin_amdgcn_sched_barrier(0);  // eight coefficients from LDS at a time
+    }
+    if (in) w[i] = v;
+    if (base + lane + (kBlock - kWave) < ch.hi) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] += q[c] * v;
+    }
+    if (base + kBlock > ch.hi) {  // the last, partial trip
+      vs[threadIdx.x] = v;
+      __syncthreads();
+      if (wave == 0 && base + lane + (kBlock - kWave) >= ch.hi) {
+        for (int k = 0; k < kBlock / kWave - 1; ++k) {
+          const long row = base + lane + k * kWave;
+          if (row >= ch.hi) break;
+          const double x = vs[lane + k * kWave];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) acc[c] += Q[(long)(c < ncol ? c : ncol - 1) * ldq + row] * x;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int c0 = 0; c0 < NC; c0 += G) {
+    if (c0 >= ncol) break;
+#pragma unroll
+    for (int c = 0; c < G; ++c) sm[wave][c][lane] = acc[c0 + c];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < G / (kBlock / kWave); ++k) {
+      const int c = wave * (G / (kBlock / kWave)) + k;
+      const double a = wave_sum((sm[0][c][lane] + sm[1][c][lane]) + (sm[2][c][lane] + sm[3][c][lane]));
+      if (lane == 0 && c0 + c < ncol) part[(long)(c0 + c) * pld + blockIdx.x] = a;
+    }
+    __syncthreads();
+  }
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -712,11 +793,22 @@ void launch_gs2_ordered(long n, int ncol, const double* Q, long ldq, double* w, 
                         int nb, double* h1, double* h2, hipStream_t st) {
   const dim3 cols(nb, (ncol + kBlock / kWave - 1) / (kBlock / kWave));
   const int rows = (int)((n + kBlock - 1) / kBlock);
-  for (double* h : {h1, h2}) {
+  const bool fused = nb >= 128 && ncol <= 64;  // see k_sub_dots_ordered
+  hipLaunchKernelGGL(k_dots_ordered, cols, dim3(kBlock), 0, st, n, ncol, Q, ldq, w, part, pld);
+  fin_dots(ncol, part, pld, nb, h1, st, VecBatch{});
+  if (fused) {
+    if (ncol <= 16)
+      hipLaunchKernelGGL(k_sub_dots_ordered<16>, dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, h1, w, part, pld);
+    else if (ncol <= 32)
+      hipLaunchKernelGGL(k_sub_dots_ordered<32>, dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, h1, w, part, pld);
+    else
+      hipLaunchKernelGGL(k_sub_dots_ordered<64>, dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, h1, w, part, pld);
+  } else {
+    hipLaunchKernelGGL(k_sub_ordered, dim3(rows), dim3(kBlock), 0, st, n, ncol, Q, ldq, h1, w);
     hipLaunchKernelGGL(k_dots_ordered, cols, dim3(kBlock), 0, st, n, ncol, Q, ldq, w, part, pld);
-    fin_dots(ncol, part, pld, nb, h, st, VecBatch{});
-    hipLaunchKernelGGL(k_sub_ordered, dim3(rows), dim3(kBlock), 0, st, n, ncol, Q, ldq, h, w);
   }
+  fin_dots(ncol, part, pld, nb, h2, st, VecBatch{});
+  hipLaunchKernelGGL(k_sub_ordered, dim3(rows), dim3(kBlock), 0, st, n, ncol, Q, ldq, h2, w);
   hipLaunchKernelGGL(k_norm_ordered, dim3(nb), dim3(kBlock), 0, st, n, w, part_n, pld);
 }
 

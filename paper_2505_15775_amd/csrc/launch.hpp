@@ -152,12 +152,11 @@ void launch_dots(long n, int ncol, const double* Q, long ldq, double* w, double*
 void launch_gs2(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_b, double* part_n,
                 int pld, int nb, double* h1, double* h2, hipStream_t st, const VecBatch& vb = VecBatch{});
 // launch_gs2 with sums whose order follows from n and nb alone (single
-// instances).  Costs with hub rows take it: their largest eigenvalues are far
-// from the rest, and a pass restarted from a Ritz vector, in which those
-// directions are only rounding noise, brings the noise back to size one, so
-// that a different order of sums gives another residual (R-MAT 2^13, four
-// passes: 5 % apart; 1e-13 on Poisson degrees).  The order is the price of a
-// fourth read of the basis.
+// instances), for alm_bm_lanczos_min_eig and for costs with hub rows.  A pass
+// restarted from a Ritz vector brings the rounding of the one before, in the
+// directions that it has found already, back to size one, so that another order
+// of sums gives another vector (Poisson degrees, n = 1e6, two passes: 1.7e-8
+// apart) or, on power-law costs, another residual (R-MAT 2^13, four passes: 5 %).
 void launch_gs2_ordered(long n, int ncol, const double* Q, long ldq, double* w, double* part, double* part_n, int pld,
                         int nb, double* h1, double* h2, hipStream_t st);
 void launch_fin_ab(const double* part, int nb, int pld, const double* h1, const double* h2, int j, double* alpha,

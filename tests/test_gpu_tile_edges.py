@@ -150,6 +150,24 @@ def test_lanczos_step_shapes(n, kmax):
         assert abs(np.linalg.norm(zmat(Vh[:, k]) - th[k] * Vh[:, k]) - rs[k]) <= 1e-9 * scale
 
 
+@pytest.mark.parametrize("n,kmax", [(520000, 20), (524289, 70), (530001, 33), (600065, 16)])
+def test_lanczos_ordered_sums_over_many_row_chunks(n, kmax):
+    """Row chunks on both sides of the 128 from which a projection and the next pass's products read the basis once,
+    column counts on both sides of 16, 32 and 64, and chunks that end inside a trip of 256 rows.  The recurrence's
+    theta is the Rayleigh quotient of its vector only if every projection is right (1e-11 of the spectrum's size)."""
+    g = gen.er_graph(n, n, 3, "gauss")
+    po = oracle.maxcut_sdp(g)
+    p = _almbm().Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=4, lanczos_kmax=kmax, device=DEV)
+    y = np.random.default_rng(n).standard_normal(n)
+    theta, v, resid, iters = p.lanczos_min_eig(torch.from_numpy(y).to(DEV), max_iter=kmax, tol=0.0, seed=5)
+    zmat = lambda x: oracle.cost_apply(po, x[:, None])[:, 0] - y * x  # noqa: E731
+    vh = v.cpu().numpy()
+    scale = np.abs(y).max() + np.abs(g.w).max() * 8
+    assert kmax <= iters <= 4 * kmax and abs(np.linalg.norm(vh) - 1) <= 1e-12
+    assert abs(vh @ zmat(vh) - theta) <= 1e-11 * scale
+    assert abs(np.linalg.norm(zmat(vh) - theta * vh) - resid) <= 1e-9 * scale
+
+
 @pytest.mark.parametrize("h", [16, 32, 64])
 @pytest.mark.parametrize("nin,n,nblocks", [(8, 1, 1), (8, 31, 3), (5, 32, 1), (8, 33, 2), (1, 129, 4), (4, 1000, 7),
                                            (8, 4097, 512), (3, 5000, 64)])
