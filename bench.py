@@ -96,7 +96,7 @@ def bench_mode(g, prec, r, steps, warmup, seed, refresh_every=0, lbfgs_memory=0)
     Av = torch.empty(g.n, dtype=torch.float64, device=dev)
     sigma = 1.0
 
-    # the solve's inner loop (graph-captured, one sparse product per step between
+    # the solve's inner loop (one sparse product per step between
     # refreshes), run for a fixed number of steps (tolerance 0: never stops early)
     prob.inner_solve(R, y, 0.0, warmup, sigma=sigma, refresh_every=refresh_every)
     torch.cuda.synchronize()

@@ -480,7 +480,7 @@ alm_bm_status alm_bm_kkt(alm_bm_problem* prob, int32_t r, const void* R, const d
  * n_in <= 8.                                                                    */
 #define ALM_BM_WS_NFEAT 8
 /* feats: device n x 8 float (row-major); scratch: device n floats.  Handle must
- * be DIAG family.                                                               */
+ * be DIAG family; its own workspace is used as well, as by its other calls.     */
 alm_bm_status alm_bm_ws_features(alm_bm_problem* prob, float* feats, float* scratch, hipStream_t stream);
 /* out[k] = mean over rows of feats[:, k] (device 8 doubles); n rows; work:
  * device 512 doubles.                                                           */
