@@ -1724,9 +1724,9 @@ static alm_bm_status inner_solve(alm_bm_problem* p, int r, T* R, const double* y
   // FP32: 182 against 178), before counting its capture (about 0.3 ms a call).
   const int U = std::max(1, o.graph_unroll);
   int32_t hflag = 0;
-  int launched = 0;
+  long launched = 0;
   while (true) {
-    const int steps = std::min(U, o.max_inner + 1 - launched);
+    const int steps = (int)std::min<long>(U, (long)o.max_inner + 1 - launched);
     if (steps <= 0) return fail(ALM_BM_ERR_HIP, "inner loop did not reach its stop flag");
     for (int u = 0; u < steps; ++u) enqueue_inner_step<T>(p, r, R, y, sigma, G, refresh, st, launched + u, o.max_inner);
     launched += steps;
@@ -2876,11 +2876,11 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
     launch_inner_reset_batch(p->sc_solve, count, b->tols_dev, b->active_dev, o.max_inner, (int)o.step_rule,
                              o.eta_fixed, st);
     if (p->lb_m > 0) launch_lbfgs_reset(p->lbs, p->lb_m, st, count);  // empty memories
-    int launched = 0;
+    long launched = 0;
     while (true) {
       // A running set and its widths first take plain launches (which know the
       // step's number); a set that lasts is worth the capture of its step.
-      const int steps = std::min(U, o.max_inner + 1 - launched);
+      const int steps = (int)std::min<long>(U, (long)o.max_inner + 1 - launched);
       if (steps <= 0) return fail(ALM_BM_ERR_HIP, "batch inner loop did not reach its stop flags");
       if (steps < U || chunks < kBatchPlainChunks) {
         for (int u = 0; u < steps; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st, launched + u);
@@ -3043,7 +3043,7 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
     }
     if (o.verbose)
       std::fprintf(stderr,
-                   "[almbm batch] k=%d active=%d t=%.2fs (inner %.3fs, %d graph launches, %d captures; "
+                   "[almbm batch] k=%d active=%d t=%.2fs (inner %.3fs, %ld graph launches, %d captures; "
                    "lanczos %.3fs)\n",
                    k, nactive, now_s() - t0, tinner, launched / U, captures, tlan + tlan2);
     if (o.time_limit_s > 0.0 && now_s() - t0 > o.time_limit_s) break;

@@ -1,0 +1,54 @@
+"""Calls that an earlier change of the kernels or of the host path answered wrongly, refused or slowed down."""
+
+import numpy as np
+import pytest
+import torch
+
+import gen
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+NO_LIMIT = 2 ** 31 - 1
+
+
+def _almbm():
+    import paper_2505_15775_amd as m
+
+    return m
+
+
+@pytest.mark.parametrize("family,solver", [("diag", "gd"), ("diag", "lbfgs"), ("edges", "gd")])
+def test_inner_steps_without_a_limit(family, solver):
+    """The largest step limit: a subproblem whose stop test holds at once, and one that takes some steps, end as
+    with a limit that is merely large."""
+    m = _almbm()
+    g = gen.er_graph(500, 2000, 3, "gauss")
+    if family == "diag":
+        p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=8, lanczos_kmax=0, lbfgs_memory_max=3,
+                             device=DEV)
+    else:
+        p = m.Problem.edges(g.n, g.ei, g.ej, np.zeros(g.ei.size + 1), 0.0, cost_diag=np.full(g.n, 0.5),
+                            precision="f64", r_max=8, lanczos_kmax=0, device=DEV)
+    opts = dict(inner_solver=m._lib.INNER_LBFGS, lbfgs_memory=3) if solver == "lbfgs" else {}
+    y = torch.zeros(p.m, dtype=torch.float64, device=DEV)
+    R0 = np.random.default_rng(1).standard_normal((g.n, 8)) / 3
+    for tol in (1e30, 0.5):
+        ends = []
+        for limit in (100000, NO_LIMIT):
+            R = p.factor(R0)
+            ends.append(p.inner_solve(R, y, tol, limit, sigma=1.0, **opts) + (R.cpu().numpy().tobytes(),))
+        assert ends[0] == ends[1] and ends[0][1] == 1
+
+
+def test_batch_steps_without_a_limit():
+    m = _almbm()
+    gs = [gen.cycle_graph(9), gen.er_graph(400, 1500, 2, "pm1")]
+    probs = [m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=16, lanczos_kmax=20, device=DEV) for g in gs]
+    batch = m.Batch(probs, rank_stride=16)
+    factors = [gen.init_factor(g.n, 4, 1) for g in gs]
+    ends = []
+    for limit in (100000, NO_LIMIT):
+        st, sts, res, R, ranks, y = batch.solve(factors, eps_kkt=1e-2, max_outer=2, max_inner=limit)
+        ends.append((st, sts, ranks, [r["inner_total"] for r in res], R.cpu().numpy().tobytes()))
+    assert ends[0] == ends[1]
