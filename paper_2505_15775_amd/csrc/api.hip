@@ -93,8 +93,8 @@ struct alm_bm_problem {
   double* lv = nullptr;
   double* ls = nullptr;
   double* lscal = nullptr;
-  double* lz_host = nullptr;      // behind sc_host: two buffers of kmax + 1 alpha, kmax + 1 beta
-  hipEvent_t lz_ev[2] = {};
+  double* lz_host = nullptr;      // behind sc_host: kmax + 1 alpha, kmax + 1 beta
+  hipEvent_t lz_ev = nullptr;
   std::vector<void*> allocs;
   double* bk_h = nullptr;         // block Krylov: (kmax+1)^2 projected matrix, column sums, Ritz coefficients
   double* bk_colsum = nullptr;
@@ -146,10 +146,8 @@ static void free_all(alm_bm_problem* p) {
   if (p->sc_host) (void)hipHostFree(p->sc_host);
   p->sc_host = nullptr;
   p->lz_host = nullptr;
-  for (hipEvent_t& e : p->lz_ev) {
-    if (e) (void)hipEventDestroy(e);
-    e = nullptr;
-  }
+  if (p->lz_ev) (void)hipEventDestroy(p->lz_ev);
+  p->lz_ev = nullptr;
 }
 
 template <typename T> static const Cost<typename Acc<T>::type>& cost_of(const alm_bm_problem* p);
@@ -587,7 +585,7 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   p->lnb = vec_blocks(n, p->C64.nh > 0);
   CK(dalloc_t(p, &p->part_vec, (size_t)std::max(p->lnb, dual_blocks(d.m)) * 2 + 16));
   {
-    const size_t lz = d.lanczos_kmax > 0 ? (size_t)(d.lanczos_kmax + 1) * 4 * sizeof(double) : 0;
+    const size_t lz = d.lanczos_kmax > 0 ? (size_t)(d.lanczos_kmax + 1) * 2 * sizeof(double) : 0;
     hipError_t e = hipHostMalloc((void**)&p->sc_host, sizeof(DevScalars) + lz, hipHostMallocDefault);
     if (e != hipSuccess) return bail(fail(ALM_BM_ERR_OOM, "hipHostMalloc failed"));
     std::memset(p->sc_host, 0, sizeof(DevScalars));
@@ -617,7 +615,7 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
       *v = q;
       q += pv;
     }
-    for (hipEvent_t& e : p->lz_ev) HK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    HK(hipEventCreateWithFlags(&p->lz_ev, hipEventDisableTiming));
     CK(dalloc_t(p, &p->bk_h, (size_t)(p->kmax + 1) * (p->kmax + 1)));
     CK(dalloc_t(p, &p->bk_colsum, (size_t)(p->kmax + 1)));
     CK(dalloc_t(p, &p->bk_coef, (size_t)(p->kmax + 1) * kMaxBlockQ));
@@ -1293,13 +1291,21 @@ extern "C" alm_bm_status alm_bm_psd_step(int32_t q, const double* theta, const d
   return ALM_BM_OK;
 }
 
-// Rows up to which a Lanczos pass runs ahead of its checks (lanczos_pass).
-constexpr long kLzAheadRows = 65536;
+// Steps that a Lanczos pass enqueues between a check's copies and the host's look at
+// it, so that the device has work during the look (about 60 us with the copies and the
+// tridiagonal eigenproblem, against 20 to 40 us a step).  The check may end the pass, and
+// what was enqueued past it is then for nothing.  With none / one / two / all steps up to
+// the next check: Lovasz n = 2e4 to a residual of 1e-3 (16 steps) 499 / 543 / 584 / 850 us;
+// a whole solve of three outer iterations at n = 2000 9.0 / 8.2 / 8.3 / 8.3 ms; four passes
+// of 60 steps at n = 2e4 3.79 / 3.64 / 3.72 / 3.92 ms.  Beyond 65536 rows a step takes as
+// long as the look.
+static int lanczos_ahead(long n) { return n <= 65536 ? 1 : 0; }
 
 struct LanczosOut {
   double theta = 0.0;
   double resid = 0.0;
   int iters = 0;
+  int steps = 0;  // steps enqueued by the last pass
 };
 
 // Lanczos on Z(y) with two classical Gram-Schmidt passes per step; the Ritz
@@ -1337,20 +1343,15 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   double theta = 0.0;
   bool sums = false;
   const int check_every = n <= 4096 ? 4 : 8;
-  // Small problems: the next steps are enqueued before the host looks at a check,
-  // so that the device does not wait for the tridiagonal eigenproblem (about 60
-  // us with the copies, every 4 steps of 20 us at n = 2000).  Steps enqueued
-  // past the one that ends the pass are not used; at most 8 of 30 us at 65536
-  // rows, they cost less than the waits of the checks before, beyond more.
-  const bool ahead = n <= kLzAheadRows;
-  int slot = 0, pending = 0;  // pending: steps of the check not yet looked at
-  auto host_a = [&](int s) { return p->lz_host + (size_t)s * 2 * (p->kmax + 1); };
-  auto host_b = [&](int s) { return host_a(s) + (p->kmax + 1); };
-  // the check after `steps` steps, whose entries are on their way to buffer s
-  auto look = [&](int s, int steps, bool last, bool& done) -> alm_bm_status {
-    HIPCHK(hipEventSynchronize(p->lz_ev[s]));
-    std::copy(host_a(s), host_a(s) + steps, ha.begin());
-    std::copy(host_b(s), host_b(s) + steps, hb.begin());
+  const int ahead = lanczos_ahead(n);
+  int pending = 0;  // steps of the check not yet looked at
+  double* const host_a = p->lz_host;
+  double* const host_b = host_a + (p->kmax + 1);
+  // the check after `steps` steps, whose entries are on their way to the host
+  auto look = [&](int steps, bool last, bool& done) -> alm_bm_status {
+    HIPCHK(hipEventSynchronize(p->lz_ev));
+    std::copy(host_a, host_a + steps, ha.begin());
+    std::copy(host_b, host_b + steps, hb.begin());
     double anorm = 0.0;
     for (int i = 0; i < steps; ++i) anorm = std::max(anorm, std::fabs(ha[i]) + std::fabs(hb[i]));
     for (int i = 0; i < steps; ++i)
@@ -1388,22 +1389,22 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
       sums = !check && nb <= kLzFewBlocks;
       if (!sums) launch_fin_ab(p->lpart2, nb, p->lnb, p->lh1, p->lh2, j, p->lalpha, p->lbeta, qsum, st);
     }
+    out.steps = j + 1;
+    bool done = false;
     if (check) {
-      HIPCHK(hipMemcpyAsync(host_a(slot), p->lalpha, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-      HIPCHK(hipMemcpyAsync(host_b(slot), p->lbeta, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-      HIPCHK(hipEventRecord(p->lz_ev[slot], st));
-      bool done = false;
-      if (pending > 0) {
-        STCHK(look(1 - slot, pending, false, done));
+      if (pending > 0) {  // the last step comes before the look that is due
+        STCHK(look(pending, false, done));
         if (done) break;
       }
+      HIPCHK(hipMemcpyAsync(host_a, p->lalpha, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipMemcpyAsync(host_b, p->lbeta, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipEventRecord(p->lz_ev, st));
       pending = j + 1;
-      slot = 1 - slot;
-      if (last || !ahead) {
-        STCHK(look(1 - slot, pending, last, done));
-        pending = 0;
-        if (done) break;
-      }
+    }
+    if (pending > 0 && (last || j + 1 - pending >= ahead)) {
+      STCHK(look(pending, last, done));
+      pending = 0;
+      if (done) break;
     }
   }
   HIPCHK(hipMemcpyAsync(p->ls, z.data(), m * sizeof(double), hipMemcpyHostToDevice, st));
@@ -1451,6 +1452,24 @@ extern "C" alm_bm_status alm_bm_lanczos_min_eig(alm_bm_problem* p, const double*
   if (resid) HIPCHK(hipMemcpyAsync(resid, &o.resid, sizeof(double), hipMemcpyHostToDevice, st));
   if (iters) HIPCHK(hipMemcpyAsync(iters, &o.iters, sizeof(int32_t), hipMemcpyHostToDevice, st));
   HIPCHK(hipStreamSynchronize(st));
+  return ALM_BM_OK;
+}
+
+alm_bm_status alm_bm_internal_lanczos(alm_bm_problem* p, const double* y, int32_t max_iter, double tol, uint64_t seed,
+                                      int32_t restarts, int32_t ordered, double* v, double* tri, double* out,
+                                      hipStream_t st) {
+  if (!p || !y || !v || !tri || !out) return fail(ALM_BM_ERR_INVALID_ARG, "internal_lanczos: null argument");
+  if (max_iter < 1 || max_iter > p->kmax) return fail(ALM_BM_ERR_INVALID_ARG, "internal_lanczos: max_iter");
+  LanczosOut o;
+  STCHK(lanczos_run(p, y, max_iter, tol, seed, v, o, st, restarts, ordered != 0));
+  const size_t len = (size_t)std::min<long>(max_iter, p->d.n) * sizeof(double);
+  HIPCHK(hipMemcpyAsync(tri, p->lalpha, len, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipMemcpyAsync(tri + max_iter, p->lbeta, len, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipStreamSynchronize(st));
+  out[0] = o.theta;
+  out[1] = o.resid;
+  out[2] = o.iters;
+  out[3] = o.steps;
   return ALM_BM_OK;
 }
 
