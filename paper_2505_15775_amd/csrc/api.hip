@@ -79,7 +79,7 @@ struct alm_bm_problem {
   double* ybuf = nullptr;         // m
   // Lanczos workspace
   int kmax = 0;
-  int lnb = 0;
+  int lnb = 0;                    // most blocks of a vector kernel: row stride of their partial sums
   double* Q = nullptr;
   double* lw = nullptr;
   double* lh1 = nullptr;
@@ -154,6 +154,10 @@ template <typename T> static const Cost<typename Acc<T>::type>& cost_of(const al
 template <> const Cost<double>& cost_of<double>(const alm_bm_problem* p) { return p->C64; }
 template <> const Cost<float>& cost_of<float>(const alm_bm_problem* p) { return p->C32; }
 template <> const Cost<float>& cost_of<bf16>(const alm_bm_problem* p) { return p->C32; }
+
+// Grid of the vector kernels over a handle's rows: that of the ordered sums while its
+// FP64 cost has hub rows, whose Lanczos passes always take those.
+static int vec_grid(const alm_bm_problem* p) { return vec_blocks(p->d.n, p->C64.nh > 0); }
 
 // Rows of the cost with more stored entries than this are hub rows (Cost):
 // twice the average row length (rounded up), at least 32.  On R-MAT graphs of
@@ -397,6 +401,20 @@ static int max_row_blocks(long n) {
   return (int)((nb + 7) / 8 * 8);
 }
 
+// Default grid of a handle's row kernels (its hub rows as they are now).
+static int default_blocks(const alm_bm_problem* p) {
+  const long n = p->d.n;
+  // long edge-family rows (each split over a whole wave) need more, shorter blocks to fill the chip
+  if (p->d.cons_kind == ALM_BM_CONS_TRACE_EDGES && p->adj.avg_deg >= 32.f) return std::min(1024, max_row_blocks(n));
+  const int nb = row_blocks(n);
+  // Skewed row lengths: more blocks to even out the long ones, and a count that is no
+  // power of two (R-MAT row lengths follow the bits of the row number, which would
+  // line up with the XCD a block runs on).  R-MAT 2^18, r = 16, FP64 evaluation:
+  // 157 us with 1024 blocks, 162 with 2048, 136 with 1536; at most n / 64 of them.
+  if (p->C64.skewed && nb == 1024) return (int)std::min<long>(1536, (n + 511) / 512 * 8);
+  return nb;
+}
+
 extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStream_t st, alm_bm_problem** out) {
   if (!desc || !out) return fail(ALM_BM_ERR_INVALID_ARG, "create: null desc or out");
   *out = nullptr;
@@ -563,15 +581,8 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   }
 
   // ---- workspace
-  p->nblk = row_blocks(n);
+  p->nblk = default_blocks(p);
   p->max_blocks = std::max(p->nblk, max_row_blocks(n));
-  // Skewed row lengths: more blocks to even out the long ones, and a count that is no
-  // power of two (R-MAT row lengths follow the bits of the row number, which would
-  // line up with the XCD a block runs on).  R-MAT 2^18, r = 16, FP64 evaluation:
-  // 157 us with 1024 blocks, 162 with 2048, 136 with 1536; at most n / 64 of them.
-  if (p->C64.skewed && p->nblk == 1024) p->nblk = (int)std::min<long>(1536, (n + 511) / 512 * 8);
-  // long edge-family rows (each split over a whole wave) need more, shorter blocks to fill the chip
-  if (d.cons_kind == ALM_BM_CONS_TRACE_EDGES && p->adj.avg_deg >= 32.f) p->nblk = std::min(1024, max_row_blocks(n));
   const size_t es = esize(d.precision);
   CK(dalloc_t(p, &p->part, (size_t)p->max_blocks * (NUM_P + kMaxR)));
   CK(dalloc_t(p, &p->part_c2, (size_t)p->max_blocks));
@@ -582,7 +593,7 @@ extern "C" alm_bm_status alm_bm_create(const alm_bm_problem_desc* desc, hipStrea
   CK(dalloc(p, &p->Qbuf, (size_t)n * d.r_max * (d.precision == ALM_BM_F64 ? 8 : 4)));
   CK(dalloc_t(p, &p->Av, d.m));
   CK(dalloc_t(p, &p->ybuf, d.m));
-  p->lnb = vec_blocks(n, p->C64.nh > 0);
+  p->lnb = vec_blocks(n);
   CK(dalloc_t(p, &p->part_vec, (size_t)std::max(p->lnb, dual_blocks(d.m)) * 2 + 16));
   {
     const size_t lz = d.lanczos_kmax > 0 ? (size_t)(d.lanczos_kmax + 1) * 2 * sizeof(double) : 0;
@@ -971,7 +982,7 @@ extern "C" alm_bm_status alm_bm_ws_ridge_fit(const double* X, const double* t, i
 extern "C" alm_bm_status alm_bm_set_tiles(alm_bm_problem* p, int32_t variant, int32_t row_blocks_) {
   if (!p) return fail(ALM_BM_ERR_INVALID_ARG, "set_tiles: null handle");
   if (variant < 0 || variant > 2) return fail(ALM_BM_ERR_INVALID_ARG, "set_tiles: variant must be 0..2");
-  int nb = row_blocks_ == 0 ? row_blocks(p->d.n) : row_blocks_;
+  int nb = row_blocks_ == 0 ? default_blocks(p) : row_blocks_;
   if (nb < 8 || nb % 8 != 0 || nb > p->max_blocks)
     return fail(ALM_BM_ERR_INVALID_ARG, "set_tiles: row_blocks must be a multiple of 8 in [8, " +
                                             std::to_string(p->max_blocks) + "]");
@@ -983,7 +994,10 @@ extern "C" alm_bm_status alm_bm_set_tiles(alm_bm_problem* p, int32_t variant, in
 extern "C" alm_bm_status alm_bm_set_hub_threshold(alm_bm_problem* p, int32_t min_degree, int32_t* hubs_out) {
   if (!p) return fail(ALM_BM_ERR_INVALID_ARG, "set_hub_threshold: null handle");
   if (p->tab.inst) return fail(ALM_BM_ERR_UNSUPPORTED, "set_hub_threshold: not on a batch");
-  STCHK(build_hubs(p, min_degree, false));
+  const bool default_grid = p->nblk == default_blocks(p);
+  const alm_bm_status s = build_hubs(p, min_degree, false);
+  if (default_grid) p->nblk = default_blocks(p);
+  STCHK(s);
   if (hubs_out) *hubs_out = p->hubs;
   return ALM_BM_OK;
 }
@@ -997,7 +1011,7 @@ extern "C" alm_bm_status alm_bm_autotune(alm_bm_problem* p, int32_t r, int32_t r
   HIPCHK(hipMemsetAsync(p->Rtmp, 0, (size_t)d.n * r * esize(d.precision), st));
   HIPCHK(hipMemsetAsync(p->ybuf, 0, (size_t)d.m * sizeof(double), st));
   std::vector<int> cands;
-  for (int nb : {row_blocks(d.n), 1024, 2048, 4096, 8192, 16384})
+  for (int nb : {default_blocks(p), row_blocks(d.n), 1024, 2048, 4096, 8192, 16384})
     if (nb >= 8 && nb % 8 == 0 && nb <= p->max_blocks &&
         std::find(cands.begin(), cands.end(), nb) == cands.end())
       cands.push_back(nb);
@@ -1320,7 +1334,7 @@ static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, 
   const long n = d.n;
   const long ldq = n;
   ordered = ordered || p->C64.nh > 0;
-  const int nb = ordered ? vec_blocks(n, true) : p->lnb;
+  const int nb = vec_blocks(n, ordered);
   Cost<double> C = p->C64;
   if (ordered) C.nh = p->hubs;
   kmax = std::min(kmax, p->kmax);
@@ -1492,7 +1506,7 @@ static alm_bm_status block_krylov(alm_bm_problem* p, const double* y, int q, int
                                   hipStream_t st) {
   const auto& d = p->d;
   const long n = d.n, ldq = n;
-  const int nb = p->lnb, ld = p->kmax + 1;
+  const int nb = vec_grid(p), ld = p->kmax + 1;
   kmax = std::min(kmax, p->kmax);
   const int m = (int)std::min<long>(kmax + 1, n);
   if (q < 1 || q > kMaxBlockQ) return fail(ALM_BM_ERR_INVALID_ARG, "block Lanczos: q must be in 1..8");
@@ -1791,16 +1805,17 @@ static alm_bm_status block_moments(alm_bm_problem* p, int q, const double* V, do
   const auto& d = p->d;
   const int np = q * (q + 1) / 2, ne = np * (np + 1) / 2;
   const bool edges = d.cons_kind != ALM_BM_CONS_DIAG;
-  if (edges) launch_gram4_edges(d.n_edges, d.n, q, d.edge_i, d.edge_j, V, p->gpart, p->lnb, st);
-  else launch_gram4(d.n, q, V, p->gpart, p->lnb, st);
-  std::vector<double> gp((size_t)p->lnb * ne);
+  const int nb = vec_grid(p);
+  if (edges) launch_gram4_edges(d.n_edges, d.n, q, d.edge_i, d.edge_j, V, p->gpart, nb, st);
+  else launch_gram4(d.n, q, V, p->gpart, nb, st);
+  std::vector<double> gp((size_t)nb * ne);
   HIPCHK(hipMemcpyAsync(gp.data(), p->gpart, gp.size() * sizeof(double), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   HIPCHK(hipGetLastError());
   M4.assign((size_t)np * np, 0.0);
   for (int e = 0, p1 = 0, p2 = 0; e < ne; ++e) {
     double s = 0.0;
-    for (int b = 0; b < p->lnb; ++b) s += gp[(size_t)b * ne + e];
+    for (int b = 0; b < nb; ++b) s += gp[(size_t)b * ne + e];
     M4[(size_t)p1 * np + p2] = M4[(size_t)p2 * np + p1] = (edges ? edge_w : 1.0) * s;
     if (++p2 == np) p2 = ++p1;
   }
@@ -1872,7 +1887,7 @@ static alm_bm_status block_rank_step(alm_bm_problem* p, T* R, int& r, int& w, in
   if (added == 0) return ALM_BM_OK;
   HIPCHK(hipMemcpyAsync(p->ycoef, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice, st));
   for (int j = 0; j < added; ++j) {
-    launch_combine(n, qv, p->vblk, n, p->ycoef + (long)j * qv, p->lw, p->lpart2, p->lnb, st);
+    launch_combine(n, qv, p->vblk, n, p->ycoef + (long)j * qv, p->lw, p->lpart2, vec_grid(p), st);
     if (r + 1 <= w) {
       launch_set_column<T>(n, w, r, R, p->lw, 1.0, st);
     } else {
@@ -1945,8 +1960,8 @@ static alm_bm_status solve_impl(alm_bm_problem* p, const alm_bm_options& o, T* R
       }
     } else if (o.rank_policy == ALM_BM_RANK_ADAPT && gate && lo.theta < -tau_k && r < r_cap) {
       // ||A(v v^T)||^2 for the unit Ritz vector
-      launch_quartic_norm(n, d.cons_kind == ALM_BM_CONS_DIAG ? 0 : 1, p->adj, p->lv, p->lpart2, p->lnb, st);
-      launch_fin_sum(p->lpart2, p->lnb, p->lscal + 3, 0, st);
+      launch_quartic_norm(n, d.cons_kind == ALM_BM_CONS_DIAG ? 0 : 1, p->adj, p->lv, p->lpart2, vec_grid(p), st);
+      launch_fin_sum(p->lpart2, vec_grid(p), p->lscal + 3, 0, st);
       double q4 = 0.0;
       HIPCHK(hipMemcpyAsync(&q4, p->lscal + 3, sizeof(double), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));

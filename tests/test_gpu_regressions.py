@@ -52,3 +52,45 @@ def test_batch_steps_without_a_limit():
         st, sts, res, R, ranks, y = batch.solve(factors, eps_kkt=1e-2, max_outer=2, max_inner=limit)
         ends.append((st, sts, ranks, [r["inner_total"] for r in res], R.cpu().numpy().tobytes()))
     assert ends[0] == ends[1]
+
+
+def _bits(p, R, y):
+    """Five totals of the rows (those of the line search), whose last bits follow the grid."""
+    f, G, _ = p.objective_grad(R, y, 1.3)
+    return p.line_search(R, G, y, 1.3)[0].cpu().numpy().tobytes()
+
+
+@pytest.mark.parametrize("kind", ["skewed", "skewed_f32", "dense_edges", "plain"])
+def test_default_grid_of_a_handle(kind):
+    """row_blocks = 0 gives the grid that the handle was made with (sums in the same order, so the same bits), also
+    where that depends on the row lengths; so does a change of the hub rows and back."""
+    m = _almbm()
+    rng = np.random.default_rng(3)
+    if kind == "dense_edges":
+        n = 2000
+        iu, ju = np.triu_indices(n, 1)
+        pick = np.sort(rng.choice(iu.size, size=40000, replace=False))
+        p = m.Problem.edges(n, iu[pick], ju[pick], np.zeros(40001), 0.0, cost_diag=np.full(n, 0.5), precision="f64",
+                            r_max=16, lanczos_kmax=0, device=DEV)
+    else:
+        g = gen.er_graph(70000, 200000, 3, "gauss") if kind == "plain" else gen.rmat_graph(17, 8, 5, "gauss")
+        p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f32" if kind == "skewed_f32" else "f64", r_max=16,
+                             lanczos_kmax=0, device=DEV)
+    R = p.factor(rng.standard_normal((p.n, 16)))
+    y = torch.from_numpy(rng.standard_normal(p.m)).to(DEV)
+    fresh = _bits(p, R, y)
+    p.set_tiles(0, 64)
+    p.set_tiles(0, 0)
+    assert _bits(p, R, y) == fresh
+    if kind.startswith("skewed"):
+        assert p.set_hub_threshold(-1) == 0
+        off = _bits(p, R, y)
+        p.set_tiles(0, 0)
+        assert _bits(p, R, y) == off
+        assert p.set_hub_threshold(0) > 0
+        assert _bits(p, R, y) == fresh
+        p.set_tiles(0, 64)
+        few = _bits(p, R, y)
+        p.set_hub_threshold(-1)
+        p.set_hub_threshold(0)
+        assert _bits(p, R, y) == few  # a grid that the caller chose stays
