@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import gen
+import oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +95,19 @@ def test_default_grid_of_a_handle(kind):
         p.set_hub_threshold(-1)
         p.set_hub_threshold(0)
         assert _bits(p, R, y) == few  # a grid that the caller chose stays
+
+
+@pytest.mark.parametrize("n", [511, 513, 8191, 70001, 262145, 300001])
+def test_product_on_either_grid(n):
+    """C X with and without <X, C X>: the same rows on both grids (sizes around 64 rows a block, 1024 blocks and
+    4096), against the oracle.  Sums of a few products in FP64: 1e-13 of the largest."""
+    m = _almbm()
+    g = gen.er_graph(n, 3 * n, 3, "gauss")
+    p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=5, lanczos_kmax=0, device=DEV)
+    X = np.random.default_rng(n).standard_normal((n, 5))
+    P_o = oracle.cost_apply(oracle.maxcut_sdp(g), X)
+    P = p.cost_apply(p.factor(X)).cpu().numpy()
+    Q, xpx = p.cost_apply(p.factor(X), want_xpx=True)
+    assert np.abs(P - P_o).max() <= 1e-13 * np.abs(P_o).max()
+    assert P.tobytes() == Q.cpu().numpy().tobytes()
+    assert abs(xpx.item() - (X * P_o).sum()) <= 1e-12 * np.abs(X * P_o).sum()
