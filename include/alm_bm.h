@@ -479,8 +479,9 @@ alm_bm_status alm_bm_kkt(alm_bm_problem* prob, int32_t r, const void* R, const d
  * W2[h][h], b2[h], W3[h], b3 (alm_bm_ws_param_count floats).  h in {16,32,64},
  * n_in <= 8.                                                                    */
 #define ALM_BM_WS_NFEAT 8
-/* feats: device n x 8 float (row-major); scratch: device n floats.  Handle must
- * be DIAG family; its own workspace is used as well, as by its other calls.     */
+/* feats: device n x 8 float (row-major); scratch: not null, not used (the
+ * handle keeps a buffer for this call alone, so that it may overlap with the
+ * handle's other calls).  Handle must be DIAG family.                            */
 alm_bm_status alm_bm_ws_features(alm_bm_problem* prob, float* feats, float* scratch, hipStream_t stream);
 /* out[k] = mean over rows of feats[:, k] (device 8 doubles); n rows; work:
  * device 512 doubles.                                                           */

@@ -9,7 +9,6 @@
 namespace almbm {
 
 constexpr int kWsFeat = 8;    // features per vertex
-constexpr int kWsMaxH = 64;   // largest hidden width
 
 // Features of vertex i (row i of the cost):
 //   f0 = log1p(deg_i), f1 = sum_j |S_ij|, f2 = sum_j S_ij, f3 = d_i,

@@ -39,8 +39,7 @@ RANK_CHOICES = (4, 8, 16, 32)
 def features(prob):
     """n x 8 float features of the handle's cost (device tensor)."""
     F = torch.empty((prob.n, NFEAT), dtype=torch.float32, device=prob.device)
-    scratch = torch.empty(prob.n, dtype=torch.float32, device=prob.device)
-    check(lib.alm_bm_ws_features(prob._h, _ptr(F), _ptr(scratch), _stream()), "ws_features")
+    check(lib.alm_bm_ws_features(prob._h, _ptr(F), _ptr(F), _stream()), "ws_features")  # no scratch is used
     return F
 
 

@@ -111,3 +111,32 @@ def test_product_on_either_grid(n):
     assert np.abs(P - P_o).max() <= 1e-13 * np.abs(P_o).max()
     assert P.tobytes() == Q.cpu().numpy().tobytes()
     assert abs(xpx.item() - (X * P_o).sum()) <= 1e-12 * np.abs(X * P_o).sum()
+
+
+def test_features_beside_the_handles_other_calls():
+    """The feature pass shares no workspace with the handle's other calls: on two streams at once, both give what
+    they give alone, bit for bit."""
+    from paper_2505_15775_amd import warmstart
+
+    m = _almbm()
+    g = gen.er_graph(300000, 1500000, 3, "gauss")
+    p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=8, lanczos_kmax=0, device=DEV)
+    R0 = p.factor(np.random.default_rng(1).standard_normal((g.n, 8)) / 3)
+    y = torch.zeros(g.n, dtype=torch.float64, device=DEV)
+    F0, steps = warmstart.features(p), 20
+    R1 = R0.clone()
+    for _ in range(steps):
+        p.gd_step(R1, y, 1.0)
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(4):
+        R = R0.clone()
+        torch.cuda.synchronize()
+        Fs = []
+        for k in range(steps):
+            p.gd_step(R, y, 1.0, stream=s2)
+            with torch.cuda.stream(s1):
+                Fs += [warmstart.features(p), warmstart.features(p)]
+        torch.cuda.synchronize()
+        assert torch.equal(R, R1)
+        assert all(torch.equal(F, F0) for F in Fs)
