@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cfloat>
 #include <chrono>
 #include <cmath>
@@ -11,11 +10,11 @@
 #include <cstring>
 #include <map>
 #include <string>
-#include <thread>
 #include <vector>
 
 #include "alm_bm.h"
 #include "api_internal.hpp"
+#include "host_parallel.hpp"
 #include "launch.hpp"
 
 using namespace almbm;
@@ -2484,24 +2483,6 @@ extern "C" alm_bm_status alm_bm_batch_create(int32_t count, const alm_bm_problem
 
 namespace {
 
-// f(0), ..., f(count - 1), each once, over up to eight threads (one per four
-// calls).  f must not throw and its calls must not share what they write.
-template <typename F> void host_parallel(int count, F&& f) {
-  const int nt = std::min({8, (int)std::thread::hardware_concurrency(), count / 4});
-  std::atomic<int> next{0};
-  auto work = [&]() {
-    for (int t = next++; t < count; t = next++) f(t);
-  };
-  std::vector<std::thread> pool;
-  try {
-    for (int t = 1; t < nt; ++t) pool.emplace_back(work);
-  } catch (...) {
-    // fewer threads then: the caller's own takes what is left
-  }
-  work();
-  for (std::thread& t : pool) t.join();
-}
-
 struct BatchLanczos {
   std::vector<double> theta, resid;
   std::vector<int> m;
@@ -2635,7 +2616,7 @@ static alm_bm_status batch_lanczos_pass(alm_bm_batch* b, const double* y, int km
       for (int q = 0; q < count; ++q)
         if (!done[q]) todo.push_back(q);
       std::vector<char> ends(count, 0), bad(count, 0);
-      host_parallel((int)todo.size(), [&](int t) {
+      const bool ran = host_parallel((int)todo.size(), [&](int t) {
         const int q = todo[t];
         const std::vector<double> a(ha.begin() + (long)q * kp, ha.begin() + (long)q * kp + j + 1);
         const std::vector<double> bt(hb.begin() + (long)q * kp, hb.begin() + (long)q * kp + j + 1);
@@ -2661,6 +2642,7 @@ static alm_bm_status batch_lanczos_pass(alm_bm_batch* b, const double* y, int km
         const double est = breakdown ? 0.0 : std::fabs(bt[mm - 1] * z[q][mm - 1]);
         ends[q] = breakdown || est <= tol[q] || mm >= b->kmax[q] || mm >= (int)(b->off[q + 1] - b->off[q]);
       });
+      if (!ran) return fail(ALM_BM_ERR_OOM, "batch lanczos: host memory");
       bool dropped = false;
       for (int q : todo) {
         if (bad[q]) return fail(ALM_BM_ERR_NUMERIC, "batch lanczos: NaN/Inf");
