@@ -140,3 +140,13 @@ def test_features_beside_the_handles_other_calls():
         torch.cuda.synchronize()
         assert torch.equal(R, R1)
         assert all(torch.equal(F, F0) for F in Fs)
+
+
+def test_stream_of_a_call():
+    """The raw handle that calls get is the one of the current stream, or of the stream given."""
+    m = _almbm()
+    side = torch.cuda.Stream()
+    assert m._stream() == torch.cuda.current_stream().cuda_stream
+    assert m._stream(side) == side.cuda_stream
+    with torch.cuda.stream(side):
+        assert m._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
