@@ -694,12 +694,21 @@ static void enqueue_objgrad(alm_bm_problem* p, int r, const T* R, const double* 
   }
 }
 
-// Grids up to which an inner step's totals are left to a block of its next pass.
-// The pass that finds the subproblem converged then runs for nothing, once, which
-// large problems pay more for than a launch a step saves: 20 steps at n = 1000,
-// r = 5, FP64 474 -> 423 us, at n = 20000, r = 16, BF16 535 -> 463 us, but n = 1e7,
-// r = 16, BF16 one product (1.8 ms) a subproblem for 5 us of each 2.3 ms step.
+// Grids up to which an inner step's totals are left to a block of its next pass, which
+// saves the finalizer's launch but lets the product that follows a converged gradient
+// run for nothing, once a subproblem.  Per step, at degree 8: n = 2e4, r = 16, FP64 28.2
+// -> 24.6 us, BF16 24.8 -> 21.1; beyond the line n = 4e4, r = 4, FP64 26.5 -> 23.0, n =
+// 1.5e5, r = 16 62.9 -> 58.4, n = 1e6, r = 16 351 -> 346, against products of about 7, 35
+// and 200 us: the block would pay there from 2, 8 and 40 steps a subproblem on, and at n
+// = 1e7, r = 16, BF16 (1.8 ms) from 360.
 constexpr int kSideFinBlocks = 512;
+
+// The same for the totals of an L-BFGS direction, whose pass is never for nothing.  The
+// block is the grid's last and has a quarter of a finalizer's threads: up to 2048 blocks
+// it runs beside the others, beyond, it starts after most of them.  n = 7e4, r = 4,
+// FP64 per step: 63.4 -> 59.8 us with 1024 blocks, 65.2 -> 65.1 with 2048, 82.1 -> 84.6
+// with 4096, 116 -> 124 with 8192.
+constexpr int kSideDirBlocks = 2048;
 
 // One inner gradient step (flag-guarded, decisions taken on the device):
 // DIAG family: apply the pending step and evaluate the new gradient from the
@@ -737,7 +746,8 @@ static void enqueue_inner_step(alm_bm_problem* p, int r, T* R, const double* y, 
           launch_lbfgs_dots<T>((long)d.n * r, r, p->lb_m, G, lb, dots, p->nblk, sc, st, BlockTab{}, objgrad);
       launch_fin_lbfgs(dots, nbd, p->lb_m, sc, lb.s, st);
       launch_lbfgs_combine<T>(d.n, r, p->variant, R, G, y, d.b, sigma, p->Av, lb, p->part, sc, p->nblk, st);
-      lsdir = {p->part, p->nblk, sc, sigma, lb.s};
+      if (p->nblk <= kSideDirBlocks) lsdir = {p->part, p->nblk, sc, sigma, lb.s};
+      else launch_fin_lsdir(p->part, p->nblk, sc, lb.s, st);
       launch_quadq_diag<S>(cost_of<S>(p), r, p->variant, lb.e, Q, p->part_c2, sc, p->tab, p->nblk, st, lb, lsdir);
     } else {
       launch_quadq_diag<T>(cost_of<T>(p), r, p->variant, G, Q, p->part_c2, sc, p->tab, p->nblk, st, {}, objgrad);

@@ -566,6 +566,20 @@ static void p3_cfg(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, int r
                        part, sc, rho, side);
 }
 
+// Whether a block of pass 3 adds the totals of passes 1 and 2 (len doubles of partial
+// sums; bytes: one gathered row per edge).  It saves a launch and the finalizer's own
+// time if pass 3 lasts as long as the block, which has a quarter of a finalizer's
+// threads, takes some 0.35 ns a double and starts last: with more than 2048 blocks after
+// most of them.  Per step, kernel -> block: completion n = 1000 and 2e4, r = 3, FP64
+// (len 2e3, 7e3) 32.6 -> 29.1 and 122 -> 116 us; with a -J term n = 1e5, E = 2e5, r = 32,
+// FP32 (3.7e4) 99.6 -> 97.0, n = 5e4, E = 2e5, r = 100, FP32 (8.2e4 and 8e7 bytes) 201 ->
+// 184, but n = 1e5, E = 2e5, r = 64, BF16 (7.0e4, 2.6e7) 124 -> 129, n = 7e4, E = 1e5, r =
+// 100, BF16 (1.1e5, 2.1e7) 200 -> 210; on chosen grids n = 1e5, E = 1e6, r = 32, FP32 198
+// -> 193 with 2048 blocks, 212 -> 219 with 4096.
+static bool side_edges12(long len, int nblk, double bytes) {
+  return nblk <= 2048 && (len <= 40000 || bytes >= 512.0 * (double)len);
+}
+
 template <typename T>
 void launch_edges_eval(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, long n, int r, int variant, const T* R,
                        const double* y, const double* b, double sigma, double c_tr, double j_coef, double rho,
@@ -583,7 +597,7 @@ void launch_edges_eval(const Cost<typename Acc<T>::type>& C, const EdgeAdj& A, l
   fin.part1 = wait ? nullptr : part;
   fin.part2 = part2;
   fin.f_out = f_out;
-  if (defer)
+  if (defer && side_edges12((long)nblk * (E2_N + ncs + (wait ? 0 : E1_N)), nblk, (double)A.E * r * sizeof(T)))
     *defer = fin;
   else
     hipLaunchKernelGGL(k_fin_edges12, dim3(1), dim3(kFin), 0, st, fin);

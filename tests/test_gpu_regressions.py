@@ -150,3 +150,40 @@ def test_stream_of_a_call():
     assert m._stream(side) == side.cuda_stream
     with torch.cuda.stream(side):
         assert m._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("blocks", [368, 504])
+def test_edge_totals_in_a_block_or_a_kernel(blocks):
+    """A long table of partial sums (104 a block) is added by a kernel, a shorter one by a block of the line-search
+    pass: either way the steps are those of the single calls.  Four FP64 steps: 1e-10 as for the other edge steps."""
+    rng = np.random.default_rng(blocks)
+    n, r = 4000, 100
+    g = gen.er_graph(n, 9000, 3)
+    p = _almbm().Problem.edges(n, g.ei, g.ej, rng.standard_normal(9001), 1.5, j_coef=0.5,
+                               cost_diag=rng.standard_normal(n), precision="f64", r_max=r, lanczos_kmax=0, device=DEV)
+    p.set_tiles(0, blocks)
+    R0, y = rng.standard_normal((n, r)) / 10, torch.from_numpy(rng.standard_normal(9001)).to(DEV)
+    R, S = p.factor(R0), p.factor(R0)
+    assert p.inner_solve(R, y, 0.0, 4, sigma=1.3)[:2] == (4, 2)
+    for _ in range(4):
+        _, G, _ = p.objective_grad(S, y, 1.3)
+        S = S - p.line_search(S, G, y, 1.3)[1] * G
+    assert (R - S).norm() <= 1e-10 * S.norm()
+
+
+@pytest.mark.parametrize("blocks", [2048, 2056])
+def test_direction_totals_in_a_block_or_a_kernel(blocks):
+    """L-BFGS steps on both sides of the grid up to which a block of the product adds the direction's totals, against
+    the default grid: other sums, the same path to 1e-9 over eight FP64 steps."""
+    m = _almbm()
+    g = gen.er_graph(17000, 60000, 5, "gauss")
+    ends = []
+    for nb in (0, blocks):
+        p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=8, lanczos_kmax=0, lbfgs_memory_max=3,
+                             device=DEV)
+        p.set_tiles(0, nb)
+        R = p.factor(np.random.default_rng(7).standard_normal((g.n, 8)) / 3)
+        y = torch.zeros(g.n, dtype=torch.float64, device=DEV)
+        ends.append(p.inner_solve(R, y, 0.0, 8, sigma=1.0, inner_solver=m._lib.INNER_LBFGS, lbfgs_memory=3))
+    assert ends[0][:2] == ends[1][:2] == (8, 2)
+    assert abs(ends[0][2] - ends[1][2]) <= 1e-9 * abs(ends[0][2])
