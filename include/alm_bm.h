@@ -49,9 +49,7 @@
  *   - The handle owns its workspace, allocated in alm_bm_create and sized by the
  *     descriptor (r_max, lanczos_kmax, rank_block_max, lbfgs_memory_max,
  *     hub_min_degree; BF16 handles also reserve the float factor of the
- *     precision ladder).  No other call allocates device memory, except that
- *     alm_bm_batch_solve instantiates HIP graphs of its inner loop
- *     (runtime-owned).
+ *     precision ladder).  No other call allocates device memory.
  */
 #ifndef ALM_BM_H
 #define ALM_BM_H
@@ -149,8 +147,7 @@ typedef struct {
   double lanczos_tol_rel;    /* 0.1    Ritz residual <= 0.1 eps (1 + ||C||_F)         */
   uint64_t seed;             /* 1      Lanczos start vector                            */
   int32_t graph_unroll;      /* 8      inner iterations enqueued between two looks at the
-                                stop flag (0: one); batched solves replay a captured
-                                HIP graph of that many once a running set lasts   */
+                                stop flag (0: one)                                */
   int32_t verbose;           /* 0      1: one line per outer iteration on stderr      */
   double time_limit_s;       /* 0      > 0: stop (NOT_CONVERGED) after this wall time  */
   int32_t bf16_promote;      /* 1      BF16 handle: ladder to float storage when stalled */
@@ -408,8 +405,7 @@ alm_bm_status alm_bm_autotune(alm_bm_problem* prob, int32_t r, int32_t reps, int
  * Many independent problems (DIAG family, one storage precision) solved
  * together: the instances are concatenated block-diagonally on the device and
  * each launch of the method covers every instance still running (per-instance
- * step sizes, tolerances, stop flags, duals, Lanczos recurrences and ranks; the
- * inner loop of all instances is one captured HIP graph per chunk of steps).
+ * step sizes, tolerances, stop flags, duals, Lanczos recurrences and ranks).
  * At the interface the factors share one row width, rank_stride: instance q's
  * rows sit at rows [off_q, off_q + n_q) of one (sum n) x rank_stride array, its
  * first r_q columns used and the rest zero (zero columns stay exactly zero

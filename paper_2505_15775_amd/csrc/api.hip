@@ -409,8 +409,11 @@ static int default_blocks(const alm_bm_problem* p) {
   const int nb = row_blocks(n);
   // Skewed row lengths: more blocks to even out the long ones, and a count that is no
   // power of two (R-MAT row lengths follow the bits of the row number, which would
-  // line up with the XCD a block runs on).  R-MAT 2^18, r = 16, FP64 evaluation:
-  // 157 us with 1024 blocks, 162 with 2048, 136 with 1536; at most n / 64 of them.
+  // line up with the XCD a block runs on); at most n / 64 of them.  R-MAT, degree 16,
+  // evaluation with 1024 / 1536 / 2048 blocks: r = 16, FP64 2^17 88 / 82 / 91 us, 2^18
+  // 159 / 137 / 164, 2^19 279 / 240 / 278, 2^21 1316 / 1066 / 1300; 2^18 r = 4 100 / 86 /
+  // 102, r = 64 449 / 421 / 446, r = 16, FP32 92 / 80 / 92, r = 32, BF16 102 / 94 / 102
+  // (2^17, r = 32, BF16 58 in each).
   if (p->C64.skewed && nb == 1024) return (int)std::min<long>(1536, (n + 511) / 512 * 8);
   return nb;
 }
@@ -1735,22 +1738,6 @@ extern "C" alm_bm_status alm_bm_kkt(alm_bm_problem* p, int32_t r, const void* R,
 
 namespace {
 
-// The captured step of a batched solve, made after kBatchPlainChunks runs of
-// plain launches with the same running set and widths (the two take the same
-// time; the plain ones cost no capture).
-constexpr int kBatchPlainChunks = 4;
-struct GraphCache {
-  hipGraphExec_t exec = nullptr;
-  hipGraph_t graph = nullptr;
-  void reset() {
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
-    exec = nullptr;
-    graph = nullptr;
-  }
-  ~GraphCache() { reset(); }
-};
-
 double now_s() {
   return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
 }
@@ -2795,11 +2782,10 @@ static BlockTab batch_class_tab(const alm_bm_batch* b, int c) {
 
 // One inner step of every running instance: each row kernel once per width.
 // step: its number from the start of the subproblem, which leaves out the pass
-// that would do nothing in it; -1: any step (the captured graph), every pass
-// deciding on the device.
+// that would do nothing in it.
 template <typename T>
 static void batch_enqueue_step(alm_bm_batch* b, T* R, const double* y, double sigma, T* G, int refresh,
-                               hipStream_t st, int step = -1) {
+                               hipStream_t st, int step) {
   using V = typename Acc<T>::type;
   alm_bm_problem* p = b->p;
   const auto& d = p->d;
@@ -2810,7 +2796,7 @@ static void batch_enqueue_step(alm_bm_batch* b, T* R, const double* y, double si
   for (int c = 0; c < b->nclass && step != 0; ++c)
     launch_upd_eval_diag<T>(d.n, b->c_w[c], b->c_var[c], R, G, Q, y, d.b, sigma, p->Av, p->part, sc, refresh,
                             batch_class_tab(b, c), b->c_nb[c], st, lb);
-  const bool full = step < 0 || refresh <= 1 || step % refresh == 0;
+  const bool full = refresh <= 1 || step % refresh == 0;
   for (int c = 0; c < b->nclass && full; ++c)
     launch_objgrad_diag<T>(cost_of<T>(p), b->c_w[c], b->c_var[c], R, y, d.b, sigma, G, p->Av, p->part, sc, refresh,
                            batch_class_tab(b, c), b->c_nb[c], st, lb);
@@ -2884,12 +2870,10 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
     xb[q] = batch_xbase(b, q, w[q]);
   }
   STCHK(batch_restride<T>(b, R, zero64, rsv, xb, wv, r, st));
-  GraphCache gc;
-  // The launch tables and the captured step depend only on the widths and the
-  // running set: both are rebuilt when either changed since they were made.
-  std::vector<int> tab_w, gr_w;
-  std::vector<int32_t> tab_active, gr_active;
-  int captures = 0, chunks = 0;
+  // The launch tables depend only on the widths and the running set: rebuilt when
+  // either changed since they were made.
+  std::vector<int> tab_w;
+  std::vector<int32_t> tab_active;
   std::vector<int32_t> fl(2 * count);
   int nactive = count;
   for (int k = 0; k < o.max_outer && nactive > 0; ++k) {
@@ -2898,18 +2882,12 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
       tolv[q] = std::max(o.eps_kkt / 10.0, std::min(o.inner_tol_scale, std::min(pinf_prev[q], o.inner_tol_decay * tol_prev[q])));
       tol_prev[q] = tolv[q];
     }
-    // launch tables of this outer iteration's running instances, and the graph
+    // launch tables of this outer iteration's running instances
     const double ti = now_s();
     if (w != tab_w || active != tab_active) {
       STCHK(batch_classes(b, w, active, st));
       tab_w = w;
       tab_active = active;
-    }
-    if (w != gr_w || active != gr_active) {
-      gc.reset();
-      gr_w = w;
-      gr_active = active;
-      chunks = 0;
     }
     HIPCHK(hipMemcpyAsync(b->tols_dev, tolv.data(), count * sizeof(double), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b->active_dev, active.data(), count * sizeof(int32_t), hipMemcpyHostToDevice, st));
@@ -2918,24 +2896,14 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
     if (p->lb_m > 0) launch_lbfgs_reset(p->lbs, p->lb_m, st, count);  // empty memories
     long launched = 0;
     while (true) {
-      // A running set and its widths first take plain launches (which know the
-      // step's number); a set that lasts is worth the capture of its step.
+      // Plain launches, which know the step's number: a captured graph of a chunk was
+      // slower for 4 to 256 instances of up to 4e4 rows and 40 to 400 steps (24 instances
+      // of up to 4e4 rows, 200 steps: 61.6 against 59.4 ms; 64 of up to 2e4, L-BFGS: 42.4
+      // against 40.4), and needs a new capture whenever the running set or a width changes.
       const int steps = (int)std::min<long>(U, (long)o.max_inner + 1 - launched);
       if (steps <= 0) return fail(ALM_BM_ERR_HIP, "batch inner loop did not reach its stop flags");
-      if (steps < U || chunks < kBatchPlainChunks) {
-        for (int u = 0; u < steps; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st, launched + u);
-      } else {
-        if (!gc.exec) {
-          HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-          for (int u = 0; u < U; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st);
-          HIPCHK(hipStreamEndCapture(st, &gc.graph));
-          HIPCHK(hipGraphInstantiate(&gc.exec, gc.graph, nullptr, nullptr, 0));
-          ++captures;
-        }
-        HIPCHK(hipGraphLaunch(gc.exec, st));
-      }
+      for (int u = 0; u < steps; ++u) batch_enqueue_step<T>(b, R, y, sigma, G, refresh, st, launched + u);
       launched += steps;
-      ++chunks;
       launch_gather_flags(p->sc_solve, count, b->flags_dev, st);
       HIPCHK(hipMemcpyAsync(fl.data(), b->flags_dev, 2 * count * sizeof(int32_t), hipMemcpyDeviceToHost, st));
       HIPCHK(hipStreamSynchronize(st));
@@ -3083,9 +3051,8 @@ static alm_bm_status batch_solve_impl(alm_bm_batch* b, const alm_bm_options& o, 
     }
     if (o.verbose)
       std::fprintf(stderr,
-                   "[almbm batch] k=%d active=%d t=%.2fs (inner %.3fs, %ld graph launches, %d captures; "
-                   "lanczos %.3fs)\n",
-                   k, nactive, now_s() - t0, tinner, launched / U, captures, tlan + tlan2);
+                   "[almbm batch] k=%d active=%d t=%.2fs (inner %.3fs, %ld steps enqueued; lanczos %.3fs)\n",
+                   k, nactive, now_s() - t0, tinner, launched, tlan + tlan2);
     if (o.time_limit_s > 0.0 && now_s() - t0 > o.time_limit_s) break;
   }
   // back to the caller's layout
