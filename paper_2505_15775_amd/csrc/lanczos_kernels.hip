@@ -58,15 +58,14 @@ __device__ __forceinline__ void load_coef(const LzCoef& hc, int inst, int ncol, 
   __syncthreads();
 }
 
-// SUB: w -= Q h.  DOTS: per-block partial sums of q_c . w (after SUB) into part;
-// otherwise of ||w||^2 and sum w into part[slot], part[pld + slot].  A thread
+// Per-block partial sums of q_c . w into part; SUB: of the w left by w -= Q h.  A thread
 // owns a row and holds its entries of all ncol <= NC columns at once, so a wave
 // has ncol 512-byte loads in flight; the columns' dots are summed over the wave
 // by halving, which leaves column l / (64 / NC) in lane l.  Bound by HBM: over a
-// 56-column pass at n = 1e6 the dots run at 5.2 TB/s and SUB with DOTS at 4.7
+// 56-column pass at n = 1e6 the dots run at 5.2 TB/s and with SUB at 4.7
 // TB/s, where column-per-wave dots and row-per-thread subtraction on 248 blocks
 // ran at 3.0 and 3.5 TB/s and read the basis once more.
-template <int NC, bool SUB, bool DOTS>
+template <int NC, bool SUB>
 __global__ void __launch_bounds__(kBlock)
 k_lz_proj(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef hc, double* __restrict__ w,
           double* __restrict__ part, int pld, BlockTab tab) {
@@ -74,7 +73,7 @@ k_lz_proj(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef hc, d
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   __shared__ double hs[SUB ? NC : 1];
   if constexpr (SUB) load_coef(hc, ch.inst, ncol, hs);
-  double acc = 0.0, nrm = 0.0, sum = 0.0;
+  double acc = 0.0;
   for (long base = ch.lo; base < ch.hi; base += kBlock) {
     const long i = base + threadIdx.x;
     const bool in = i < ch.hi;
@@ -103,38 +102,26 @@ k_lz_proj(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef hc, d
       if (in) w[i] = v;
       if (!in) v = 0.0;
     }
-    if constexpr (DOTS) {
 #pragma unroll
-      for (int c = 0; c < NC; ++c) q[c] *= v;
-      acc += wave_sum_many<NC>(q, lane);
-    } else {
-      nrm += v * v;
-      sum += v;
-    }
+    for (int c = 0; c < NC; ++c) q[c] *= v;
+    acc += wave_sum_many<NC>(q, lane);
   }
-  if constexpr (DOTS) {
-    __shared__ double red[kBlock / kWave][NC];
-    constexpr int W = kWave / NC;
-    if (lane % W == 0) red[wave][lane / W] = acc;
-    __syncthreads();
-    for (int c = threadIdx.x; c < ncol; c += kBlock) {
-      double t = 0.0;
+  __shared__ double red[kBlock / kWave][NC];
+  constexpr int W = kWave / NC;
+  if (lane % W == 0) red[wave][lane / W] = acc;
+  __syncthreads();
+  for (int c = threadIdx.x; c < ncol; c += kBlock) {
+    double t = 0.0;
 #pragma unroll
-      for (int k = 0; k < kBlock / kWave; ++k) t += red[k][c];
-      part[(long)c * pld + part_slot(tab)] = t;
-    }
-  } else {
-    double two[2] = {nrm, sum};
-    __shared__ double out[2];
-    block_sum_store<2>(two, out);
-    __syncthreads();
-    if (threadIdx.x < 2) part[(long)threadIdx.x * pld + part_slot(tab)] = out[threadIdx.x];
+    for (int k = 0; k < kBlock / kWave; ++k) t += red[k][c];
+    part[(long)c * pld + part_slot(tab)] = t;
   }
 }
 
-// The same for more than 64 columns: the columns go by in chunks of CH, and
-// SUB + DOTS reads them twice (the second time the block's tile is in L2 or the
-// Infinity Cache).
+// The same for more than 64 columns (DOTS), and for any number without the dots, with
+// partial sums of ||w||^2 and of w in part[slot] and part[pld + slot] instead: the
+// columns go by in chunks of CH, and SUB + DOTS reads them twice (the second time the
+// block's tile is in L2 or the Infinity Cache).
 template <bool SUB, bool DOTS>
 __global__ void __launch_bounds__(kBlock)
 k_lz_proj_wide(long n, int ncol, const double* __restrict__ Q, long ldq, LzCoef hc, double* __restrict__ w,
@@ -741,13 +728,13 @@ static void launch_proj(long n, int ncol, const double* Q, long ldq, const LzCoe
                         int pld, int nb, hipStream_t st, const BlockTab& tab) {
 #define ALMBM_PROJ(K) hipLaunchKernelGGL((K), dim3(nb), dim3(kBlock), 0, st, n, ncol, Q, ldq, hc, w, part, pld, tab)
   if constexpr (!DOTS) {  // nothing to keep from the subtraction
-    ALMBM_PROJ((k_lz_proj_wide<SUB, DOTS>));
-    return;
+    ALMBM_PROJ((k_lz_proj_wide<SUB, false>));
+  } else {
+    if (ncol <= 16) ALMBM_PROJ((k_lz_proj<16, SUB>));
+    else if (ncol <= 32) ALMBM_PROJ((k_lz_proj<32, SUB>));
+    else if (ncol <= 64) ALMBM_PROJ((k_lz_proj<64, SUB>));
+    else ALMBM_PROJ((k_lz_proj_wide<SUB, true>));
   }
-  if (ncol <= 16) ALMBM_PROJ((k_lz_proj<16, SUB, DOTS>));
-  else if (ncol <= 32) ALMBM_PROJ((k_lz_proj<32, SUB, DOTS>));
-  else if (ncol <= 64) ALMBM_PROJ((k_lz_proj<64, SUB, DOTS>));
-  else ALMBM_PROJ((k_lz_proj_wide<SUB, DOTS>));
 #undef ALMBM_PROJ
 }
 
