@@ -360,7 +360,10 @@ alm_bm_status alm_bm_set_tiles(alm_bm_problem* prob, int32_t variant, int32_t ro
  * product C X a kernel with one workgroup per hub sums that row's neighbour
  * rows with all of the workgroup's lanes, and the row kernels read the sum
  * instead of walking the row with one lane group.  min_degree: 0 = the
- * default (twice the average row length rounded up, at least 32), > 0 = that
+ * default (twice the average row length rounded up, at least 32; where that
+ * finds only the tail of a Poisson degree distribution, under 1 % of the
+ * entries and no row over four times the threshold, the FP64 products walk
+ * those rows, which hubs still counts, without the kernel), > 0 = that
  * threshold, < 0 = no hubs.  alm_bm_create applies desc.hub_min_degree and
  * reserves the hub list and sums (2 x hubs x r_max values per precision kept)
  * for exactly the hubs of that threshold; this call rewrites them in place

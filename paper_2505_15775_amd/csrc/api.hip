@@ -162,7 +162,8 @@ static int vec_grid(const alm_bm_problem* p) { return vec_blocks(p->d.n, p->C64.
 // Rows of the cost with more stored entries than this are hub rows (Cost):
 // twice the average row length (rounded up), at least 32.  On R-MAT graphs of
 // 2^20 and 2^22 vertices this was within a few per cent of the best
-// threshold of a sweep from 16 to 256 entries; Poisson-degree graphs get none.
+// threshold of a sweep from 16 to 256 entries; Poisson-degree graphs get none, or the few
+// rows of their tail (build_hubs).
 static int32_t hub_threshold(long nnz, long n) {
   const long avg = (nnz + n - 1) / std::max<long>(1, n);
   return (int32_t)std::min<long>(INT32_MAX, std::max<long>(32, 2 * avg));
@@ -215,7 +216,10 @@ static alm_bm_status build_hubs(alm_bm_problem* p, int32_t min_degree, bool rese
   // The default threshold also catches the few longest rows of a Poisson degree
   // distribution (n = 193 176, average 18: rows of 37..45 entries).  Walking
   // those with one lane group costs less than a launch before every product
-  // (5 us of a 235 us L-BFGS step, twice); FP64 products then have no hubs.
+  // (5 us of a 235 us L-BFGS step, twice); FP64 products then have no hubs.  Float and
+  // BF16 handles keep them and that cost (r = 16, a gradient-descent step with / without:
+  // n = 2e4 26 / 22 us, n = 193 176 92 / 88, BF16 86 / 81, n = 1e6 463 / 458): the float
+  // sums of those rows keep their order, which BF16 paths follow to every rounding.
   const bool few = min_degree == 0 && 100 * hub_nnz < d.nnz && longest <= 4L * thr;
   p->C64.nh = few ? 0 : (int32_t)nh;
   if (d.precision != ALM_BM_F64) {
@@ -1350,10 +1354,13 @@ struct LanczosOut {
 
 // Lanczos on Z(y) with two classical Gram-Schmidt passes per step; the Ritz
 // vector for the smallest Ritz value goes to v (device, n).
-// ordered: every sum over a grid of the row count alone, the hub rows of the
-// default threshold included.  A pass that restarts from a Ritz vector, and a power-law
-// cost in its first, magnify the rounding of their sums by 1e6 and more, so where
-// the vector itself is the result its sums keep one order, whatever the kernels.
+// ordered: every sum over a grid of the row count alone, the products with the hub rows
+// of the current threshold (those of a Poisson tail too).  A pass that restarts from a
+// Ritz vector, and a power-law cost in its first, magnify the rounding of their sums by
+// 1e6 and more, so where the vector itself is the result its sums keep one order.  A
+// solve's passes, whose Ritz pair only decides on a rank step and the KKT measure, take
+// the faster order for costs without hubs, so that the two give the same eigenpair to
+// its residual and not the same bits.
 static alm_bm_status lanczos_pass(alm_bm_problem* p, const double* y, int kmax, double tol, uint64_t seed,
                                   bool restart, bool ordered, double* v, LanczosOut& out, hipStream_t st) {
   const auto& d = p->d;

@@ -11,8 +11,8 @@ namespace almbm {
 // returns s.
 alm_bm_status set_error(alm_bm_status s, const std::string& msg);
 
-// Default grid of the row kernels for n rows: one block per 64 rows, at least
-// 8 and at most 1024 blocks, a multiple of 8 (one share per XCD).
+// Default grid of the row kernels for n rows: one block per 16 rows up to 512 blocks,
+// beyond that one per 64 rows up to 1024; at least 8, a multiple of 8 (one share per XCD).
 int row_blocks(long n);
 
 }  // namespace almbm

@@ -95,7 +95,7 @@ template <int U, int LPR> struct EdgeLanes {
 // Bound by the gathers of R_j (and, at small r, by the 44 bytes of edge data).
 // Lovasz n = 1e5, 1e6 edges, r = 32, FP32: 90 us walking rows, 40 us here
 // (25e9 rows/s); completion n = 2e4, 1.8e6 edges, r = 3, FP64: 69 us with 4
-// lanes per edge and half of the rows idle, 24 us (3.3 TB/s) here.
+// lanes per edge and half of the rows idle, 20 us (3.9 TB/s) here.
 template <typename T, int LPR, int VEC, bool FULL>
 __global__ void __launch_bounds__(kBlock)
 k_edges_p1(EdgeAdj A, long n, int r, const T* __restrict__ R, const double* __restrict__ y,

@@ -471,8 +471,8 @@ void launch_lbfgs_reset(LbfgsState* s, int m, hipStream_t st, int count) {
 }
 
 // Without a table: one virtual block per 64 rows, up to 4096, on blocks of at
-// least four vector chunks per thread and at most eight blocks per CU, so that
-// the block sums and the finalizer's rows stay few.
+// least four vector chunks per thread and at most nb of them (the row kernels' grid, 1024
+// by default), so that the block sums and the finalizer's rows stay few.
 template <typename T>
 int launch_lbfgs_dots(long len, int r, int m, const T* G, const LbfgsRing<RingT<T>>& lb, double* part, int nb,
                       const DevScalars* sc, hipStream_t st, const BlockTab& tab, const SideFin& side) {

@@ -30,7 +30,8 @@ k_fin_objgrad(const double* __restrict__ part, int nb, DevScalars* __restrict__ 
 // Step rule: reduce the <G, CG> partials into tot[P_C2], form the quartic and
 // pick t.  mode 0: API (coeffs/t to the given pointers).  mode 1: inner loop.
 __global__ void __launch_bounds__(kFin)
-k_fin_step(const double* __restrict__ part_c2, int nb, DevScalars* __restrict__ sc_base, double sigma, int mode, double* __restrict__ coeffs_out, double* __restrict__ t_out, BlockTab tab) {
+k_fin_step(const double* __restrict__ part_c2, int nb, DevScalars* __restrict__ sc_base, double sigma, int mode,
+           double* __restrict__ coeffs_out, double* __restrict__ t_out, BlockTab tab) {
   const int q = blockIdx.x;
   DevScalars* sc = sc_base + q;
   if (mode == 1 && sc->flag) return;
@@ -138,8 +139,7 @@ k_fin_dual(const double* __restrict__ part, int nb, DevScalars* __restrict__ sc_
   if (pinf_out) *pinf_out = sc->pinf;
 }
 
-// Start of an inner solve: clear the flag and counters (a kernel, not a memset,
-// so that it can sit inside a captured graph).
+// Start of an inner solve: its limits, the flag and the counters.
 __global__ void k_inner_reset(DevScalars* sc, double tol, int max_inner, int step_rule, double eta) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     sc->flag = 0;

@@ -18,8 +18,8 @@ constexpr int kWsFeat = 8;    // features per vertex
 // neighbours' pairs (one random access per entry instead of one for each of two
 // tables) and writes whole feature rows.  Both walk a row with kWsLpr lanes and
 // kWsUnroll entries in flight per lane; the float sums of pass 2 still run over
-// a row in its order (each lane adds all of its row group's values in turn).  Pass 1 streams the cost, pass 2 is
-// bound by the gathers.  n = 1e6, 8e6 entries: 115 + 344 us with a thread per row
+// a row in its order (each lane adds all of its row group's values in turn).
+// Pass 1 streams the cost, pass 2 is bound by the gathers.  n = 1e6, 8e6 entries: 115 + 344 us with a thread per row
 // and two gathered tables, 24 + 98 us (82e9 gathers/s) now.
 constexpr int kWsLpr = 4;  // quad_lane below works on groups of four
 constexpr int kWsUnroll = 4;
@@ -249,7 +249,7 @@ __device__ __forceinline__ float ws_output(const float* __restrict__ S, int nin,
 }
 
 // Bound by the matrix cores (n = 1e6, h = 32: 20 instructions of 64 cycles per 32
-// vertices, 16 us of them): 313 us on the vector ALUs, 34 us (77 TFLOP/s) now.
+// vertices, 16 us of them): 313 us on the vector ALUs, 39 us (67 TFLOP/s) now.
 template <int H>
 __global__ void __launch_bounds__(kBlock)
 k_ws_forward(const float* __restrict__ P, int nin, const float* __restrict__ mu, const float* __restrict__ isd,
@@ -324,7 +324,7 @@ k_ws_pool_fin(const double* __restrict__ part, int nb, long n, double* __restric
 // extended by a column of ones, dW1 and db1 = [x 1]^T d1 (16 x 16 x 4 tiles).
 // The waves' gradients are added in wave order, the blocks' later in block
 // order, so the gradient is deterministic.  Bound by the matrix cores and LDS;
-// 262 144 rows, h = 32: 260 us on the vector ALUs, 34 us (61 TFLOP/s) now.
+// 262 144 rows, h = 32: 260 us on the vector ALUs, 43 us (48 TFLOP/s) now.
 template <int H>
 __global__ void __launch_bounds__(kBlock)
 k_ws_backward(const float* __restrict__ P, int nin, const float* __restrict__ mu, const float* __restrict__ isd, long n,
