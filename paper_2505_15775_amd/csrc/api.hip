@@ -823,16 +823,26 @@ extern "C" alm_bm_status alm_bm_cost_apply(alm_bm_problem* p, int32_t r, const v
   if (!p || !X || !P) return fail(ALM_BM_ERR_INVALID_ARG, "cost_apply: null argument");
   STCHK(check_r(p, r));
   if (p->d.j_coef != 0.0) return fail(ALM_BM_ERR_UNSUPPORTED, "cost_apply: cost with a -J term");
-  // Without <X, C X> there are no partial sums to add, and 64 rows a block leave fuller
-  // last trips than 1024 blocks do (n = 7e4, r = 4, FP64 11.3 -> 10.4 us; n = 1e5, r = 8
-  // 22.0 -> 21.2; n = 1.5e5, r = 8, BF16 16.3 -> 15.0; n = 1e6 the same within 1 %).  With
-  // it their addition costs more (n = 3e5, r = 8, FP64 65.3 us on 1024 blocks, 67.6 on
-  // 4096).  Not for skewed costs, nor on a grid that the caller chose.
-  int nb = p->nblk;
-  if (!xpx && !p->C64.skewed && nb == default_blocks(p))
-    nb = std::max(nb, (int)std::min<long>(4096, (p->d.n + 511) / 512 * 8));
   with_storage(p->d.precision, [&]<typename T>() {
     using V = typename Acc<T>::type;
+    // Without <X, C X> there are no partial sums to add, and up to 4096 blocks of 64 rows
+    // are ahead of the default grid (not of a grid that the caller chose) for short rows
+    // (r <= 8, in BF16 4 and 8) up to 128 rows a block, and where they take at most three
+    // quarters of the default grid's trips, whose last ones are nearly empty then (FP64
+    // beyond r = 16 fills the chip with 1024 blocks and pays more for a second round).
+    // Default / 64 rows a block, degree 10: n = 7e4, r = 4, FP64 12.1 / 11.1 us, r = 24,
+    // BF16 28.0 / 18.7, r = 33 55 / 44; n = 1e5, r = 5, FP64 33 / 23, r = 8 22.4 / 21.5;
+    // n = 2e5, r = 4, FP32 21.8 / 20.1; n = 4e5, r = 8, BF16 52.7 / 49.1.  Elsewhere either
+    // may be ahead: n = 1.3e5, r = 13, BF16 33 / 44, n = 7e4, r = 33, FP64 52 / 61, n = 3e5,
+    // r = 33, BF16 165 / 185, n = 1e6, r = 4, FP32 158 / 166.
+    int nb = p->nblk;
+    const int fine = (int)std::min<long>(4096, (p->d.n + 511) / 512 * 8);
+    if (!xpx && !p->C64.skewed && fine > nb && nb == default_blocks(p)) {
+      const int rpt = diag_rows_per_trip<T>(r, p->variant);
+      auto trips = [&](long k) { return k * (((p->d.n + k - 1) / k + rpt - 1) / rpt); };
+      const bool short_rows = (sizeof(T) > 2 ? r <= 8 : r == 4 || r == 8) && p->d.n <= 128L * fine;
+      if (short_rows || (4 * trips(fine) <= 3 * trips(nb) && !(sizeof(T) == 8 && r > 16))) nb = fine;
+    }
     launch_quadq_diag<T>(cost_of<T>(p), r, p->variant, static_cast<const T*>(X), static_cast<V*>(P), p->part_c2,
                          nullptr, p->tab, nb, st);
     if (xpx) launch_fin_sum(p->part_c2, nb, xpx, 0, st);

@@ -436,6 +436,13 @@ static void launch_objgrad_cfg(const Cost<typename Acc<T>::type>& C, int r, cons
                        sigma, G, Av, part, sc, refresh_every, tab, lb);
 }
 
+template <typename T, int LPR, int VEC> static void rows_per_trip_cfg(int& rows) { rows = kBlock / LPR; }
+template <typename T> int diag_rows_per_trip(int r, int variant) {
+  int rows = 0;
+  ALMBM_DISPATCH_DIAG(T, rows_per_trip_cfg, rows);
+  return rows;
+}
+
 template <typename T, int LPR, int VEC>
 static void launch_quadq_cfg(const Cost<typename Acc<T>::type>& C, int r, const T* G, typename Acc<T>::type* Q,
                              double* part, const DevScalars* sc, const BlockTab& tab, int nblk, hipStream_t st,
@@ -535,6 +542,7 @@ void launch_ls_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, co
   template void launch_objgrad_diag<T>(const Cost<Acc<T>::type>&, int, int, const T*, const double*,      \
                                        const double*, double, T*, double*, double*, const DevScalars*, int, \
                                        const BlockTab&, int, hipStream_t, const LbfgsRing<RingT<T>>&);    \
+  template int diag_rows_per_trip<T>(int, int);                                                            \
   template void launch_quadq_diag<T>(const Cost<Acc<T>::type>&, int, int, const T*, Acc<T>::type*, double*, \
                                      const DevScalars*, const BlockTab&, int, hipStream_t,                 \
                                      const LbfgsRing<T>&, const SideFin&);                                 \

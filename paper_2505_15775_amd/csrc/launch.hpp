@@ -52,6 +52,8 @@ void launch_lbfgs_combine(long n, int r, int variant, const T* R, const T* G, co
 // Direction-dependent totals of the quartic from the combine partials (one block per instance).
 void launch_fin_lsdir(const double* part, int nb, DevScalars* sc, LbfgsState* s, hipStream_t st,
                       const BlockTab& tab = BlockTab{}, int count = 1);
+// Rows that a block of the row kernels takes at a time at rank r.
+template <typename T> int diag_rows_per_trip(int r, int variant);
 template <typename T>
 void launch_quad_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, const T* G, double* part,
                       const DevScalars* sc, int nblk, hipStream_t st);

@@ -97,20 +97,25 @@ def test_default_grid_of_a_handle(kind):
         assert _bits(p, R, y) == few  # a grid that the caller chose stays
 
 
-@pytest.mark.parametrize("n", [511, 513, 8191, 70001, 262145, 300001])
-def test_product_on_either_grid(n):
+@pytest.mark.parametrize("n,r,prec", [(511, 5, "f64"), (513, 5, "f64"), (8191, 5, "f64"), (70001, 5, "f64"),
+                                      (70001, 24, "bf16"), (70001, 40, "f32"), (262145, 5, "f64"), (300001, 8, "bf16"),
+                                      (530000, 3, "f32")])
+def test_product_on_either_grid(n, r, prec):
     """C X with and without <X, C X>: the same rows on both grids (sizes around 64 rows a block, 1024 blocks and
-    4096), against the oracle.  Sums of a few products in FP64: 1e-13 of the largest."""
+    4096, and those where only one grid is used), against the oracle.  Sums of a few products of exact entries: FP64
+    1e-13 of the largest, float 1e-6."""
     m = _almbm()
     g = gen.er_graph(n, 3 * n, 3, "gauss")
-    p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=5, lanczos_kmax=0, device=DEV)
-    X = np.random.default_rng(n).standard_normal((n, 5))
-    P_o = oracle.cost_apply(oracle.maxcut_sdp(g), X)
-    P = p.cost_apply(p.factor(X)).cpu().numpy()
-    Q, xpx = p.cost_apply(p.factor(X), want_xpx=True)
-    assert np.abs(P - P_o).max() <= 1e-13 * np.abs(P_o).max()
+    p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision=prec, r_max=r, lanczos_kmax=0, device=DEV)
+    X = p.factor(np.random.default_rng(n).standard_normal((n, r)))
+    P_o = oracle.cost_apply(oracle.maxcut_sdp(g), X.double().cpu().numpy())
+    P = p.cost_apply(X).cpu().numpy()
+    Q, xpx = p.cost_apply(X, want_xpx=True)
+    tol = 1e-13 if prec == "f64" else 1e-6
+    assert np.abs(P - P_o).max() <= tol * np.abs(P_o).max()
     assert P.tobytes() == Q.cpu().numpy().tobytes()
-    assert abs(xpx.item() - (X * P_o).sum()) <= 1e-12 * np.abs(X * P_o).sum()
+    terms = X.double().cpu().numpy() * P_o
+    assert abs(xpx.item() - terms.sum()) <= 10 * tol * np.abs(terms).sum()
 
 
 def test_features_beside_the_handles_other_calls():
