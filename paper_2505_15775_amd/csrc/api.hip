@@ -689,12 +689,12 @@ extern "C" alm_bm_status alm_bm_destroy(alm_bm_problem* p) {
 // f, G (nullable), Av (nullable) at (R, y): one objective/gradient evaluation.
 template <typename T>
 static void enqueue_objgrad(alm_bm_problem* p, int r, const T* R, const double* y, double sigma, T* G, double* Av,
-                            DevScalars* sc, int mode, double* f_out, hipStream_t st) {
+                            DevScalars* sc, int mode, double* f_out, hipStream_t st, int nb = 0) {
   const auto& d = p->d;
   if (d.cons_kind == ALM_BM_CONS_DIAG) {
-    launch_objgrad_diag<T>(cost_of<T>(p), r, p->variant, R, y, d.b, sigma, G, Av, p->part, sc, 0, p->tab, p->nblk,
-                           st);
-    launch_fin_objgrad(p->part, p->nblk, sc, sigma, mode, f_out, st, p->tab, p->count);
+    if (nb == 0) nb = p->nblk;
+    launch_objgrad_diag<T>(cost_of<T>(p), r, p->variant, R, y, d.b, sigma, G, Av, p->part, sc, 0, p->tab, nb, st);
+    launch_fin_objgrad(p->part, nb, sc, sigma, mode, f_out, st, p->tab, p->count);
   } else {
     launch_edges_eval<T>(cost_of<T>(p), p->adj, d.n, r, p->variant, R, y, d.b, sigma, d.trace_coef, d.j_coef, p->rho,
                          Av, p->wE, nullptr, G, p->part, sc, p->nblk, mode, f_out, st);
@@ -806,12 +806,19 @@ static alm_bm_status check_r(const alm_bm_problem* p, int r) {
 
 // --------------------------------------------------------------------- API: per call
 
+// Grid of a call's passes: the handle's, or on its default grid what suits the rank.
+template <typename T> static int call_blocks(const alm_bm_problem* p, int r) {
+  if (p->d.cons_kind != ALM_BM_CONS_DIAG || p->C64.skewed || p->nblk != default_blocks(p)) return p->nblk;
+  return diag_call_blocks<T>(p->d.n, r, p->variant, p->nblk);
+}
+
 extern "C" alm_bm_status alm_bm_objective_grad(alm_bm_problem* p, int32_t r, const void* R, const double* y,
                                                double sigma, double* f, void* G, double* Av, hipStream_t st) {
   if (!p || !R || !y || !f) return fail(ALM_BM_ERR_INVALID_ARG, "objective_grad: null argument");
   STCHK(check_r(p, r));
   with_storage(p->d.precision, [&]<typename T>() {
-    enqueue_objgrad<T>(p, r, static_cast<const T*>(R), y, sigma, static_cast<T*>(G), Av, p->sc_api, 0, f, st);
+    enqueue_objgrad<T>(p, r, static_cast<const T*>(R), y, sigma, static_cast<T*>(G), Av, p->sc_api, 0, f, st,
+                       call_blocks<T>(p, r));
     return 0;
   });
   HIPCHK(hipGetLastError());
@@ -862,8 +869,9 @@ extern "C" alm_bm_status alm_bm_line_search(alm_bm_problem* p, int32_t r, const 
     const T* Rt = static_cast<const T*>(R);
     const T* Gt = static_cast<const T*>(G);
     if (d.cons_kind == ALM_BM_CONS_DIAG) {
-      launch_ls_diag<T>(cost_of<T>(p), r, p->variant, Rt, Gt, y, d.b, p->part, p->nblk, st);
-      launch_fin_ls(p->part, p->nblk, p->sc_api, sigma, coeffs, t_star, st);
+      const int nb = call_blocks<T>(p, r);
+      launch_ls_diag<T>(cost_of<T>(p), r, p->variant, Rt, Gt, y, d.b, p->part, nb, st);
+      launch_fin_ls(p->part, nb, p->sc_api, sigma, coeffs, t_star, st);
     } else {
       DevScalars* sc = p->sc_api;
       launch_edges_eval<T>(cost_of<T>(p), p->adj, d.n, r, p->variant, Rt, y, d.b, sigma, d.trace_coef, d.j_coef, 1.0,
@@ -886,10 +894,11 @@ extern "C" alm_bm_status alm_bm_gd_step(alm_bm_problem* p, int32_t r, void* R, c
     T* Rt = static_cast<T*>(R);
     T* Gt = G ? static_cast<T*>(G) : static_cast<T*>(p->G);
     DevScalars* sc = p->sc_api;
-    enqueue_objgrad<T>(p, r, Rt, y, sigma, Gt, p->Av, sc, 0, f, st);
+    const int nb = call_blocks<T>(p, r);
+    enqueue_objgrad<T>(p, r, Rt, y, sigma, Gt, p->Av, sc, 0, f, st, nb);
     if (d.cons_kind == ALM_BM_CONS_DIAG) {
-      launch_quad_diag<T>(cost_of<T>(p), r, p->variant, Gt, p->part_c2, sc, p->nblk, st);
-      launch_fin_step(p->part_c2, p->nblk, sc, sigma, 0, nullptr, t, st);
+      launch_quad_diag<T>(cost_of<T>(p), r, p->variant, Gt, p->part_c2, sc, nb, st);
+      launch_fin_step(p->part_c2, nb, sc, sigma, 0, nullptr, t, st);
     } else {
       launch_edges_p3<T>(cost_of<T>(p), p->adj, r, p->variant, Rt, Gt, y, d.b, p->Av, p->part, sc, p->nblk, st);
       launch_fin_edges3(p->part, p->nblk, r, sc, y, d.b, sigma, d.trace_coef, d.j_coef, 0, nullptr, t, st);

@@ -10,6 +10,8 @@
 // work is a sparse gather at ~2r flop per 12 B of matrix plus r*sizeof(T) of
 // gathered row, far below the vector ALU balance, so the kernels are bound by
 // HBM/Infinity-Cache bandwidth.
+#include <algorithm>
+
 #include "finalize.hpp"
 #include "spmm_row.hpp"
 
@@ -443,6 +445,31 @@ template <typename T> int diag_rows_per_trip(int r, int variant) {
   return rows;
 }
 
+// Rows of a partial tile with one column per lane (FP64 r = 1..3 and 5..7, FP32 r = 1..3)
+// cost a trip's latency rather than its bytes, and the 1024 blocks of the default grid
+// leave a last trip that is nearly empty (n = 1e5, r = 5: 98 rows, trips of 32).  Such
+// calls take chunks of whole trips, if that needs at most 1280 blocks or saves a quarter
+// of the trips; with trips of 32 rows (r > 4) rather 64 rows a block, if that saves a
+// tenth of them and more than the former.  Beyond 512 rows a block a trip no longer
+// shows.  Inner steps keep one grid for all their passes.
+// Evaluation and line search, default -> here, FP64: n = 7e4, r = 3 20.5 -> 17.6 and 36.6
+// -> 27.9 us; n = 1e5, r = 5 39.5 -> 30.8 and 73.4 -> 52.0; n = 1.6e5, r = 3 36.8 -> 33.3
+// and 65.5 -> 56.2; n = 2e5, r = 7 72.8 -> 65.1 and 133 -> 110; n = 3e5, r = 5 100 -> 93
+// and 185 -> 171.  Left as they are: n = 1.15e5, r = 3 26.6 on 1024 blocks, 28.8 on 1800.
+template <typename T> int diag_call_blocks(long n, int r, int variant, int nb) {
+  const bool narrow = sizeof(T) == 8 ? r < 8 && r != 4 : sizeof(T) == 4 && r < 4;
+  if (!narrow || variant != 0 || n > (1L << 19)) return nb;
+  const int rpt = diag_rows_per_trip<T>(r, variant);
+  auto trips = [&](long k) { return k * (((n + k - 1) / k + rpt - 1) / rpt); };
+  const long whole = (n + nb - 1) / nb / rpt * rpt;
+  if (whole == 0) return nb;
+  const long even = ((n + whole - 1) / whole + 7) / 8 * 8, fine = (n + 511) / 512 * 8;
+  const bool few = even <= 1280;
+  if (r > 4 && fine <= 4096 && 10 * trips(fine) <= 9 * trips(nb) && !(few && trips(even) <= trips(fine)))
+    return (int)fine;
+  return (few ? trips(even) < trips(nb) : 4 * trips(even) <= 3 * trips(nb)) ? (int)std::max<long>(even, nb) : nb;
+}
+
 template <typename T, int LPR, int VEC>
 static void launch_quadq_cfg(const Cost<typename Acc<T>::type>& C, int r, const T* G, typename Acc<T>::type* Q,
                              double* part, const DevScalars* sc, const BlockTab& tab, int nblk, hipStream_t st,
@@ -542,6 +569,7 @@ void launch_ls_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, co
   template void launch_objgrad_diag<T>(const Cost<Acc<T>::type>&, int, int, const T*, const double*,      \
                                        const double*, double, T*, double*, double*, const DevScalars*, int, \
                                        const BlockTab&, int, hipStream_t, const LbfgsRing<RingT<T>>&);    \
+  template int diag_call_blocks<T>(long, int, int, int);                                                   \
   template int diag_rows_per_trip<T>(int, int);                                                            \
   template void launch_quadq_diag<T>(const Cost<Acc<T>::type>&, int, int, const T*, Acc<T>::type*, double*, \
                                      const DevScalars*, const BlockTab&, int, hipStream_t,                 \

@@ -54,6 +54,8 @@ void launch_fin_lsdir(const double* part, int nb, DevScalars* sc, LbfgsState* s,
                       const BlockTab& tab = BlockTab{}, int count = 1);
 // Rows that a block of the row kernels takes at a time at rank r.
 template <typename T> int diag_rows_per_trip(int r, int variant);
+// Grid of a single evaluation or line search where nb is the default grid for n rows.
+template <typename T> int diag_call_blocks(long n, int r, int variant, int nb);
 template <typename T>
 void launch_quad_diag(const Cost<typename Acc<T>::type>& C, int r, int variant, const T* G, double* part,
                       const DevScalars* sc, int nblk, hipStream_t st);

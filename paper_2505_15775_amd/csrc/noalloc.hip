@@ -76,7 +76,7 @@ extern "C" alm_bm_status alm_bm_objective_grad_noalloc(const alm_bm_problem_desc
     return set_error(ALM_BM_ERR_INVALID_ARG, "objective_grad_noalloc: ELL needs nnz = n * ell_width");
   if (d.ell_width == 0 && d.nnz > 0 && !d.row_ptr)
     return set_error(ALM_BM_ERR_INVALID_ARG, "objective_grad_noalloc: CSR needs row_ptr");
-  const int nblk = row_blocks(d.n);
+  const int nblk = diag_call_blocks<double>(d.n, r, 0, row_blocks(d.n));
   if (nblk > kScratchBlocks)
     return set_error(ALM_BM_ERR_INVALID_ARG, "objective_grad_noalloc: grid larger than the scratch array");
   double* base = nullptr;

@@ -192,3 +192,35 @@ def test_direction_totals_in_a_block_or_a_kernel(blocks):
         ends.append(p.inner_solve(R, y, 0.0, 8, sigma=1.0, inner_solver=m._lib.INNER_LBFGS, lbfgs_memory=3))
     assert ends[0][:2] == ends[1][:2] == (8, 2)
     assert abs(ends[0][2] - ends[1][2]) <= 1e-9 * abs(ends[0][2])
+
+
+@pytest.mark.parametrize("n,r", [(65537, 1), (70001, 3), (85003, 6), (100000, 5), (115001, 7), (160001, 5), (200003, 2),
+                                 (300001, 7), (530003, 3)])
+def test_narrow_rows_on_the_grid_of_a_call(n, r):
+    """Ranks whose rows hold one column per lane, over the grids that a single call takes for them (whole trips, 64
+    rows a block, the default): evaluation, line search and gradient step against the oracle, and the handle-free
+    evaluation with the same bits.  FP64 sums of n r products: 1e-12 relative covers any order."""
+    m = _almbm()
+    g = gen.er_graph(n, 3 * n, 3, "gauss")
+    po = oracle.maxcut_sdp(g)
+    p = m.Problem.maxcut(g.n, g.ei, g.ej, g.w, precision="f64", r_max=8, lanczos_kmax=0, device=DEV)
+    rng = np.random.default_rng(n)
+    R, D, y = rng.standard_normal((n, r)), rng.standard_normal((n, r)), rng.standard_normal(n)
+    Rd, yd = p.factor(R), torch.from_numpy(y).to(DEV)
+    f_o, G_o, a_o, _ = oracle.objective_grad(po, R, y, 1.3)
+    f, G, Av = p.objective_grad(Rd, yd, 1.3)
+    assert abs(f.item() - f_o) <= 1e-12 * abs(f_o) + 1e-10
+    assert np.linalg.norm(G.cpu().numpy() - G_o) <= 1e-12 * np.linalg.norm(G_o)
+    assert np.linalg.norm(Av.cpu().numpy() - a_o) <= 1e-12 * np.linalg.norm(a_o)
+    f2, G2, Av2 = torch.zeros_like(f), torch.zeros_like(G), torch.zeros_like(Av)
+    m.objective_grad_noalloc(p.desc, Rd, yd, 1.3, f2, G2, Av2)
+    assert f2.item() == f.item() and torch.equal(G2, G) and torch.equal(Av2, Av)
+    k, _ = p.line_search(Rd, p.factor(D), yd, 1.3)
+    k_o = oracle.line_search_coeffs(po, R, D, y, 1.3)
+    np.testing.assert_allclose(k.cpu().numpy(), k_o, rtol=1e-10, atol=1e-10 * float(np.max(np.abs(k_o))))
+    t = torch.zeros(1, dtype=torch.float64, device=DEV)
+    S = Rd.clone()
+    p.gd_step(S, yd, 1.3, t=t)
+    _, t_ls = p.line_search(Rd, G, yd, 1.3)
+    assert abs(t.item() - t_ls.item()) <= 1e-9 * abs(t_ls.item())
+    assert (S - (Rd - t_ls * G)).norm() <= 1e-9 * S.norm()
